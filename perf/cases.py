@@ -1,0 +1,253 @@
+"""The work a user has this library do, as cases that can be timed.
+
+A case is one pass through the public entry points: the gate, dispatch, expert FFN and combine of a
+failure-remapped MoE layer (eagerly or as the captured graph a serving loop replays), the same step
+right after a map update (the recovery), and the routing side of the lost-expert study.
+
+listed()          the cases
+draw(rng)         one more case of the same ranges
+prepare(c, seed)  layer, placement, map, weights, inputs, output buffers and (where used) the graph
+run(state)        one pass; returns what it computed
+work(c)           bytes and flops the pass cannot do without
+tolerance(c)      how far another correct implementation may be away
+"""
+from __future__ import annotations
+
+import math
+from types import SimpleNamespace
+
+import numpy as np
+import torch
+
+from paper_2602_21140_amd import ReviveLayer
+
+DEVICE = "cuda:0"
+
+# Layer shapes of the five workloads (placement and failed ranks are derived below).
+_TINY = dict(dtype="fp32", H=256, E=16, k=2, I=128, I_shared=0, n_ranks=4, slots_per_rank=5, score_fn="softmax", n_group=1,
+             topk_group=1, n_failed=1)
+_MID = dict(dtype="bf16", H=2048, E=64, k=6, I=1408, I_shared=2816, n_ranks=8, slots_per_rank=9, score_fn="softmax", n_group=1,
+            topk_group=1, n_failed=1)
+_LARGE = dict(dtype="bf16", H=7168, E=256, k=8, I=2048, I_shared=2048, n_ranks=32, slots_per_rank=9, score_fn="sigmoid",
+              n_group=8, topk_group=4, n_failed=1)
+_WIDE = dict(dtype="bf16", H=7168, E=384, k=8, I=2048, I_shared=2048, n_ranks=48, slots_per_rank=9, score_fn="softmax",
+             n_group=1, topk_group=1, n_failed=2)
+
+
+def _case(name, shape, T, kind="layer", graph=True, skew=0.0, static_scratch=False, **changes):
+    return dict(shape, name=name, kind=kind, T=T, graph=graph, skew=skew, static_scratch=static_scratch, **changes)
+
+
+def listed():
+    return [
+        # the fp32 layer at its smallest: a correctness or debugging run, called eagerly; launches and latency are all of it
+        _case("fp32_tiny", _TINY, 64, graph=False),
+        # an fp32 layer of ordinary size with a ragged token count (a run that wants fp32 results)
+        _case("fp32_mid", _TINY, 1001, H=1024, E=32, k=4, I=512, I_shared=512, n_ranks=8, graph=False),
+        # single-stream decode: one token, eight experts out of 256; every launch and every latency shows
+        _case("decode_1", _LARGE, 1),
+        # small decode batches: a few rows per expert, the experts' weights are streamed once
+        _case("decode_24", _LARGE, 24),
+        _case("decode_192", _LARGE, 192),
+        # an eager step of a smaller layer with an odd batch, by a caller that allocates nothing
+        _case("eager_37", _MID, 37, graph=False, static_scratch=True),
+        # a ragged chunk with uneven expert load: slots with no rows beside slots with hundreds
+        _case("chunk_skewed", _LARGE, 1003, skew=0.3),
+        # a prefill step of the smaller layer
+        _case("prefill_mid", _MID, 4096),
+        # a large batch after three ranks have failed: some experts lost every copy
+        _case("batch_lost", _LARGE, 8192, n_failed=3),
+        # the largest prefill chunk one GPU holds: 384 experts, two ranks failed
+        _case("prefill_large", _WIDE, 32768),
+        # recovery: a rank fails, the map is updated and the next decode step runs under it
+        _case("recover", _MID, 64, kind="recover"),
+        # lost-expert study: routing of given logits under a mask, with activation counts
+        _case("study", _LARGE, 8192, kind="study", n_failed=3),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """A case of the same ranges, without a name: 1 to 8192 tokens, hidden sizes 256 to 7168, 8 to 256 experts."""
+    while True:
+        kind = rng.choice(["layer"] * 8 + ["recover", "study"])
+        fp32 = kind == "layer" and rng.random() < 0.2
+        if fp32:
+            H, I = 8 * _log_int(rng, 16, 128), 4 * _log_int(rng, 16, 128)
+            I_shared = rng.choice([0, I])
+            E, T = rng.choice([8, 16, 32]), _log_int(rng, 1, 1024)
+        else:
+            H, I = 64 * _log_int(rng, 4, 112), 64 * _log_int(rng, 2, 32)
+            I_shared = rng.choice([0, I, I, 2 * I])
+            E, T = rng.choice([16, 32, 64, 128, 192, 256]), _log_int(rng, 1, 8192)
+        per = rng.choice([2, 4, 8])
+        n_group = rng.choice([1, 1, 4, 8])
+        c = dict(kind=kind, dtype="fp32" if fp32 else "bf16", T=T, H=H, E=E, k=rng.randint(1, min(8, E // 4)), I=I,
+                 I_shared=I_shared, n_ranks=E // per, slots_per_rank=per + 1, score_fn=rng.choice(["softmax", "sigmoid"]),
+                 n_group=n_group, topk_group=max(1, n_group // 2), n_failed=rng.choice([0, 1, 1, 2]),
+                 graph=not fp32 and rng.random() < 0.7, skew=rng.choice([0.0, 0.0, 0.3]), static_scratch=False)
+        c["n_failed"] = min(c["n_failed"], c["n_ranks"] - 1)
+        if kind == "recover":
+            c["graph"] = True
+        c["static_scratch"] = not c["graph"] and c["T"] * c["k"] <= 65536 and rng.random() < 0.5
+        if _reachable(c) and c["T"] * 3 * H * (c["k"] * I + I_shared) < 8192 * 3 * 7168 * 2048 * 9:
+            return c
+
+
+# ---- placement, as the library's users build it: primaries rank by rank, each rank's spare slots
+# copy the first primaries of the next rank ------------------------------------------------------
+
+def _placement(c):
+    per = c["E"] // c["n_ranks"]
+    S, R = c["slots_per_rank"], c["n_ranks"]
+    p2l = np.full(R * S, -1, dtype=np.int32)
+    for r in range(R):
+        p2l[r * S:r * S + per] = np.arange(r * per, (r + 1) * per)
+        for j in range(S - per):
+            p2l[r * S + per + j] = ((r + 1) % R) * per + j % per
+    return p2l
+
+
+def _failed(c):
+    m = np.zeros(c["n_ranks"], dtype=np.uint8)
+    for i in range(c["n_failed"]):
+        m[(2 * i + 1) * c["n_ranks"] // (2 * c["n_failed"])] = 1
+    return m
+
+
+def _replicas(c):
+    """Live copies of every expert, and the expert of every live slot."""
+    p2l = _placement(c)
+    live = p2l[np.repeat(_failed(c) == 0, c["slots_per_rank"])]
+    return np.bincount(live, minlength=c["E"]), live
+
+
+def _reachable(c):
+    """Every token can still be given k live experts."""
+    per_group = np.sort((_replicas(c)[0] > 0).reshape(c["n_group"], -1).sum(axis=1))
+    per_group = per_group[per_group > 0]
+    return per_group[:c["topk_group"]].sum() >= c["k"]
+
+
+# ---- the state a user's program holds ------------------------------------------------------------
+
+def _normal(gen, shape, std, dtype):
+    return torch.empty(shape, dtype=dtype, device=DEVICE).normal_(0.0, std, generator=gen)
+
+
+def _padded(rows, dtype):
+    return rows if dtype == torch.float32 else -(-rows // 128) * 128  # bf16 matrices are stored in whole 128-row panels
+
+
+def _expert(gen, H, I, dtype):
+    """Weights in the library's packed layout.  They are drawn in it: the elements are independent."""
+    std = H ** -0.5
+    rows = _padded(I, dtype)
+    gu = _normal(gen, (2 * rows, H), std, dtype)
+    dn = _normal(gen, (_padded(H, dtype), I), std, dtype)
+    if dtype == torch.bfloat16:  # padding rows are zero
+        for m, valid in ((gu[:rows], I), (gu[rows:], I), (dn, H)):
+            if m.shape[0] != valid:
+                panel = m[m.shape[0] - 128:].view(-1, 128, 32)  # the last panel, [K/32][128][32]
+                panel[:, valid % 128:, :] = 0
+    return gu, dn
+
+
+def prepare(case, seed):
+    c = SimpleNamespace(**case)
+    gen = torch.Generator(device=DEVICE)
+    gen.manual_seed(seed * 7919 + 17)
+    dtype = torch.bfloat16 if c.dtype == "bf16" else torch.float32
+    p2l = _placement(case)
+    c.max_replicas = int(np.bincount(p2l, minlength=c.E).max())
+    L = ReviveLayer(c, device=DEVICE)
+    L.set_placement(p2l)
+    s = SimpleNamespace(c=c, L=L, failed=_failed(case), graph=None)
+    L.update_map(s.failed)
+    T, k, N = c.T, c.k, c.T * c.k
+    s.logits = L.empty(T, c.E, dtype=torch.float32)
+    s.top = (L.empty(T, k, dtype=torch.int32), L.empty(T, k, dtype=torch.float32), L.empty(T, k, dtype=torch.int32))
+    if c.kind == "study":
+        s.logits.normal_(0.0, 1.0, generator=gen)
+        s.counts = torch.zeros(c.E, dtype=torch.int64, device=DEVICE)
+        return s
+    s.x = _normal(gen, (T, c.H), 1.0, dtype)
+    w = _normal(gen, (c.E, c.H), c.H ** -0.5, torch.float32)
+    if c.skew:  # some experts' logits spread wider and win more often
+        w *= torch.exp(c.skew * _normal(gen, (c.E, 1), 1.0, torch.float32))
+    s.w_router = w.to(dtype)
+    gu, dn = [None] * len(p2l), [None] * len(p2l)
+    for e in range(c.E):
+        slots = np.nonzero(p2l == e)[0]
+        gu[slots[0]], dn[slots[0]] = _expert(gen, c.H, c.I, dtype)
+        for p in slots[1:]:  # a replica holds the same bits in memory of its own
+            gu[p], dn[p] = gu[slots[0]].clone(), dn[slots[0]].clone()
+    L.set_expert_weights(gu, dn)
+    s.shared = _expert(gen, c.H, c.I_shared, dtype) if c.I_shared else (None, None)
+    s.disp = (L.empty(N, c.H), L.empty(L.P + 1, dtype=torch.int32), L.empty(N, dtype=torch.int32), L.empty(N, dtype=torch.int32))
+    s.y = (L.empty(N, c.H), L.empty(T, c.H) if c.I_shared else None)
+    s.out = L.empty(T, c.H)
+    if c.graph:
+        stream = torch.cuda.Stream(device=DEVICE)
+        stream.wait_stream(torch.cuda.current_stream())
+        L.graph_begin(stream)
+        _step(s, stream)
+        s.graph = L.graph_end(stream)
+    return s
+
+
+def _step(s, stream=None):
+    c, L = s.c, s.L
+    L.route(s.x, s.w_router, c.T, logits=s.logits, out=s.top, stream=stream)
+    L.dispatch(s.x, s.top[2], c.T, out=s.disp, static_scratch=c.static_scratch, stream=stream)
+    L.expert_ffn(s.disp[0], s.disp[1], c.T, x=s.x, w_sh_gate_up=s.shared[0], w_sh_down=s.shared[1], out=s.y, stream=stream)
+    L.combine(s.y[0], s.disp[2], s.top[1], s.y[1], c.T, out=s.out, stream=stream)
+
+
+def run(state):
+    s = state
+    if s.c.kind == "study":
+        s.counts.zero_()
+        s.L.route(None, None, s.c.T, logits=s.logits, logits_given=True, out=s.top)
+        s.L.expert_counts(s.top[0], s.c.T, counts=s.counts)
+        return {"experts": s.top[0], "weights": s.top[1], "slots": s.top[2], "counts": s.counts}
+    if s.c.kind == "recover":
+        s.L.update_map(s.failed)
+    if s.graph is not None:
+        s.L.graph_launch(s.graph, torch.cuda.current_stream())
+    else:
+        _step(s)
+    return {"out": s.out, "logits": s.logits, "experts": s.top[0], "weights": s.top[1], "slots": s.top[2]}
+
+
+def work(case):
+    """Each call's inputs read once and its outputs written once; of the weights, those of the slots that a token is
+    expected to reach (even load).  The FFN's intermediate is the library's own and is not counted."""
+    c = SimpleNamespace(**case)
+    b = 2 if c.dtype == "bf16" else 4
+    T, N = c.T, c.T * c.k
+    if c.kind == "study":
+        return {"bytes": 4 * T * c.E + 12 * N + 4 * N + 8 * c.E, "flops": 0}
+    count, live = _replicas(case)
+    hit = 1.0 - (1.0 - c.k / (np.count_nonzero(count) * count[live])) ** T
+    weights = (hit.sum() * 3 * c.I + 3 * c.I_shared) * c.H * b
+    sh = T * c.H * b if c.I_shared else 0
+    route = T * c.H * b + c.E * c.H * b + 4 * T * c.E + 12 * N
+    dispatch = (T + N) * c.H * b + 12 * N
+    ffn = 2 * N * c.H * b + 2 * sh + weights
+    combine = (N + T) * c.H * b + sh + 8 * N
+    flops = 2 * T * c.H * c.E + 6 * N * c.H * c.I + 6 * T * c.H * c.I_shared
+    return {"bytes": int(route + dispatch + ffn + combine), "flops": int(flops)}
+
+
+def tolerance(case):
+    """About four times what the library shows against the same path in 64 bits.  bf16 (the intermediate, the expert outputs
+    and the result are rounded once each): 2.9e-3 at every shape.  fp32 (sums of up to a thousand products): 1.0e-6.  Whole
+    values (experts, slots) may differ where two logits tie within the rounding of the router product; on given logits
+    there is no such product and whole values stay the same."""
+    if case["kind"] == "study":
+        return {"rel": 1e-6, "differ": 0.0}
+    return {"rel": 1e-2 if case["dtype"] == "bf16" else 5e-6, "differ": 1e-3}
