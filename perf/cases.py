@@ -10,6 +10,7 @@ prepare(c, seed)  layer, placement, map, weights, inputs, output buffers and (wh
 run(state)        one pass; returns what it computed
 work(c)           bytes and flops the pass cannot do without
 tolerance(c)      how far another correct implementation may be away
+exact(c, seed)    what run() returns for these inputs, in 64 bits and plain torch
 """
 from __future__ import annotations
 
@@ -251,3 +252,69 @@ def tolerance(case):
     if case["kind"] == "study":
         return {"rel": 1e-6, "differ": 0.0}
     return {"rel": 1e-2 if case["dtype"] == "bf16" else 5e-6, "differ": 1e-3}
+
+
+# ---- the same pass in 64 bits, by the definition of the layer -----------------------------------
+
+def _unpacked(m, rows, dtype):
+    """The first `rows` rows of a matrix in the packed layout, row-major in 64 bits."""
+    K = m.shape[1]
+    if dtype == torch.bfloat16:
+        m = m.view(-1, K // 32, 128, 32).transpose(1, 2).reshape(-1, K)
+    return m[:rows].double()
+
+
+def _swiglu(x, gu, dn, H, I, dtype):
+    half = _padded(I, dtype)
+    g, u = (x @ _unpacked(m, I, dtype).T for m in (gu[:half], gu[half:]))
+    return (torch.nn.functional.silu(g) * u) @ _unpacked(dn, H, dtype).T
+
+
+def exact(case, seed):
+    c = SimpleNamespace(**case)
+    gen = torch.Generator(device=DEVICE)
+    gen.manual_seed(seed * 7919 + 17)
+    dtype = torch.bfloat16 if c.dtype == "bf16" else torch.float32
+    T, E, k = c.T, c.E, c.k
+    if c.kind == "study":
+        logits = torch.empty(T, E, dtype=torch.float32, device=DEVICE).normal_(0.0, 1.0, generator=gen).double()
+    else:
+        x = _normal(gen, (T, c.H), 1.0, dtype)
+        w = _normal(gen, (E, c.H), c.H ** -0.5, torch.float32)
+        if c.skew:
+            w *= torch.exp(c.skew * _normal(gen, (E, 1), 1.0, torch.float32))
+        x = x.double()
+        logits = x @ w.to(dtype).double().T
+    # gate: lost experts are out, the best groups are kept, the k best experts of those are taken
+    score = torch.sigmoid(logits) if c.score_fn == "sigmoid" else torch.softmax(logits, dim=1)
+    live = torch.from_numpy(_replicas(case)[0] > 0).to(DEVICE)
+    sel = score.masked_fill(~live, -math.inf)
+    if c.n_group > 1:
+        two = sel.view(T, c.n_group, -1).topk(2, dim=2).values
+        group = torch.where(two[:, :, 1] > -math.inf, two.sum(dim=2), two[:, :, 0])
+        keep = torch.zeros(T, c.n_group, dtype=torch.bool, device=DEVICE).scatter_(1, group.topk(c.topk_group, dim=1).indices, True)
+        sel = sel.masked_fill(~keep.repeat_interleave(E // c.n_group, dim=1), -math.inf)
+    experts = sel.topk(k, dim=1).indices
+    weights = score.gather(1, experts)
+    weights = weights / weights.sum(dim=1, keepdim=True)
+    # copy: token t takes the (t mod copies)-th live slot of its expert
+    p2l, failed = _placement(case), np.repeat(_failed(case), c.slots_per_rank)
+    table = [np.nonzero((p2l == e) & (failed == 0))[0] for e in range(E)]
+    cnt = torch.tensor([max(1, len(t)) for t in table], device=DEVICE)
+    most = max(len(t) for t in table)
+    flat = torch.tensor([[int(t[j % len(t)]) if len(t) else -1 for j in range(most)] for t in table], device=DEVICE)
+    slots = flat[experts, torch.arange(T, device=DEVICE)[:, None] % cnt[experts]]
+    res = {"experts": experts.int(), "weights": weights, "slots": slots.int()}
+    if c.kind == "study":
+        return dict(res, counts=torch.bincount(experts.flatten(), minlength=E))
+    out = torch.zeros(T, c.H, dtype=torch.float64, device=DEVICE)
+    for e in range(E):
+        gu, dn = _expert(gen, c.H, c.I, dtype)
+        t, j = torch.nonzero(experts == e, as_tuple=True)
+        if len(t):
+            out.index_add_(0, t, weights[t, j, None] * _swiglu(x[t], gu, dn, c.H, c.I, dtype))
+    if c.I_shared:
+        gu, dn = _expert(gen, c.H, c.I_shared, dtype)
+        for a in range(0, T, 8192):
+            out[a:a + 8192] += _swiglu(x[a:a + 8192], gu, dn, c.H, c.I_shared, dtype)
+    return dict(res, out=out, logits=logits)
