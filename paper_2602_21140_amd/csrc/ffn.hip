@@ -10,6 +10,7 @@
 // grids cover floor(N / tile) + P tiles; workgroups beyond the list's end exit at once.
 #include "gemm_bf16.hpp"
 #include "gemm_f32.hpp"
+#include "gemm_stream.hpp"
 
 namespace revive {
 
@@ -153,6 +154,75 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
                                                                     f1 ? f1->max_m_tiles : 0, stream);
 }
 
+// Which problems take the streaming kernel (gemm_stream.hpp).  Up to 96 routed rows per slot on average the
+// weights dominate and it wins whatever the load's shape: against the 256-row-tile kernel, H = 7168, I = 2048,
+// 288 slots, whole layer: 5 rows 4.31 -> 3.80 ms, 28 uneven rows 4.38 -> 3.99, 42 rows 4.71 -> 4.44, 89 rows
+// 5.17 -> 4.87; at 114 rows a slot often needs a second row-tile of 128 and it loses (5.70 -> 5.89).  The
+// shared expert's rows go along in the same launches however many they are (k = 1, 8192 tokens: 5.16 -> 4.85).
+// Alone, the shared expert streams as long as its rows are one row-tile.
+constexpr int kStreamRowsPerSlot = 96;
+constexpr int kStreamDenseRows = 128;
+
+// The FFN of few rows per slot: two launches of the streaming kernel.
+struct StreamFfn {
+  const void* x_perm; const int32_t* slot_offsets; const void* const* w_gate_up; const void* const* w_down; void* h; void* y_perm;
+  int N;  // routed rows; 0 = no routed experts
+  const void* x; const void* w_sh_gate_up; const void* w_sh_down; void* h_shared; void* y_shared;
+  int T;  // tokens of the shared expert; 0 = none
+};
+
+template <int TMX, int W, int D, int NW, int EPI, int KID>
+int stream_gemm(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
+  constexpr int tile_n = stream_tile_n<W, NW, EPI>, tile_m = 16 * TMX;
+  constexpr bool gu = EPI == EPI_SWIGLU;
+  const revive_config& c = ctx->cfg;
+  auto problem = [&](const void* x, void* h, void* y, int rows, int I, int m_tiles) {
+    StreamProblem p{};
+    p.A = gu ? x : h; p.lda = gu ? c.H : I; p.a_rows = gu ? 0 : rows;
+    p.C = gu ? h : y; p.ldc = gu ? I : c.H; p.c_rows = gu ? rows : 0;
+    p.n_out = gu ? I : c.H; p.K = gu ? c.H : I;
+    p.b_rows_pad = ceil_div(p.n_out, kWeightTileRows) * kWeightTileRows;
+    p.n_col_tiles = ceil_div(p.n_out, tile_n);
+    p.blocks = m_tiles * p.n_col_tiles;
+    p.M = rows;
+    return p;
+  };
+  StreamArgs a{};
+  a.slot_offsets = f.slot_offsets;
+  a.P = ctx->P;
+  if (f.T > 0) {
+    a.dense = problem(f.x, f.h_shared, f.y_shared, f.T, c.I_shared, ceil_div(f.T, tile_m));
+    a.dense.B_one = gu ? f.w_sh_gate_up : f.w_sh_down;
+  }
+  if (f.N > 0) {
+    const int used = f.N < ctx->P ? f.N : ctx->P;  // slots that can hold a row
+    a.grouped = problem(f.x_perm, f.h, f.y_perm, f.N, c.I, f.N / tile_m + used);
+    a.grouped.blocks = ceil_div(a.grouped.blocks, 8) * 8;
+    a.grouped.B_tab = gu ? f.w_gate_up : f.w_down;
+  }
+  KernelTimer timer(ctx, KID, stream);
+  return launch_gemm_bf16_stream<TMX, W, D, NW, EPI, KID>(ctx, a, stream);
+}
+
+template <int TMX, int W, int D, int NW, int K_GATE_UP, int K_DOWN>
+int stream_ffn_as(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
+  const int rc = stream_gemm<TMX, W, D, NW, EPI_SWIGLU, K_GATE_UP>(ctx, f, stream);
+  return rc != REVIVE_OK ? rc : stream_gemm<TMX, W, D, NW, EPI_BF16, K_DOWN>(ctx, f, stream);
+}
+
+template <int K_GATE_UP, int K_DOWN>
+int stream_ffn(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
+  // Above 8 rows per slot some slots hold more than 64: row-tiles of 128 then read those slots' weights once
+  // (28 uneven rows per slot: gate/up 2.95 -> 2.52 ms), at one workgroup less per CU.
+  if (f.N > 8 * ctx->P || f.T > 128) return stream_ffn_as<8, 4, 2, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+  // Fewer than two workgroups per CU: half as large ones spread the streams evenly over the CUs, and a CU
+  // alone does not pull more than about 38 GB/s from HBM (one token, 288 -> 576 workgroups: 110 -> 95 us).
+  const int64_t slots = (f.N < ctx->P ? f.N : ctx->P) + (f.T > 0);
+  const int64_t blocks = slots * ceil_div(ctx->cfg.I, stream_tile_n<2, 4, EPI_SWIGLU>);
+  if (blocks < 2 * 256) return stream_ffn_as<4, 2, 4, 2, K_GATE_UP, K_DOWN>(ctx, f, stream);
+  return stream_ffn_as<4, 2, 4, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+}
+
 template <int K_GATE_UP, int K_DOWN>
 int f32_gemm_pair(revive_ctx* ctx, const void* A, const void* const* gu_tab, const void* gu_one, const void* const* dn_tab,
                   const void* dn_one, void* h, void* y, int I, const MTile* tiles, const int32_t* tile_count, int M,
@@ -193,6 +263,11 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
   MTile* tiles = reinterpret_cast<MTile*>(ctx->d_ws + ctx->ws.off_tiles);
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);
   void* h = ctx->d_ws + ctx->ws.off_h;
+  if (bf16 && N <= static_cast<int64_t>(kStreamRowsPerSlot) * ctx->P) {
+    const StreamFfn f{x_perm, slot_offsets, w_gate_up, w_down, h, y_perm, static_cast<int>(N),
+                      x, w_sh_gate_up, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, y_shared ? T : 0};
+    return stream_ffn<REVIVE_K_FFN_GATE_UP, REVIVE_K_FFN_DOWN>(ctx, f, stream);
+  }
   {
     KernelTimer timer(ctx, REVIVE_K_FFN_TILES, stream);
     hipLaunchKernelGGL(ffn_tiles_kernel, dim3(1), dim3(kMaxP), 0, stream, slot_offsets, ctx->P, tile_m, w_gate_up, w_down, tiles,
@@ -221,6 +296,10 @@ int launch_shared_ffn(revive_ctx* ctx, const void* x, const void* w_sh_gate_up, 
   const int dense_tiles = ceil_div(T, bf16 ? kTileM_bf16 : kTileM_f32);
   void* h_shared = ctx->d_ws + ctx->ws.off_h_shared;
   constexpr int SGU = REVIVE_K_FFN_SHARED_GATE_UP, SDN = REVIVE_K_FFN_SHARED_DOWN;
+  if (bf16 && T <= kStreamDenseRows) {
+    const StreamFfn f{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, x, w_sh_gate_up, w_sh_down, h_shared, y_shared, T};
+    return stream_ffn<SGU, SDN>(ctx, f, stream);
+  }
   if (bf16) {
     Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, h_shared, y_shared, c.I_shared, nullptr, nullptr, T, dense_tiles, T};
     return bf16_ffn<SGU, SDN>(ctx, shared, nullptr, stream);

@@ -1,0 +1,68 @@
+"""Expert FFN with few rows per slot, at the row counts where a row-tile ends, against fp32 torch."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+import torch
+
+from harness import TOL, f64, rel_err
+from paper_2602_21140_amd import ReviveLayer
+from paper_2602_21140_amd.binding import pack_expert
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 0, 16, 15, 17, 32, 33, 64, 0, 65, 2, 127, 128, 129, 256, 257, 300, 0]
+# (H, I, rows of the slots): one group of K up to several, K no multiple of the ring, columns that are half a tile
+CASES = {
+    "edges": (256, 192, EDGES + [0] * 10),
+    "short_k": (64, 64, EDGES + [0] * 10),
+    "odd_k": (704, 320, EDGES + [3] * 10),
+    "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
+    "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
+    "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
+}
+
+
+def _reference(x, w):
+    g, u, d = (t.float().cpu() for t in w)
+    h = (torch.nn.functional.silu(x @ g) * (x @ u)).to(torch.bfloat16).float()
+    return h @ d
+
+
+@pytest.mark.parametrize("shared", [0, 1, 2])  # 0: none, 1: in the same call, 2: alone
+@pytest.mark.parametrize("name", list(CASES))
+def test_few_rows_per_slot(name, shared):
+    H, I, counts = CASES[name]
+    P, N = len(counts), sum(counts)
+    assert N <= 96 * P  # the average up to which the weights are streamed
+    T = N if shared < 2 else min(N, 100)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(*shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+
+    cfg = SimpleNamespace(T=N, H=H, E=min(P, 512), k=1, I=I, I_shared=I if shared else 0, n_ranks=P, slots_per_rank=1, max_replicas=2,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype="bf16")
+    L = ReviveLayer(cfg)
+    experts = [(normal(H, I, std=H ** -0.5), normal(H, I, std=H ** -0.5), normal(I, H, std=I ** -0.5)) if c else None for c in counts]
+    packed = [pack_expert(*w) if w else (None, None) for w in experts]
+    L.set_expert_weights([p[0] for p in packed], [p[1] for p in packed])
+    w_sh = (normal(H, I, std=H ** -0.5), normal(H, I, std=H ** -0.5), normal(I, H, std=I ** -0.5))
+    gu, dn = pack_expert(*w_sh)
+    x = normal(N, H)
+    y, y_sh = L.empty(N, H).fill_(float("nan")), L.empty(T, H).fill_(float("nan"))
+    off = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    if shared == 2:
+        L.shared_ffn(x[:T].contiguous(), gu, dn, T, out=y_sh)
+    else:
+        L.expert_ffn(x, off, N, x=x, w_sh_gate_up=gu if shared else None, w_sh_down=dn if shared else None, out=(y, y_sh))
+    torch.cuda.synchronize()
+    xf = x.float().cpu()
+    if shared < 2:
+        for p, c in enumerate(counts):
+            if c:
+                a, b = int(off[p]), int(off[p + 1])
+                assert rel_err(f64(y[a:b]), _reference(xf[a:b], experts[p]).double().numpy()) < TOL["bf16"], (p, c)
+    if shared:
+        assert rel_err(f64(y_sh), _reference(xf[:T], w_sh).double().numpy()) < TOL["bf16"]
+    L.close()
