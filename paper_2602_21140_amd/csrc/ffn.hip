@@ -163,16 +163,17 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
 constexpr int kStreamRowsPerSlot = 96;
 constexpr int kStreamDenseRows = 128;
 
-// The FFN of few rows per slot: two launches of the streaming kernel.
-struct StreamFfn {
+// One FFN call: routed experts, shared expert, or both.
+struct FfnArgs {
   const void* x_perm; const int32_t* slot_offsets; const void* const* w_gate_up; const void* const* w_down; void* h; void* y_perm;
   int N;  // routed rows; 0 = no routed experts
   const void* x; const void* w_sh_gate_up; const void* w_sh_down; void* h_shared; void* y_shared;
   int T;  // tokens of the shared expert; 0 = none
 };
 
+// The FFN of few rows per slot: two launches of the streaming kernel.
 template <int TMX, int W, int D, int NW, int EPI, int KID>
-int stream_gemm(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
+int stream_gemm(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
   constexpr int tile_n = stream_tile_n<W, NW, EPI>, tile_m = 16 * TMX;
   constexpr bool gu = EPI == EPI_SWIGLU;
   const revive_config& c = ctx->cfg;
@@ -205,13 +206,13 @@ int stream_gemm(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
 }
 
 template <int TMX, int W, int D, int NW, int K_GATE_UP, int K_DOWN>
-int stream_ffn_as(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
+int stream_ffn_as(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
   const int rc = stream_gemm<TMX, W, D, NW, EPI_SWIGLU, K_GATE_UP>(ctx, f, stream);
   return rc != REVIVE_OK ? rc : stream_gemm<TMX, W, D, NW, EPI_BF16, K_DOWN>(ctx, f, stream);
 }
 
 template <int K_GATE_UP, int K_DOWN>
-int stream_ffn(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
+int stream_ffn(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
   // Above 8 rows per slot some slots hold more than 64: row-tiles of 128 then read those slots' weights once
   // (28 uneven rows per slot: gate/up 2.95 -> 2.52 ms), at one workgroup less per CU.
   if (f.N > 8 * ctx->P || f.T > 128) return stream_ffn_as<8, 4, 2, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
@@ -223,32 +224,41 @@ int stream_ffn(revive_ctx* ctx, const StreamFfn& f, hipStream_t stream) {
   return stream_ffn_as<4, 2, 4, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
 }
 
-template <int K_GATE_UP, int K_DOWN>
-int f32_gemm_pair(revive_ctx* ctx, const void* A, const void* const* gu_tab, const void* gu_one, const void* const* dn_tab,
-                  const void* dn_one, void* h, void* y, int I, const MTile* tiles, const int32_t* tile_count, int M,
-                  int max_m_tiles, hipStream_t stream) {
-  const int H = ctx->cfg.H;
+// fp32: the routed and the shared experts in the same two launches.
+template <bool SWIGLU, int KID>
+int f32_gemm(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
+  constexpr bool gu = SWIGLU;
+  const revive_config& c = ctx->cfg;
+  auto problem = [&](const void* x, void* h, void* y, int rows, int I, int m_tiles) {
+    GemmF32Problem p{};
+    p.A = static_cast<const float*>(gu ? x : h); p.lda = gu ? c.H : I; p.ldb = p.lda;
+    p.C = static_cast<float*>(gu ? h : y); p.ldc = gu ? I : c.H;
+    p.n_out = gu ? I : c.H; p.K = gu ? c.H : I;
+    p.n_col_tiles = ceil_div(p.n_out, kTileN_f32);
+    p.blocks = m_tiles * p.n_col_tiles;
+    p.M = rows;
+    return p;
+  };
   GemmF32Args a{};
-  a.A = static_cast<const float*>(A); a.lda = H;
-  a.B_tab = gu_tab; a.B_one = static_cast<const float*>(gu_one); a.ldb = H;
-  a.C = static_cast<float*>(h); a.ldc = I;
-  a.n_out = I; a.K = H;
-  a.tiles = tiles; a.tile_count = tile_count; a.M = M;
-  a.n_col_tiles = ceil_div(I, 64);
-  {
-    KernelTimer timer(ctx, K_GATE_UP, stream);
-    int rc = launch_gemm_f32<true>(ctx, a, max_m_tiles, stream);
-    if (rc != REVIVE_OK) return rc;
+  a.slot_offsets = f.slot_offsets;
+  a.P = ctx->P;
+  if (f.T > 0) {
+    a.dense = problem(f.x, f.h_shared, f.y_shared, f.T, c.I_shared, ceil_div(f.T, kTileM_f32));
+    a.dense.B_one = static_cast<const float*>(gu ? f.w_sh_gate_up : f.w_sh_down);
   }
-  GemmF32Args d{};
-  d.A = static_cast<const float*>(h); d.lda = I;
-  d.B_tab = dn_tab; d.B_one = static_cast<const float*>(dn_one); d.ldb = I;
-  d.C = static_cast<float*>(y); d.ldc = H;
-  d.n_out = H; d.K = I;
-  d.tiles = tiles; d.tile_count = tile_count; d.M = M;
-  d.n_col_tiles = ceil_div(H, 64);
-  KernelTimer timer(ctx, K_DOWN, stream);
-  return launch_gemm_f32<false>(ctx, d, max_m_tiles, stream);
+  if (f.N > 0) {
+    a.grouped = problem(f.x_perm, f.h, f.y_perm, f.N, c.I, f.N / kTileM_f32 + (f.N < ctx->P ? f.N : ctx->P));
+    a.grouped.blocks = ceil_div(a.grouped.blocks, 8) * 8;
+    a.grouped.B_tab = gu ? f.w_gate_up : f.w_down;
+  }
+  KernelTimer timer(ctx, KID, stream);
+  return launch_gemm_f32<SWIGLU>(ctx, a, stream);
+}
+
+template <int K_GATE_UP, int K_DOWN>
+int f32_ffn(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
+  const int rc = f32_gemm<true, K_GATE_UP>(ctx, f, stream);
+  return rc != REVIVE_OK ? rc : f32_gemm<false, K_DOWN>(ctx, f, stream);
 }
 
 }  // namespace
@@ -257,54 +267,39 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
                       const void* const* w_down, void* y_perm, const void* x, const void* w_sh_gate_up, const void* w_sh_down,
                       void* y_shared, int T, hipStream_t stream) {
   const revive_config& c = ctx->cfg;
-  const bool bf16 = c.dtype == REVIVE_DTYPE_BF16;
-  const int tile_m = bf16 ? kTileM_bf16 : kTileM_f32;
   const int64_t N = static_cast<int64_t>(T) * c.k;
+  constexpr int GU = REVIVE_K_FFN_GATE_UP, DN = REVIVE_K_FFN_DOWN;
+  const FfnArgs f{x_perm, slot_offsets, w_gate_up, w_down, ctx->d_ws + ctx->ws.off_h, y_perm, static_cast<int>(N),
+                  x, w_sh_gate_up, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, y_shared ? T : 0};
+  if (c.dtype != REVIVE_DTYPE_BF16) return f32_ffn<GU, DN>(ctx, f, stream);
+  if (N <= static_cast<int64_t>(kStreamRowsPerSlot) * ctx->P) return stream_ffn<GU, DN>(ctx, f, stream);
   MTile* tiles = reinterpret_cast<MTile*>(ctx->d_ws + ctx->ws.off_tiles);
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);
-  void* h = ctx->d_ws + ctx->ws.off_h;
-  if (bf16 && N <= static_cast<int64_t>(kStreamRowsPerSlot) * ctx->P) {
-    const StreamFfn f{x_perm, slot_offsets, w_gate_up, w_down, h, y_perm, static_cast<int>(N),
-                      x, w_sh_gate_up, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, y_shared ? T : 0};
-    return stream_ffn<REVIVE_K_FFN_GATE_UP, REVIVE_K_FFN_DOWN>(ctx, f, stream);
-  }
   {
     KernelTimer timer(ctx, REVIVE_K_FFN_TILES, stream);
-    hipLaunchKernelGGL(ffn_tiles_kernel, dim3(1), dim3(kMaxP), 0, stream, slot_offsets, ctx->P, tile_m, w_gate_up, w_down, tiles,
+    hipLaunchKernelGGL(ffn_tiles_kernel, dim3(1), dim3(kMaxP), 0, stream, slot_offsets, ctx->P, kTileM_bf16, w_gate_up, w_down, tiles,
                        tile_count);
     REVIVE_HIP(ctx, hipGetLastError());
   }
-  const int bound = max_tiles(N, ctx->P, tile_m);
-  constexpr int GU = REVIVE_K_FFN_GATE_UP, DN = REVIVE_K_FFN_DOWN;
-  if (bf16) {
-    Bf16Ffn routed{x_perm, w_gate_up, nullptr, w_down, nullptr, h, y_perm, c.I, tiles, tile_count, 0, bound, static_cast<int>(N)};
-    if (!y_shared) return bf16_ffn<GU, DN>(ctx, routed, nullptr, stream);
-    // routed and shared experts in the same two launches
-    Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, c.I_shared,
-                   nullptr, nullptr, T, ceil_div(T, tile_m), T};
-    return bf16_ffn<GU, DN>(ctx, routed, &shared, stream);
-  }
-  int rc = f32_gemm_pair<GU, DN>(ctx, x_perm, w_gate_up, nullptr, w_down, nullptr, h, y_perm, c.I, tiles, tile_count, 0, bound, stream);
-  if (rc != REVIVE_OK || !y_shared) return rc;
-  return launch_shared_ffn(ctx, x, w_sh_gate_up, w_sh_down, y_shared, T, stream);
+  Bf16Ffn routed{x_perm, w_gate_up, nullptr, w_down, nullptr, f.h, y_perm, c.I, tiles, tile_count, 0,
+                 max_tiles(N, ctx->P, kTileM_bf16), f.N};
+  if (!y_shared) return bf16_ffn<GU, DN>(ctx, routed, nullptr, stream);
+  // routed and shared experts in the same two launches
+  Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, f.h_shared, y_shared, c.I_shared,
+                 nullptr, nullptr, T, ceil_div(T, kTileM_bf16), T};
+  return bf16_ffn<GU, DN>(ctx, routed, &shared, stream);
 }
 
 int launch_shared_ffn(revive_ctx* ctx, const void* x, const void* w_sh_gate_up, const void* w_sh_down, void* y_shared, int T,
                       hipStream_t stream) {
   const revive_config& c = ctx->cfg;
-  const bool bf16 = c.dtype == REVIVE_DTYPE_BF16;
-  const int dense_tiles = ceil_div(T, bf16 ? kTileM_bf16 : kTileM_f32);
   void* h_shared = ctx->d_ws + ctx->ws.off_h_shared;
   constexpr int SGU = REVIVE_K_FFN_SHARED_GATE_UP, SDN = REVIVE_K_FFN_SHARED_DOWN;
-  if (bf16 && T <= kStreamDenseRows) {
-    const StreamFfn f{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, x, w_sh_gate_up, w_sh_down, h_shared, y_shared, T};
-    return stream_ffn<SGU, SDN>(ctx, f, stream);
-  }
-  if (bf16) {
-    Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, h_shared, y_shared, c.I_shared, nullptr, nullptr, T, dense_tiles, T};
-    return bf16_ffn<SGU, SDN>(ctx, shared, nullptr, stream);
-  }
-  return f32_gemm_pair<SGU, SDN>(ctx, x, nullptr, w_sh_gate_up, nullptr, w_sh_down, h_shared, y_shared, c.I_shared, nullptr, nullptr, T, dense_tiles, stream);
+  const FfnArgs f{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, x, w_sh_gate_up, w_sh_down, h_shared, y_shared, T};
+  if (c.dtype != REVIVE_DTYPE_BF16) return f32_ffn<SGU, SDN>(ctx, f, stream);
+  if (T <= kStreamDenseRows) return stream_ffn<SGU, SDN>(ctx, f, stream);
+  Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, h_shared, y_shared, c.I_shared, nullptr, nullptr, T, ceil_div(T, kTileM_bf16), T};
+  return bf16_ffn<SGU, SDN>(ctx, shared, nullptr, stream);
 }
 
 }  // namespace revive

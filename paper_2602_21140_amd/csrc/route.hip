@@ -290,13 +290,15 @@ int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* log
     return launch_gemm_bf16<BM, BN, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, BM), stream);
   }
   GemmF32Args a{};
-  a.A = static_cast<const float*>(x); a.lda = c.H;
-  a.B_tab = nullptr; a.B_one = static_cast<const float*>(w); a.ldb = c.H;
-  a.C = logits; a.ldc = c.E;
-  a.n_out = c.E; a.K = c.H;
-  a.tiles = nullptr; a.tile_count = nullptr; a.M = T;
-  a.n_col_tiles = ceil_div(c.E, 64);
-  return launch_gemm_f32<false>(ctx, a, ceil_div(T, kTileM_f32), stream);
+  GemmF32Problem& p = a.dense;
+  p.A = static_cast<const float*>(x); p.lda = c.H;
+  p.B_one = static_cast<const float*>(w); p.ldb = c.H;
+  p.C = logits; p.ldc = c.E;
+  p.n_out = c.E; p.K = c.H;
+  p.M = T;
+  p.n_col_tiles = ceil_div(c.E, kTileN_f32);
+  p.blocks = ceil_div(T, kTileM_f32) * p.n_col_tiles;
+  return launch_gemm_f32<false>(ctx, a, stream);
 }
 
 int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk_logical, float* topk_weight,

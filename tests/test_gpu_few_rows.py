@@ -1,4 +1,4 @@
-"""Expert FFN with few rows per slot, at the row counts where a row-tile ends, against fp32 torch."""
+"""Expert FFN with few rows per slot and in fp32, at the row counts where a row-tile ends, against plain torch."""
 from types import SimpleNamespace
 
 import numpy as np
@@ -65,4 +65,49 @@ def test_few_rows_per_slot(name, shared):
                 assert rel_err(f64(y[a:b]), _reference(xf[a:b], experts[p]).double().numpy()) < TOL["bf16"], (p, c)
     if shared:
         assert rel_err(f64(y_sh), _reference(xf[:T], w_sh).double().numpy()) < TOL["bf16"]
+    L.close()
+
+
+# (H, I): K a multiple of the 32-wide step and not, shorter than one step, more steps than are in flight, ragged columns
+@pytest.mark.parametrize("H,I", [(8, 4), (40, 36), (72, 132), (256, 128), (1000, 68)])
+@pytest.mark.parametrize("shared", [0, 1, 2])
+def test_fp32_row_tiles(H, I, shared):
+    counts = [1, 0, 16, 15, 17, 32, 33, 48, 49, 64, 0, 65, 2, 127, 128, 129, 300, 0]
+    P, N = len(counts), sum(counts)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+
+    def normal(*shape, std=1.0):
+        return torch.randn(*shape, generator=gen, device="cuda") * std
+
+    cfg = SimpleNamespace(T=N, H=H, E=P, k=1, I=I, I_shared=I if shared else 0, n_ranks=P, slots_per_rank=1, max_replicas=1,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype="fp32")
+    L = ReviveLayer(cfg)
+    experts = [(normal(H, I, std=H ** -0.5), normal(H, I, std=H ** -0.5), normal(I, H, std=I ** -0.5)) if c else None for c in counts]
+    packed = [pack_expert(*w) if w else (None, None) for w in experts]
+    L.set_expert_weights([p[0] for p in packed], [p[1] for p in packed])
+    w_sh = (normal(H, I, std=H ** -0.5), normal(H, I, std=H ** -0.5), normal(I, H, std=I ** -0.5))
+    gu, dn = pack_expert(*w_sh)
+    x = normal(N, H)
+    y, y_sh = L.empty(N, H).fill_(float("nan")), L.empty(N, H).fill_(float("nan"))
+    off = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    if shared == 2:
+        L.shared_ffn(x, gu, dn, N, out=y_sh)
+    else:
+        L.expert_ffn(x, off, N, x=x, w_sh_gate_up=gu if shared else None, w_sh_down=dn if shared else None, out=(y, y_sh))
+    torch.cuda.synchronize()
+
+    def reference(rows, w):
+        g, u, d = (f64(t) for t in w)
+        z = rows @ g
+        return (z / (1.0 + np.exp(-z)) * (rows @ u)) @ d
+
+    xd = f64(x)
+    if shared < 2:
+        for p, c in enumerate(counts):
+            if c:
+                a, b = int(off[p]), int(off[p + 1])
+                # sums of up to a thousand fp32 products: 2^-24 sqrt(1000) = 2e-6 of the largest, five times that allowed
+                assert rel_err(f64(y[a:b]), reference(xd[a:b], experts[p])) < 1e-5, (p, c)
+    if shared:
+        assert rel_err(f64(y_sh), reference(xd, w_sh)) < 1e-5
     L.close()
