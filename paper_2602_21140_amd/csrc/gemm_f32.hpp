@@ -174,14 +174,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = v[r] / (1.0f + expf(-v[r])) * acc[W - 1][i][r];
       }
-      float* dst = g.C + static_cast<int64_t>(row) * g.ldc + col;
-      if (((g.ldc | g.n_out) & 3) == 0) {
-        *reinterpret_cast<f32x4*>(dst) = v;
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (col + r < g.n_out) dst[r] = v[r];
-      }
+      *reinterpret_cast<f32x4*>(g.C + static_cast<int64_t>(row) * g.ldc + col) = v;  // n_out is a multiple of 4
     }
   };
   if (rows <= 16) run(std::integral_constant<int, 1>{});

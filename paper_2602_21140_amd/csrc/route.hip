@@ -5,7 +5,6 @@
 // no replica left are masked to -inf immediately before the top-k), Sec. 3.4 "Redundant experts"
 // (the logical-to-physical map decides which replica serves a token).
 #include "gemm_bf16.hpp"
-#include "gemm_f32.hpp"
 
 namespace revive {
 
@@ -146,112 +145,157 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
   }
 }
 
-// Router logits for a small router (E <= 128) without LDS staging.  A workgroup of KS wavefronts
-// owns 32 tokens and NTN tiles of 32 experts (blockIdx.y selects which); wavefront w multiplies the w-th slice of the hidden dimension
-// with operands loaded straight from global memory in MFMA fragment order, and the KS partial
-// sums are added in wavefront order through LDS (a fixed order: the result is deterministic).
-// Per 64-wide K block a lane reads 64 contiguous bytes of its token row (lanes l and l+32 cover
-// one 128-byte line), so x is streamed once in full lines; the router matrix stays in L2.
-// Up to three K blocks are in flight per wavefront.
-template <int NTN, int KS>
-__global__ __launch_bounds__(64 * KS) void router_direct_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
-                                                                float* __restrict__ logits, int T, int E, int H) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* part = reinterpret_cast<float*>(smem);  // [KS-1][NTN][16][64]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane & 31, half = lane >> 5;
-  const int row0 = blockIdx.x * 32;
-  const int e0 = blockIdx.y * (NTN * 32);  // first expert of this workgroup
-  const int kq = H / KS;  // K range of one wavefront, a multiple of 64
-  const int64_t koff = static_cast<int64_t>(wave) * kq + half * 32;
-  const unsigned char* a_ptr = reinterpret_cast<const unsigned char*>(x + static_cast<int64_t>(min(row0 + r, T - 1)) * H + koff);
-  const unsigned char* b_ptr[NTN];
+// Router logits: x [T, H] times w [E, H]^T, fp32 sums.
+//
+// A workgroup owns TM*16 tokens and TN*16 experts; its KS wavefronts each multiply a slice of the hidden
+// dimension on their own (no barrier) and the KS partial sums are added in wavefront order through LDS (a
+// fixed order: the result is deterministic).  What bounds it is how fast one CU pulls its rows of x and w in
+// out of L2, and, with few workgroups, the latency of doing so: the K split keeps KS * D * (TM + TN) * 2 KiB
+// in flight, and the loads are in address order (eight lanes take a row's 128 bytes, 130 GB/s per CU, against
+// 38 GB/s for loads in MFMA operand order), each wavefront turning its rows over to operand order in LDS of
+// its own.  A lane's 16 LDS bytes are consecutive K-elements of its row.
+//
+// Against the kernels that stood here (us): bf16, H = 7168, E = 256, T = 1: 53 -> 10, 192: 53 -> 11, 1003:
+// 55 -> 19, 4096: 59 -> 40; H = 2048, E = 64, T = 37: 12 -> 6, 4096: 13 -> 10; fp32, H = 1024, E = 32, T = 1001:
+// 59 -> 7.  The shorter sums are also nearer the exact ones (H = 7168: 5.3e-7 -> 1.8e-7).
+template <typename T> struct RouterMath;
+template <> struct RouterMath<uint16_t> {
+  static __device__ __forceinline__ f32x4 mac(u32x4 w, u32x4 x, f32x4 acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
+  }
+};
+template <> struct RouterMath<float> {
+  static __device__ __forceinline__ f32x4 mac(u32x4 w, u32x4 x, f32x4 acc) {
+    const f32x4 a = __builtin_bit_cast(f32x4, w), b = __builtin_bit_cast(f32x4, x);
 #pragma unroll
-  for (int tn = 0; tn < NTN; ++tn)
-    b_ptr[tn] = reinterpret_cast<const unsigned char*>(w + static_cast<int64_t>(min(e0 + tn * 32 + r, E - 1)) * H + koff);
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+    return acc;
+  }
+};
 
-  f32x16 acc[NTN];
-#pragma unroll
-  for (int tn = 0; tn < NTN; ++tn)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[tn][i] = 0.f;
-
-  struct Frags { u32x4 a[4]; u32x4 b[NTN][4]; };
-  auto load = [&](int blk, Frags& f) {
-    const int64_t o = static_cast<int64_t>(blk) * 128;  // 64 bf16
-#pragma unroll
-    for (int j = 0; j < 4; ++j) f.a[j] = load_global_16B(a_ptr + o + j * 16);
-#pragma unroll
-    for (int tn = 0; tn < NTN; ++tn)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) f.b[tn][j] = load_global_16B(b_ptr[tn] + o + j * 16);
-  };
-  auto mac = [&](const Frags& f) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int tn = 0; tn < NTN; ++tn)
-        acc[tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.b[tn][j]), __builtin_bit_cast(bf16x8, f.a[j]),
-                                                          acc[tn], 0, 0, 0);
-  };
-  const int n = kq >> 6;
-  Frags f0, f1, f2;
-  load(0, f0);
-  if (n > 1) load(1, f1);
-  if (NTN <= 2 && n > 2) load(2, f2);
-  if (NTN <= 2) {
-    for (int blk = 0; blk < n; blk += 3) {
-      mac(f0);
-      if (blk + 3 < n) load(blk + 3, f0);
-      if (blk + 1 < n) { mac(f1); if (blk + 4 < n) load(blk + 4, f1); }
-      if (blk + 2 < n) { mac(f2); if (blk + 5 < n) load(blk + 5, f2); }
-    }
+template <typename El, int TM, int TN, int KS, int D>
+__global__ __launch_bounds__(64 * KS, 2) void router_kernel(const El* __restrict__ x, const El* __restrict__ w, float* __restrict__ logits,
+                                                         int T, int E, int H, int n_tok, int n_exp) {
+  constexpr int ROWS = (TM + TN) * 16, NL = ROWS / 8;  // rows of both operands, 16-byte loads per lane and step
+  __shared__ __attribute__((aligned(16))) unsigned char lds[KS][ROWS * 128];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Workgroup i runs on XCD i % 8.  With at least eight token tiles a tile's workgroups share its rows of x in
+  // one XCD's L2; with fewer the experts are dealt over the XCDs.
+  int tok, ex;
+  if (n_tok >= 8) {
+    const int local = blockIdx.x >> 3;
+    tok = local / n_exp * 8 + (blockIdx.x & 7);
+    ex = local % n_exp;
   } else {
-    for (int blk = 0; blk < n; blk += 2) {
-      mac(f0);
-      if (blk + 2 < n) load(blk + 2, f0);
-      if (blk + 1 < n) { mac(f1); if (blk + 3 < n) load(blk + 3, f1); }
+    tok = blockIdx.x / n_exp;
+    ex = blockIdx.x % n_exp;
+  }
+  if (tok >= n_tok) return;
+  const int t0 = tok * (TM * 16), e0 = ex * (TN * 16);
+  const int64_t row_bytes = static_cast<int64_t>(H) * sizeof(El);
+  const unsigned char* xb = reinterpret_cast<const unsigned char*>(x) + t0 * row_bytes;
+  const unsigned char* wb = reinterpret_cast<const unsigned char*>(w) + e0 * row_bytes;
+  const int steps = static_cast<int>((row_bytes + 127) >> 7);  // of 128 bytes of K
+  const int s0 = steps * wave / KS, n = steps * (wave + 1) / KS - s0;
+  const int c16 = (lane & 7) * 16;
+  uint32_t off[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {  // rows past the last token or expert: the last one again, not stored
+    const int r = i * 8 + (lane >> 3);
+    off[i] = static_cast<uint32_t>((r < TM * 16 ? min(r, T - 1 - t0) : min(r - TM * 16, E - 1 - e0)) * row_bytes);
+  }
+  unsigned char* mine = lds[wave];
+  u32x4 buf[D][NL];
+  auto load = [&](int s, int d) {
+    const int64_t k = min(static_cast<int64_t>(s0 + max(0, min(s, n - 1))) * 128 + c16, row_bytes - 16);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) buf[d][i] = load_global_16B((i < TM * 2 ? xb : wb) + off[i] + k);
+  };
+  const int r16 = lane & 15, quad = lane >> 4;
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mac = [&](int s, int d) {
+    const bool in = static_cast<int64_t>(s0 + s) * 128 + c16 < row_bytes;  // K-elements past the last one count as zero
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int r = i * 8 + (lane >> 3);
+      *reinterpret_cast<u32x4*>(mine + r * 128 + (((lane & 7) ^ swz(r)) << 4)) = in ? buf[d][i] : zero;
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const unsigned char* p = mine + r16 * 128 + (((h * 4 + quad) ^ swz(r16)) << 4);  // swz has period 16
+      u32x4 a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const u32x4*>(p + i * (16 * 128));
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const u32x4*>(p + (TM + j) * (16 * 128));
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = RouterMath<El>::mac(b[j], a[i], acc[i][j]);
+    }
+  };
+  // unconditional loads, so that the compiler's count of loads in flight stays exact
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, d);
+  int s = 0;
+  for (; s + D < n; s += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      mac(s + d, d);
+      load(s + D + d, d);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (s + d < n) mac(s + d, d);
 
-  if (wave > 0) {
+  // partial sums into this wavefront's LDS as [token][expert], then all threads add them up
+  static_assert(TM * TN * 16 * 16 * 4 <= ROWS * 128, "the partial sums fit the wavefront's rows");
+  constexpr int NE = TN * 16;
+  __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int tn = 0; tn < NTN; ++tn)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) part[(((wave - 1) * NTN + tn) * 16 + i) * 64 + lane] = acc[tn][i];
-  }
+    for (int j = 0; j < TN; ++j)
+      *reinterpret_cast<f32x4*>(mine + ((i * 16 + r16) * NE + j * 16 + quad * 4) * 4) = acc[i][j];
   __syncthreads();
-  if (wave == 0) {
-    const int row = row0 + r;
+  for (int i = threadIdx.x; i < TM * 16 * NE; i += 64 * KS) {
+    float v = 0.f;
 #pragma unroll
-    for (int tn = 0; tn < NTN; ++tn) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        float v = acc[tn][i];
-        for (int ws = 0; ws < KS - 1; ++ws) v += part[((ws * NTN + tn) * 16 + i) * 64 + lane];
-        acc[tn][i] = v;
-      }
-      if (row < T) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int col = e0 + tn * 32 + q * 8 + half * 4;
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr)
-            if (col + rr < E) logits[static_cast<int64_t>(row) * E + col + rr] = acc[tn][q * 4 + rr];
-        }
-      }
-    }
+    for (int q = 0; q < KS; ++q) v += *reinterpret_cast<const float*>(lds[q] + i * 4);
+    const int t = t0 + i / NE, e = e0 + i % NE;
+    if (t < T && e < E) logits[static_cast<int64_t>(t) * E + e] = v;
   }
 }
 
-template <int NTN, int KS>
-int launch_router_direct(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
-  constexpr size_t lds = static_cast<size_t>(KS - 1) * NTN * 16 * 64 * sizeof(float);
-  auto kern = router_direct_kernel<NTN, KS>;
-  REVIVE_HIP(ctx, allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
-  hipLaunchKernelGGL(kern, dim3(ceil_div(T, 32), ceil_div(ctx->cfg.E, NTN * 32)), dim3(64 * KS), lds, stream, static_cast<const uint16_t*>(x),
-                     static_cast<const uint16_t*>(w), logits, T, ctx->cfg.E, ctx->cfg.H);
-  return check_hip(ctx, hipGetLastError(), "router_direct launch");
+template <typename El, int TM, int TN, int KS, int D>
+int launch_router(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
+  const int E = ctx->cfg.E, n_tok = ceil_div(T, TM * 16), n_exp = ceil_div(E, TN * 16);
+  const int grid = (n_tok >= 8 ? ceil_div(n_tok, 8) * 8 : n_tok) * n_exp;
+  hipLaunchKernelGGL((router_kernel<El, TM, TN, KS, D>), dim3(grid), dim3(64 * KS), 0, stream, static_cast<const El*>(x),
+                     static_cast<const El*>(w), logits, T, E, ctx->cfg.H, n_tok, n_exp);
+  return check_hip(ctx, hipGetLastError(), "router launch");
+}
+
+// The largest tile that still gives every CU a workgroup: larger tiles read x and w fewer times.  us, all
+// sizes of tile tried: T = 512, E = 256, H = 7168: 17 (16 x 16), 17 (32 x 32); T = 1003: 28, 19; T = 2000:
+// 49, 29, 37 (64 x 64); T = 4096: 95, 52, 40.
+template <typename El>
+int router(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
+  const int E = ctx->cfg.E;
+  auto blocks = [&](int m, int n) { return static_cast<int64_t>(ceil_div(T, m)) * ceil_div(E, n); };
+  if (E > 32 && blocks(64, 64) >= 256) return launch_router<El, 4, 4, 4, 2>(ctx, x, w, logits, T, stream);
+  if (E > 16 && blocks(32, 32) >= 256) return launch_router<El, 2, 2, 8, 2>(ctx, x, w, logits, T, stream);
+  return launch_router<El, 1, 1, 8, 4>(ctx, x, w, logits, T, stream);
 }
 
 }  // namespace
@@ -259,46 +303,21 @@ int launch_router_direct(revive_ctx* ctx, const void* x, const void* w, float* l
 int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
   const revive_config& c = ctx->cfg;
   KernelTimer timer(ctx, REVIVE_K_ROUTER_GEMM, stream);
-  if (c.dtype == REVIVE_DTYPE_BF16 && c.E <= 128 && c.H % 256 == 0 &&
-      static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20)) {
-    // small router: every 32-token workgroup re-reads its part of the router matrix from L2.  With few
-    // token blocks every 32-expert tile gets a workgroup of its own (more workgroups, and less
-    // to pull through one CU's L1), otherwise one workgroup serves all experts of its tokens.
-    const bool ks8 = c.H % 512 == 0;
-    const bool split_experts = ceil_div(T, 32) < 512;
-    switch (split_experts ? 1 : ceil_div(c.E, 32)) {
-      case 1: return ks8 ? launch_router_direct<1, 8>(ctx, x, w, logits, T, stream) : launch_router_direct<1, 4>(ctx, x, w, logits, T, stream);
-      case 2: return ks8 ? launch_router_direct<2, 8>(ctx, x, w, logits, T, stream) : launch_router_direct<2, 4>(ctx, x, w, logits, T, stream);
-      case 3: return launch_router_direct<3, 4>(ctx, x, w, logits, T, stream);
-      default: return launch_router_direct<4, 4>(ctx, x, w, logits, T, stream);
-    }
-  }
-  if (c.dtype == REVIVE_DTYPE_BF16) {
+  if (c.dtype != REVIVE_DTYPE_BF16) return router<float>(ctx, x, w, logits, T, stream);
+  const int64_t wide = static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128);
+  if (wide >= 512) {
+    // 128 x 128 tiles fill the chip twice over and read x and w half as often (T = 32768, E = 384: 267 us
+    // against 380; T = 8192, E = 256, 128 tiles: 64 against 64)
     GemmArgs a{};
     a.A = x; a.lda = c.H;
-    a.B_tab = nullptr; a.B_one = w; a.ldb = c.H;
+    a.B_one = w; a.ldb = c.H;
     a.C = logits; a.ldc = c.E;
     a.n_out = c.E; a.K = c.H;
-    a.tiles = nullptr; a.tile_count = nullptr; a.M = T;
-    if (static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128) >= 512) {
-      // enough tiles to fill the chip twice over: wider tiles read x fewer times
-      a.n_col_tiles = ceil_div(c.E, 128);
-      return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
-    }
-    constexpr int BM = 128, BN = 64;
-    a.n_col_tiles = ceil_div(c.E, BN);
-    return launch_gemm_bf16<BM, BN, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, BM), stream);
+    a.M = T;
+    a.n_col_tiles = ceil_div(c.E, 128);
+    return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
   }
-  GemmF32Args a{};
-  GemmF32Problem& p = a.dense;
-  p.A = static_cast<const float*>(x); p.lda = c.H;
-  p.B_one = static_cast<const float*>(w); p.ldb = c.H;
-  p.C = logits; p.ldc = c.E;
-  p.n_out = c.E; p.K = c.H;
-  p.M = T;
-  p.n_col_tiles = ceil_div(c.E, kTileN_f32);
-  p.blocks = ceil_div(T, kTileM_f32) * p.n_col_tiles;
-  return launch_gemm_f32<false>(ctx, a, stream);
+  return router<uint16_t>(ctx, x, w, logits, T, stream);
 }
 
 int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk_logical, float* topk_weight,

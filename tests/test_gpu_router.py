@@ -1,0 +1,44 @@
+"""Router logits at the token and expert counts where a tile, a K step or a rule of the launch ends, against
+fp64 products of the same bits."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_21140_amd import ReviveLayer
+
+pytestmark = pytest.mark.gpu
+
+
+# (T, E, H): 16 x 16 tiles (one token to several tiles, ragged in both), 32 x 32 and 64 x 64 tiles from 256
+# workgroups on, seven and eight token tiles, fewer steps of K than wavefronts, the 128 x 128 tiles
+SHAPES = [(1, 16, 64), (15, 24, 192), (17, 16, 448), (112, 40, 512), (113, 40, 576), (129, 256, 704), (1000, 256, 320),
+          (1025, 250, 448), (4090, 256, 128), (4100, 130, 1024), (65500, 70, 64), (32700, 200, 128)]
+F32_H = {64: 8, 192: 40, 448: 1000, 320: 72}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,E,H", SHAPES)
+def test_router_logits(T, E, H, dtype):
+    if dtype == "fp32":
+        H = F32_H.get(H, H)
+    cfg = SimpleNamespace(T=T, H=H, E=E, k=1, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype=dtype)
+    L = ReviveLayer(cfg)
+    L.set_placement(np.arange(E, dtype=np.int32))
+    L.update_map(np.zeros(1, dtype=np.uint8))
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn(T, H, generator=gen, device="cuda").to(L.dtype)
+    w = (torch.randn(E, H, generator=gen, device="cuda") * H ** -0.5).to(L.dtype)
+    logits = torch.full((T, E), float("nan"), device="cuda")
+    L.route(x, w, T, logits=logits)
+    again = torch.full((T, E), float("nan"), device="cuda")
+    L.route(x, w, T, logits=again)
+    exact = x.double() @ w.double().T
+    # exact products; a sum of H <= 1024 rounds H times to 2^-24 of a partial sum: below 2^-24 sqrt(1024) = 2e-6
+    # of the logit's standard deviation (1), less where the sum is split
+    assert (logits.double() - exact).abs().max().item() < 2e-5  # ten times that for the largest of 10^7
+    assert ((logits.double() - exact).norm() / exact.norm()).item() < 2e-6
+    assert torch.equal(logits, again)
+    L.close()
