@@ -10,9 +10,6 @@ namespace revive {
 
 namespace {
 
-// Ordering of candidates: larger key first, equal keys by lower expert id.
-__device__ __forceinline__ bool better(float ka, int ea, float kb, int eb) { return ka > kb || (ka == kb && ea < eb); }
-
 struct RouteParams {
   const float* logits;
   const int32_t* l2p_count;
@@ -25,123 +22,202 @@ struct RouteParams {
   float route_scale;
 };
 
-// One wavefront per token.  Lane l holds the logits of experts l, l+64, l+128, ... (VALS of them);
-// a masked or excluded expert's key is -inf.  Expert order is decided on the fp32 logits
-// themselves (softmax and sigmoid are increasing, so this is the order of the scores); group
-// scores, which add two scores, and the output weights are evaluated in fp64.
-// GROUPED variants hold the group scores in registers (n_group <= 8 or <= 32).
-template <int VALS, int MAXG>
-__global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
-  const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= p.T) return;  // whole wavefront leaves together
+// Reductions over the wavefront without LDS: four steps inside the rows of 16 lanes, two between rows, all
+// of them cross-lane operands of an ALU instruction (a shuffle through LDS takes ten times as long).
+// Step 0..3 combine halves of 2, 4, 8 and 16 lanes, after which every lane of a row has the row's result;
+// steps 4 and 5 bring the rows' results to lanes 31 and 63, and then to lane 63.  Lanes that a step has
+// nothing for get `other`.
+template <int STEP>
+__device__ __forceinline__ float dpp_step(float v, float other) {
+  constexpr int ctrl = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : STEP == 2 ? 0x141 : STEP == 3 ? 0x140 : STEP == 4 ? 0x142 : 0x143;
+  constexpr int rows = STEP == 4 ? 0xA : STEP == 5 ? 0xC : 0xF;
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(other), __float_as_int(v), ctrl, rows, 0xF, false));
+}
+__device__ __forceinline__ float wave_max(float v) {
   const float NEG = -__builtin_inff();
+  v = fmaxf(v, dpp_step<0>(v, NEG));
+  v = fmaxf(v, dpp_step<1>(v, NEG));
+  v = fmaxf(v, dpp_step<2>(v, NEG));
+  v = fmaxf(v, dpp_step<3>(v, NEG));
+  v = fmaxf(v, dpp_step<4>(v, NEG));
+  v = fmaxf(v, dpp_step<5>(v, NEG));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+// The two largest of two disjoint sets, each given by its two largest.
+template <int STEP>
+__device__ __forceinline__ void top2_step(float& m1, float& m2) {
+  const float NEG = -__builtin_inff();
+  const float o1 = dpp_step<STEP>(m1, NEG), o2 = dpp_step<STEP>(m2, NEG);
+  const float lo = fmaxf(fminf(m1, o1), fmaxf(m2, o2));
+  m1 = fmaxf(m1, o1);
+  m2 = lo;
+}
 
-  float key[VALS];
-  const float* row = p.logits + static_cast<int64_t>(t) * p.E;
-  float vmax = NEG;  // largest live logit of the row: common shift of the exponentials (the best chosen score is exactly 1)
+// A wavefront selects for TPW tokens.  Lane l holds the logits of experts l, l+64, l+128, ... (VALS of them)
+// of each; a masked or excluded expert's key is -inf.  Expert order is decided on the fp32 logits themselves
+// (softmax and sigmoid are increasing, so this is the order of the scores); group scores, which add two
+// scores, and the output weights are evaluated in fp64.
+//
+// The fp64 work (an exponential per group and per chosen expert) keeps few lanes busy and is what a token
+// costs most, so each token has LPT = 64 / TPW lanes of its own for it: lane g of them takes the best score
+// of group g, lane LPT/2 + g the second best, lane j the j-th chosen expert's weight.
+template <int VALS, int TPW, bool GROUPED>
+__global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
+  constexpr int LPT = 64 / TPW, HALF = LPT / 2;
+  const int lane = threadIdx.x & 63;
+  const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * TPW;
+  if (t0 >= p.T) return;  // whole wavefront leaves together
+  const float NEG = -__builtin_inff();
+  const int my_q = lane / LPT, li = lane % LPT;  // the token whose fp64 work this lane shares, and its place in it
+
+  int cnt[VALS];
+  float key[TPW][VALS];
 #pragma unroll
   for (int i = 0; i < VALS; ++i) {
     const int e = lane + 64 * i;
-    float z = NEG;
-    if (e < p.E) {
-      z = row[e];
-      if (p.l2p_count[e] <= 0) z = NEG;  // failure mask
-      vmax = fmaxf(vmax, z);
-    }
-    key[i] = z;
-  }
+    cnt[i] = e < p.E ? p.l2p_count[e] : 0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o));
-  const double shift = static_cast<double>(vmax);
-
-  auto score64 = [&](float z) -> double {  // unnormalised gating score of a live expert
+    for (int q = 0; q < TPW; ++q)
+      key[q][i] = e < p.E ? p.logits[static_cast<int64_t>(min(t0 + q, p.T - 1)) * p.E + e] : NEG;
+  }
+  float my_max = NEG;  // largest live logit of my token: common shift of the exponentials (the best chosen score is exactly 1)
+#pragma unroll
+  for (int q = 0; q < TPW; ++q) {
+    float m = NEG;
+#pragma unroll
+    for (int i = 0; i < VALS; ++i) {
+      if (cnt[i] <= 0) key[q][i] = NEG;  // failure mask
+      m = fmaxf(m, key[q][i]);
+    }
+    m = wave_max(m);
+    if (my_q == q) my_max = m;
+  }
+  const double shift = static_cast<double>(my_max);
+  auto score64 = [&](float z) -> double {  // unnormalised gating score of a live expert of my token
     const double zd = static_cast<double>(z);
     return p.score_fn == REVIVE_SCORE_SIGMOID ? 1.0 / (1.0 + exp(-zd)) : exp(zd - shift);
   };
 
-  if (MAXG > 1) {
-    // Group score = sum of the two best live scores of the group (one if only one is live, -inf
-    // if none).  A wave-wide top-2 per group finds the two logits; lane g then evaluates group
-    // g's score in fp64 and every lane ranks it against the others through shuffles.
+  if (GROUPED) {
+    // Group score = sum of the two best live scores of the group (one if only one is live, -inf if none).
     const int gsz = p.E / p.n_group;
-    float top1 = NEG, top2 = NEG;  // lane g keeps group g's two best keys
+    float top = NEG;  // li < HALF: best key of group li; else second best of group li - HALF
+    if (gsz >= 8 && (gsz & (gsz - 1)) == 0 && gsz <= 64) {
+      // groups are aligned runs of lanes: all groups at once
+      const int per_block = 64 / gsz, g = li % HALF;
+      const int src = (g % per_block) * gsz + gsz - 1, block = g / per_block;
+#pragma unroll
+      for (int q = 0; q < TPW; ++q) {
+#pragma unroll
+        for (int i = 0; i < VALS; ++i) {
+          float m1 = key[q][i], m2 = NEG;
+          top2_step<0>(m1, m2);
+          top2_step<1>(m1, m2);
+          top2_step<2>(m1, m2);
+          if (gsz >= 16) top2_step<3>(m1, m2);
+          if (gsz >= 32) top2_step<4>(m1, m2);
+          if (gsz >= 64) top2_step<5>(m1, m2);
+          const float a = __shfl(m1, src), b = __shfl(m2, src);
+          if (my_q == q && block == i) top = li < HALF ? a : b;
+        }
+      }
+    } else {
 #pragma unroll 1
-    for (int g = 0; g < p.n_group; ++g) {
-      float m1 = NEG, m2 = NEG;
+      for (int g = 0; g < p.n_group; ++g) {
 #pragma unroll
-      for (int i = 0; i < VALS; ++i) {
-        const int e = lane + 64 * i;
-        const float z = (e < p.E && e / gsz == g) ? key[i] : NEG;
-        if (z > m1) { m2 = m1; m1 = z; } else if (z > m2) { m2 = z; }
-      }
+        for (int q = 0; q < TPW; ++q) {
+          float m1 = NEG, m2 = NEG;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const float o1 = __shfl_xor(m1, o), o2 = __shfl_xor(m2, o);
-        const float hi = fmaxf(m1, o1);
-        const float lo = fmaxf(fminf(m1, o1), fmaxf(m2, o2));
-        m1 = hi;
-        m2 = lo;
+          for (int i = 0; i < VALS; ++i) {
+            const int e = lane + 64 * i;
+            const float z = e >= g * gsz && e < (g + 1) * gsz ? key[q][i] : NEG;
+            m2 = fmaxf(m2, fminf(m1, z));
+            m1 = fmaxf(m1, z);
+          }
+          top2_step<0>(m1, m2);
+          top2_step<1>(m1, m2);
+          top2_step<2>(m1, m2);
+          top2_step<3>(m1, m2);
+          top2_step<4>(m1, m2);
+          top2_step<5>(m1, m2);
+          const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m1), 63));
+          const float b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m2), 63));
+          if (my_q == q && li % HALF == g) top = li < HALF ? a : b;
+        }
       }
-      if (lane == g) { top1 = m1; top2 = m2; }
     }
-    double gs = -__builtin_inf();
-    if (lane < p.n_group && top1 > NEG) {
-      gs = score64(top1);
-      if (top2 > NEG) gs += score64(top2);
-    }
-    // rank of my group among all groups (better score first, ties to the lower group id)
+    const double s = top > NEG ? score64(top) : 0.0;
+    const double second = __shfl(s, lane + HALF);
+    const double gs = li < p.n_group && top > NEG ? s + second : -__builtin_inf();
+    // rank of my group among all groups of the token (better score first, ties to the lower group id)
     int rank = 0;
-#pragma unroll
-    for (int h = 0; h < MAXG; ++h) {
-      const double o = __shfl(gs, h);
-      if (h < p.n_group) rank += (o > gs) || (o == gs && h < lane);
+#pragma unroll 4
+    for (int h = 0; h < p.n_group; ++h) {
+      const double o = __shfl(gs, my_q * LPT + h);
+      rank += (o > gs) || (o == gs && h < li);
     }
-    const unsigned long long kept = __ballot(lane < p.n_group && rank < p.topk_group);
+    const unsigned long long kept = __ballot(li < p.n_group && rank < p.topk_group);
 #pragma unroll
     for (int i = 0; i < VALS; ++i) {
-      const int e = lane + 64 * i;
-      if (e < p.E && !((kept >> (e / gsz)) & 1ull)) key[i] = NEG;  // expert of a dropped group
+      // e / gsz: exact, e + 1/2 is never within 2^-11 of a multiple of gsz
+      const int g = static_cast<int>((static_cast<float>(lane + 64 * i) + 0.5f) / static_cast<float>(gsz));
+#pragma unroll
+      for (int q = 0; q < TPW; ++q)
+        if (!((static_cast<uint32_t>(kept >> (q * LPT)) >> (g & 31)) & 1u)) key[q][i] = NEG;  // expert of a dropped group
     }
   }
 
-  // k rounds of wave-wide arg-max; the winner of round j lands in lane j.
-  int my_e = -1;
+  // k rounds of wave-wide arg-max (largest key, ties to the lower expert id); the winner of token q's round j
+  // lands in lane q * LPT + j
+  int my_e = 0;
   float my_z = 0.f;
+#pragma unroll 1
   for (int j = 0; j < p.k; ++j) {
-    float bk = NEG;
-    int be = 0x7fffffff;
 #pragma unroll
-    for (int i = 0; i < VALS; ++i) {
-      const int e = lane + 64 * i;
-      if (e < p.E && better(key[i], e, bk, be)) { bk = key[i]; be = e; }
-    }
+    for (int q = 0; q < TPW; ++q) {
+      float m = key[q][0];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ok = __shfl_xor(bk, o);
-      const int oe = __shfl_xor(be, o);
-      if (better(ok, oe, bk, be)) { bk = ok; be = oe; }
-    }
-    if ((be & 63) == lane) {
+      for (int i = 1; i < VALS; ++i) m = fmaxf(m, key[q][i]);
+      const float best = wave_max(m);
+      int wi = 0;
+      unsigned long long holders = 1ull;
+#pragma unroll
+      for (int i = VALS - 1; i >= 0; --i) {
+        const unsigned long long b = __ballot(key[q][i] == best);
+        if (b) { holders = b; wi = i; }
+      }
+      const int w = __builtin_ctzll(holders);
 #pragma unroll
       for (int i = 0; i < VALS; ++i)
-        if (i == (be >> 6)) key[i] = NEG;
+        if (wi == i && lane == w) key[q][i] = NEG;
+      if (lane == q * LPT + j) { my_e = wi * 64 + w; my_z = best; }
     }
-    if (lane == j) { my_e = be; my_z = bk; }
   }
 
   // weights: score of the chosen expert over the sum of the chosen scores
-  double s = (lane < p.k) ? score64(my_z) : 0.0;
+  const int t = t0 + my_q;
+  const double s = li < p.k ? score64(my_z) : 0.0;
   double sum = s;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-  if (lane < p.k) {
-    const int64_t o = static_cast<int64_t>(t) * p.k + lane;
-    const int c = p.l2p_count[my_e];
+  for (int o = HALF; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  int c = 0;  // replicas of my expert, held by lane my_e % 64
+#pragma unroll
+  for (int i = 0; i < VALS; ++i) {
+    const int v = __shfl(cnt[i], my_e & 63);
+    if (my_e >> 6 == i) c = v;
+  }
+  if (li < p.k && t < p.T) {
+    const int64_t o = static_cast<int64_t>(t) * p.k + li;
+    // replica of this token: the (batch index of t mod count)-th surviving slot, ascending slot id
+    int phys = -1;
+    if (c > 0) {
+      const unsigned long long b = static_cast<unsigned long long>(p.t_offset) + t;
+      const int r = p.t_offset + p.T <= 0x7fffffffll ? static_cast<int>(static_cast<uint32_t>(b) % static_cast<uint32_t>(c)) : static_cast<int>(b % c);
+      phys = p.l2p_table[my_e * p.max_replicas + r];
+    }
     p.topk_logical[o] = my_e;
     p.topk_weight[o] = static_cast<float>(s / sum * static_cast<double>(p.route_scale));
-    // replica of this token: the (batch index of t mod count)-th surviving slot, ascending slot id
-    p.topk_phys[o] = c > 0 ? p.l2p_table[my_e * p.max_replicas + static_cast<int>((p.t_offset + t) % c)] : -1;
+    p.topk_phys[o] = phys;
   }
 }
 
@@ -335,13 +411,18 @@ int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk
   p.route_scale = c.route_scale;
   p.t_offset = ctx->token_offset;
   KernelTimer timer(ctx, REVIVE_K_ROUTE_TOPK, stream);
-  const dim3 grid(ceil_div(T, 4)), block(256);
+  // Four tokens to a wavefront do less work in all but take longer one by one: E = 256, 8 groups, k = 8, with the
+  // counts and launches around it, 4096 tokens 17.0 us (one) and 17.9 (four), 8192: 21.2 and 21.1, 32768: 58 and 51
+  // (shuffles through LDS, one token: 22.0, 32.5, 94).
+  const bool four = T > 8192 && c.k <= 16 && c.n_group <= 8;
+  const dim3 grid(ceil_div(T, four ? 16 : 4)), block(256);
   const int vals = ceil_div(c.E, 64);
-#define REVIVE_ROUTE_LAUNCH(V)                                                                               \
-  do {                                                                                                       \
-    if (c.n_group <= 1) hipLaunchKernelGGL((route_topk_kernel<V, 1>), grid, block, 0, stream, p);            \
-    else if (c.n_group <= 8) hipLaunchKernelGGL((route_topk_kernel<V, 8>), grid, block, 0, stream, p);       \
-    else hipLaunchKernelGGL((route_topk_kernel<V, 32>), grid, block, 0, stream, p);                          \
+#define REVIVE_ROUTE_LAUNCH(V)                                                                                       \
+  do {                                                                                                               \
+    if (four && c.n_group > 1) hipLaunchKernelGGL((route_topk_kernel<V, 4, true>), grid, block, 0, stream, p);       \
+    else if (four) hipLaunchKernelGGL((route_topk_kernel<V, 4, false>), grid, block, 0, stream, p);                  \
+    else if (c.n_group > 1) hipLaunchKernelGGL((route_topk_kernel<V, 1, true>), grid, block, 0, stream, p);          \
+    else hipLaunchKernelGGL((route_topk_kernel<V, 1, false>), grid, block, 0, stream, p);                            \
   } while (0)
   if (vals <= 1) REVIVE_ROUTE_LAUNCH(1);
   else if (vals <= 2) REVIVE_ROUTE_LAUNCH(2);

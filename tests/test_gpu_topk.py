@@ -1,0 +1,43 @@
+"""Selection on given logits at the expert, group and token counts where the kernel takes another form, with
+many equal logits, against the oracle."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+import torch
+
+from harness import f64
+from oracle import revive_oracle as orc
+from paper_2602_21140_amd import ReviveLayer
+
+pytestmark = pytest.mark.gpu
+
+# E, n_group, topk_group, k: groups that are aligned runs of 8, 16, 32 and 64 lanes, groups that are not (24, 48, 25,
+# 128, 4 experts), more groups than the four-token form takes, more choices than it takes, no groups
+SHAPES = [(64, 8, 3, 6), (128, 8, 4, 8), (256, 8, 4, 8), (512, 8, 4, 8), (192, 8, 4, 5), (384, 8, 2, 3), (200, 8, 2, 16),
+          (256, 2, 1, 8), (32, 8, 8, 16), (512, 32, 8, 32), (320, 20, 3, 8), (256, 8, 4, 17), (61, 1, 1, 1), (384, 1, 1, 8), (500, 1, 1, 32)]
+
+
+@pytest.mark.parametrize("T", [1, 301, 8193])  # 8193: four tokens to a wavefront, the last wavefront with one
+@pytest.mark.parametrize("score_fn", ["softmax", "sigmoid"])
+@pytest.mark.parametrize("E,n_group,topk_group,k", SHAPES)
+def test_topk(E, n_group, topk_group, k, score_fn, T):
+    rng = np.random.default_rng(E + k)
+    slots = -(-E * 5 // 4)
+    p2l = np.concatenate([np.arange(E), rng.permutation(E)[:slots - E]]).astype(np.int32)  # some experts twice
+    cfg = SimpleNamespace(T=T, H=64, E=E, k=k, I=64, I_shared=0, n_ranks=1, slots_per_rank=slots, max_replicas=2,
+                          score_fn=score_fn, n_group=n_group, topk_group=topk_group, dtype="bf16")
+    L = ReviveLayer(cfg)
+    L.set_placement(p2l)
+    lost = np.zeros(E, dtype=np.uint8)
+    lost[rng.permutation(E)[:E // 16]] = 1
+    L.update_map(np.zeros(1, dtype=np.uint8), expert_failed=lost)
+    logits = torch.from_numpy(np.round(rng.standard_normal((T, E)) * 8) / 8).float().cuda()  # eighths: many ties
+    _, top, w, phys = L.route(None, None, T, logits=logits, logits_given=True)
+    m = orc.build_map(p2l, np.zeros(1, dtype=np.uint8), slots, E, 2, expert_failed=lost)
+    s = orc.scores(f64(logits), score_fn)
+    ref = orc.select_topk(orc.masked_selection_scores(s, m.l2p_count), k, n_group, topk_group)
+    assert np.array_equal(top.cpu().numpy(), ref)
+    assert np.array_equal(phys.cpu().numpy(), orc.remap(ref, m))
+    assert np.abs(f64(w) - orc.gate_weights(s, ref)).max() < 2e-7  # one rounding to fp32 of a weight below 1
+    L.close()
