@@ -31,7 +31,8 @@ __device__ __forceinline__ void store_once(uint4* p, uint4 o) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
 
-// One workgroup per token, 16-byte words (8 bf16 or 4 fp32 per thread and step).
+// One workgroup per token (blockIdx.x) and part of its row (blockIdx.y), 16-byte words (8 bf16 or 4 fp32 per
+// thread and step).
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ y_perm, const int32_t* __restrict__ dst_row,
                                                       const float* __restrict__ topk_weight, const uint4* __restrict__ y_shared,
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
     wts[threadIdx.x] = topk_weight[static_cast<int64_t>(t) * k + threadIdx.x];
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < row_words; c += 256) {
+  for (int c = blockIdx.y * 256 + threadIdx.x; c < row_words; c += 256 * gridDim.y) {
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     uint4 sh = make_uint4(0, 0, 0, 0);
     if (y_shared) sh = y_shared[static_cast<int64_t>(t) * row_words + c];
@@ -103,12 +104,15 @@ int launch_combine(revive_ctx* ctx, const void* y_perm, const int32_t* dst_row, 
                    int T, void* out, hipStream_t stream) {
   const revive_config& c = ctx->cfg;
   const int row_words = static_cast<int>(c.H * ctx->elem / 16);
+  // Few tokens: a workgroup for every 256 words of a row, so that a row's gathers are all out at once (1 token,
+  // H = 7168: 10 -> 6 us between events).  From two workgroups per CU on the tokens alone fill the chip.
+  const dim3 grid(T, T < 512 ? ceil_div(row_words, 256) : 1);
   KernelTimer timer(ctx, REVIVE_K_COMBINE, stream);
   if (c.dtype == REVIVE_DTYPE_BF16)
-    hipLaunchKernelGGL(combine_kernel<true>, dim3(T), dim3(256), 0, stream, static_cast<const uint4*>(y_perm), dst_row,
+    hipLaunchKernelGGL(combine_kernel<true>, grid, dim3(256), 0, stream, static_cast<const uint4*>(y_perm), dst_row,
                        topk_weight, static_cast<const uint4*>(y_shared), c.k, row_words, static_cast<uint4*>(out));
   else
-    hipLaunchKernelGGL(combine_kernel<false>, dim3(T), dim3(256), 0, stream, static_cast<const uint4*>(y_perm), dst_row,
+    hipLaunchKernelGGL(combine_kernel<false>, grid, dim3(256), 0, stream, static_cast<const uint4*>(y_perm), dst_row,
                        topk_weight, static_cast<const uint4*>(y_shared), c.k, row_words, static_cast<uint4*>(out));
   return check_hip(ctx, hipGetLastError(), "combine launch");
 }
