@@ -160,7 +160,11 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
 // 5.17 -> 4.87; at 114 rows a slot often needs a second row-tile of 128 and it loses (5.70 -> 5.89).  The
 // shared expert's rows go along in the same launches however many they are (k = 1, 8192 tokens: 5.16 -> 4.85).
 // Alone, the shared expert streams as long as its rows are one row-tile.
-constexpr int kStreamRowsPerSlot = 96;
+// Weights that the 256 MB last-level cache holds come in faster than HBM streams; above 16 rows per slot the
+// streaming kernel's set-up then costs more than it saves (141 MB, 61 rows: 84 -> 88 us; 27 MB, 20 rows: 58 ->
+// 59; 226 MB, 40 rows: 108 -> 104; 113 MB, 14 rows: 71 -> 65).
+constexpr int kStreamRowsPerSlot = 96, kStreamRowsPerSlotCached = 16;
+constexpr int64_t kCachedWeights = 192ll << 20;
 constexpr int kStreamDenseRows = 128;
 
 // One FFN call: routed experts, shared expert, or both.
@@ -272,7 +276,8 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
   const FfnArgs f{x_perm, slot_offsets, w_gate_up, w_down, ctx->d_ws + ctx->ws.off_h, y_perm, static_cast<int>(N),
                   x, w_sh_gate_up, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, y_shared ? T : 0};
   if (c.dtype != REVIVE_DTYPE_BF16) return f32_ffn<GU, DN>(ctx, f, stream);
-  if (N <= static_cast<int64_t>(kStreamRowsPerSlot) * ctx->P) return stream_ffn<GU, DN>(ctx, f, stream);
+  const bool cached = static_cast<int64_t>(ctx->P) * 6 * c.H * c.I <= kCachedWeights;
+  if (N <= static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return stream_ffn<GU, DN>(ctx, f, stream);
   MTile* tiles = reinterpret_cast<MTile*>(ctx->d_ws + ctx->ws.off_tiles);
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);
   {
