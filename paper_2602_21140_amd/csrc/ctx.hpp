@@ -31,15 +31,23 @@ struct MTile {
   const void* w[2];     // the group's gate/up and down matrices (null when the caller uses a table)
 };
 
-// Rows [row_begin, row_end) of tile j of a group with rows [begin, end) cut into G = ceil(rows / tile_m)
-// tiles.  Tiles are tile_m rows high except the last two, which share their rows about evenly (the
+// Row-tiles of a group with `rows` rows.  tall_m > tile_m: the largest number of rows that one (the only) tile of
+// a group may have, for kernels that hold such a tile.
+__host__ __device__ inline int tiles_of(int rows, int tile_m, int tall_m) {
+  return rows <= 0 ? 0 : rows <= tall_m ? 1 : (rows + tile_m - 1) / tile_m;
+}
+
+// Rows [row_begin, row_end) of tile j of a group with rows [begin, end) cut into G tiles (tiles_of).  Tiles are tile_m rows high except the last two, which share their rows about evenly (the
 // first of them rounded up to 64 rows): a slot that overflows a tile by a few rows would otherwise
 // get a second tile that streams the whole weight matrix for almost no work, ahead of and out of
 // step with its neighbour, so that the weights come from HBM twice.  The split costs no extra
 // MFMA time: the 32-row sub-tiles are dealt to two wavefront rows, and ceil(a/2) + ceil(b/2) over
 // the two tiles is the same for both ways of cutting.
 __host__ __device__ inline void tile_span(int begin, int end, int G, int j, int tile_m, int& row_begin, int& row_end) {
-  if (G >= 2 && j >= G - 2) {
+  if (G == 1) {
+    row_begin = begin;
+    row_end = end;
+  } else if (j >= G - 2) {
     const int base = begin + (G - 2) * tile_m;
     const int both = end - base;  // tile_m + rows of the last tile
     int a = ((both + 1) / 2 + 63) & ~63;

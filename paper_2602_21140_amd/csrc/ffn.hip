@@ -16,7 +16,7 @@ namespace revive {
 
 namespace {
 
-__global__ __launch_bounds__(kMaxP) void ffn_tiles_kernel(const int32_t* __restrict__ slot_offsets, int P, int tile_m,
+__global__ __launch_bounds__(kMaxP) void ffn_tiles_kernel(const int32_t* __restrict__ slot_offsets, int P, int tile_m, int tall_m,
                                                           const void* const* __restrict__ w_gate_up,
                                                           const void* const* __restrict__ w_down,
                                                           MTile* __restrict__ tiles, int32_t* __restrict__ tile_count) {
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kMaxP) void ffn_tiles_kernel(const int32_t* __restr
     first = slot_offsets[p];
     end = slot_offsets[p + 1];
   }
-  const int mine = end > first ? (end - first + tile_m - 1) / tile_m : 0;
+  const int mine = tiles_of(end - first, tile_m, tall_m);
   const int lane = p & 63, wave = p >> 6;
   int incl = mine;
 #pragma unroll
@@ -80,7 +80,14 @@ __global__ __launch_bounds__(kMaxP) void ffn_tiles_kernel(const int32_t* __restr
 // Tile shapes of the bf16 GEMMs: 256 x 256 outputs per workgroup of 8 wavefronts (2 x 4), K in
 // steps of 32 through a four-stage ring of asynchronous global->LDS copies.  Problems too small
 // to give every CU a 256 x 256 tile use 256 x 128 tiles on 4 wavefronts (two workgroups per CU).
-constexpr int kBM = kTileM_bf16, kBN = 256, kWM = 2, kWN = 4;
+//
+// A slot of 257 to 320 rows is one tall tile instead of two: a second tile with few rows costs half a full one
+// and reads the weights again.  H = 7168, I = 2048, 8192 tokens over 261 live slots (half of them hold more than
+// 256 rows): gate/up 4.83 -> 4.40 ms, down 2.43 -> 2.25; 3000 tokens of the smaller layer (286 rows): 0.34 ->
+// 0.32 and 0.18 -> 0.165.  All tiles 320 rows high were slower where 256 does as well: 8192 tokens the same,
+// but 170 rows +4 %, 341 rows +4 %, 607 rows +2.5 % (more rows copied than there are; two tiles of 300 rows
+// against three of 200: +5 %).
+constexpr int kBM = 320, kBN = 256, kWM = 2, kWN = 4;
 
 struct Bf16Ffn {  // one SwiGLU FFN: rows of A -> h -> y
   const void* A;
@@ -134,7 +141,7 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
     int rc;
     if (small) {
       GemmArgs a0 = gate_up_args(ctx, f0, 64);
-      rc = launch_gemm_bf16_dma<kBM, 128, 2, 2, EPI_SWIGLU, K_GATE_UP>(ctx, a0, f0.max_m_tiles, nullptr, 0, stream);
+      rc = launch_gemm_bf16_dma<kTileM_bf16, 128, 2, 2, EPI_SWIGLU, K_GATE_UP>(ctx, a0, f0.max_m_tiles, nullptr, 0, stream);
     } else {
       GemmArgs a0 = gate_up_args(ctx, f0, kBN / 2), a1{};
       if (f1) a1 = gate_up_args(ctx, *f1, kBN / 2);
@@ -146,7 +153,7 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
   KernelTimer timer(ctx, K_DOWN, stream);
   if (small) {
     GemmArgs d0 = down_args(ctx, f0, 128);
-    return launch_gemm_bf16_dma<kBM, 128, 2, 2, EPI_BF16, K_DOWN>(ctx, d0, f0.max_m_tiles, nullptr, 0, stream);
+    return launch_gemm_bf16_dma<kTileM_bf16, 128, 2, 2, EPI_BF16, K_DOWN>(ctx, d0, f0.max_m_tiles, nullptr, 0, stream);
   }
   GemmArgs d0 = down_args(ctx, f0, kBN), d1{};
   if (f1) d1 = down_args(ctx, *f1, kBN);
@@ -282,7 +289,7 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);
   {
     KernelTimer timer(ctx, REVIVE_K_FFN_TILES, stream);
-    hipLaunchKernelGGL(ffn_tiles_kernel, dim3(1), dim3(kMaxP), 0, stream, slot_offsets, ctx->P, kTileM_bf16, w_gate_up, w_down, tiles,
+    hipLaunchKernelGGL(ffn_tiles_kernel, dim3(1), dim3(kMaxP), 0, stream, slot_offsets, ctx->P, kTileM_bf16, kBM, w_gate_up, w_down, tiles,
                        tile_count);
     REVIVE_HIP(ctx, hipGetLastError());
   }

@@ -326,6 +326,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmA
 // s_waitcnt immediate (gfx9 encoding) for "vmcnt(vm) lgkmcnt(0)", export counter ignored.
 __host__ __device__ constexpr int waitcnt_vm_lgkm0(int vm) { return (vm & 0xF) | ((vm >> 4) << 14) | (0x7 << 4) | (0 << 8); }
 
+// Row sub-tiles of 32 rows whose outputs all wavefronts can hold in LDS at a time.
+constexpr int epilogue_pass(int tm, int waves, int row_bytes) {
+  int pass = tm;
+  while (waves * pass * 32 * row_bytes > 160 * 1024) pass = (pass + 1) / 2;
+  return pass;
+}
+
 __device__ __forceinline__ int swz32(int row) { return (row >> 2) & 3; }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID, int STAGES = 4>
@@ -336,10 +343,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   constexpr int BN_OUT = EPI == EPI_SWIGLU ? BN / 2 : BN;
   constexpr int D = STAGES - 1;  // copies run D K-steps ahead of the MFMAs
   constexpr int STAGE = (BM + BN) * 64;       // bytes
-  constexpr int CP_A = BM / 16 / NW, CP_B = BN / 16 / NW;  // copy instructions per wavefront and stage
-  constexpr int CP = CP_A + CP_B;
-  static_assert(BM % (16 * NW) == 0 && BN % (16 * NW) == 0, "copy split");
-  static_assert(TM <= 4, "row sub-tile dispatch below covers up to four");
+  // Row-tiles are BM0 rows high; BM may be higher by a quarter, for a slot that overflows one row-tile by less
+  // than that (see tiles_of).  Copy instructions per wavefront and stage: CP_B + CP_A, and in such a tall tile
+  // the first half of the wavefronts (which then issues CPT) takes one block of A more each.
+  constexpr int BM0 = BM > kTileM_bf16 ? kTileM_bf16 : BM;
+  constexpr int CP_B = BN / 16 / NW, CP_A = BM0 / 16 / NW, CP = CP_A + CP_B, CPT = CP + (BM > BM0);
+  static_assert(BM0 % (16 * NW) == 0 && BN % (16 * NW) == 0 && (BM == BM0 || BM - BM0 == NW / 2 * 16), "copy split");
+  static_assert(BM0 / WAVES_M / 32 <= 4, "row sub-tile dispatch below covers up to four");
   static_assert(STAGES >= 3 && STAGES <= 5, "prologue and tail are written for 2 to 4 steps of copy-ahead");
   static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
   typedef __attribute__((address_space(1))) const void* gptr;
@@ -354,8 +364,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   // A dense problem (no tile list) is split by whole row-tiles instead: XCD x owns n_m / 8 of them
   // (the first n_m % 8 XCDs one more), so that the order below can walk its own block of the
   // output; its workgroup budget per XCD is that of the XCDs with one more.
-  const int nm0 = a2.p0.tiles ? *a2.p0.tile_count : (a2.p0.M + BM - 1) / BM;
-  const int nm1 = a2.two ? (a2.p1.tiles ? *a2.p1.tile_count : (a2.p1.M + BM - 1) / BM) : 0;
+  const int nm0 = a2.p0.tiles ? *a2.p0.tile_count : (a2.p0.M + BM0 - 1) / BM0;
+  const int nm1 = a2.two ? (a2.p1.tiles ? *a2.p1.tile_count : (a2.p1.M + BM0 - 1) / BM0) : 0;
   const int t0 = nm0 * a2.p0.n_col_tiles, t1 = nm1 * a2.p1.n_col_tiles;
   const int px0 = a2.p0.tiles ? (t0 + 7) >> 3 : ((nm0 + 7) >> 3) * a2.p0.n_col_tiles;
   const int px1 = !a2.two ? 0 : a2.p1.tiles ? (t1 + 7) >> 3 : ((nm1 + 7) >> 3) * a2.p1.n_col_tiles;
@@ -416,11 +426,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
         j = r - n_idx * in_group;
       }
     }
-    tile_span(t.group_begin, t.group_end, in_group, j, BM, row_begin, row_end);
+    tile_span(t.group_begin, t.group_end, in_group, j, BM0, row_begin, row_end);
     Bbase = static_cast<const unsigned char*>(g.b_sel >= 0 ? t.w[g.b_sel] : (g.B_tab ? g.B_tab[t.group] : g.B_one));
   } else {
-    row_begin = m_idx * BM;
-    row_end = min(g.M, row_begin + BM);
+    row_begin = m_idx * BM0;
+    row_end = min(g.M, row_begin + BM0);
     Bbase = static_cast<const unsigned char*>(g.B_one);
   }
   const unsigned char* Abase = static_cast<const unsigned char*>(g.A);
@@ -436,12 +446,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   // The source address of a copy is a wavefront-uniform 64-bit base (the tile's first row of A, the
   // weight matrix) kept in scalar registers plus a 32-bit per-lane byte offset that never changes:
   // walking K only advances the two scalar bases, no vector arithmetic.
-  uint32_t cp_off[CP];
-  int cp_dst[CP];  // wavefront-uniform LDS offset of the 1 KiB window inside a stage
+  uint32_t cp_off[CPT];
+  int cp_dst[CPT];  // wavefront-uniform LDS offset of the 1 KiB window inside a stage
 #pragma unroll
-  for (int i = 0; i < CP; ++i) {
-    const bool isA = i < CP_A;
-    const int blk = isA ? wave * CP_A + i : wave * CP_B + (i - CP_A);
+  for (int i = 0; i < CPT; ++i) {  // the B blocks first, a tall tile's additional block last
+    const bool isA = i >= CP_B;
+    const int blk = !isA ? wave * CP_B + i : i < CP ? wave * CP_A + (i - CP_B) : BM0 / 16 + wave;
     const int row = blk * 16 + (lane >> 2);
     const int chunk = (lane & 3) ^ swz32(row);
     if (isA) {
@@ -490,30 +500,34 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   const uint64_t kstep_a = g.a_rows > 0 ? static_cast<uint64_t>(g.a_rows) * 64 : 64;
   const uint64_t base_b = uniform64(reinterpret_cast<uint64_t>(Bbase));
   const uint32_t kstep_b = g.b_tiled ? kWeightTileRows * kWeightTileK * 2 : 64;  // bytes between K-steps of B
-  auto issue_copy = [&](int kt) {
+  auto issue_copy = [&](int kt, auto cp_tag) {
     const uint32_t stage = smem_lds + stage_of(kt) * STAGE;
     const uint64_t src_a = base_a + static_cast<uint64_t>(kt) * kstep_a;
     const uint64_t src_b = base_b + static_cast<uint64_t>(kt) * kstep_b;
 #pragma unroll
-    for (int i = 0; i < CP; ++i) {
+    for (int i = 0; i < decltype(cp_tag)::value; ++i) {
       const uint32_t dst = __builtin_amdgcn_readfirstlane(stage + cp_dst[i]);
-      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(cp_off[i]), "s"(i < CP_A ? src_a : src_b), "s"(dst) : "memory", "m0");
+      const uint32_t off = cp_off[i];
+      const uint64_t src = i < CP_B ? src_b : src_a;
+      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src), "s"(dst) : "memory", "m0");
     }
   };
 
   // The same with the ring position PH of the destination stage known at compile time.
-  auto issue_copy_at = [&](int kt, auto ph_tag) {
+  auto issue_copy_at = [&](int kt, auto ph_tag, auto cp_tag) {
     constexpr int PH = decltype(ph_tag)::value;
     const uint64_t src_a = base_a + static_cast<uint64_t>(kt) * kstep_a;
     const uint64_t src_b = base_b + static_cast<uint64_t>(kt) * kstep_b;
 #pragma unroll
-    for (int i = 0; i < CP; ++i) {
+    for (int i = 0; i < decltype(cp_tag)::value; ++i) {
       const uint32_t dst = __builtin_amdgcn_readfirstlane(smem_lds + cp_dst[i] + PH * STAGE);
       const uint32_t off = cp_off[i];
-      const uint64_t src = i < CP_A ? src_a : src_b;
+      const uint64_t src = i < CP_B ? src_b : src_a;
       asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src), "s"(dst) : "memory", "m0");
     }
   };
+  using Cp = std::integral_constant<int, CP>;
+  using CpTall = std::integral_constant<int, CPT>;
 
   // ---- per-lane fragment addresses.  32-row sub-tiles are dealt round-robin to the wavefront
   // rows (sub-tile tm*WAVES_M + wm), so a ragged row-tile keeps every wavefront equally busy.
@@ -556,8 +570,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   const int n_sub = (row_end - row_begin + 31) >> 5;  // sub-tiles holding at least one valid row
   const int tm_valid = min(TM, max(0, (n_sub - wm + WAVES_M - 1) / WAVES_M));
 
-  auto run = [&](auto tmv_tag) {
-    constexpr int TMV = decltype(tmv_tag)::value;
+  // early_tag: copies per stage of the first half of the wavefronts.
+  auto run = [&](auto tmv_tag, auto early_tag) {
+    constexpr int TMV = decltype(tmv_tag)::value, CPE = decltype(early_tag)::value;
     auto load_frags = [&](const unsigned char* base, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
       if (TMV == 0) return;
       const unsigned char* pa = base + a_off[ks];
@@ -582,7 +597,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
       constexpr int VM = decltype(vm_tag)::value;
       const unsigned char* cur = smem + stage_of(kt) * STAGE;
       // stage (kt+3)%4 held step kt-1, which every wavefront finished reading before the last barrier
-      if (COPY) issue_copy(kt + D);
+      if (COPY) issue_copy(kt + D, early_tag);
       load_frags(cur, 1, af1, bf1);
       __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the MFMAs they overlap with
       mfma_step(af0, bf0);
@@ -638,12 +653,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
     // immediates and the K loop, unrolled by four, carries no vector ALU instruction at all.
     auto step_at = [&](int kt, auto ph_tag) {
       constexpr int PH = decltype(ph_tag)::value;
-      issue_copy_at(kt + D, std::integral_constant<int, (PH + D) & 3>{});
+      issue_copy_at(kt + D, std::integral_constant<int, (PH + D) & 3>{}, early_tag);
       __builtin_amdgcn_sched_barrier(0);
       mfma_reads_at(af0, bf0, ph_tag, 1, af1, bf1);
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((D - 1) * CP));
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((D - 1) * CPE));
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       mfma_reads_at(af1, bf1, std::integral_constant<int, (PH + 1) & 3>{}, 0, af0, bf0);
@@ -657,7 +672,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
       __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((D - 1) * CP));
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      issue_copy_at(kt + D + 1, ph_tag);  // (PH + 4) % 4: into this step's own stage
+      issue_copy_at(kt + D + 1, ph_tag, Cp{});  // (PH + 4) % 4: into this step's own stage
       __builtin_amdgcn_sched_barrier(0);
       mfma_reads_at(af1, bf1, std::integral_constant<int, (PH + 1) & 3>{}, 0, af0, bf0);
       __builtin_amdgcn_sched_barrier(0);
@@ -686,7 +701,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
         __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(VM));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (COPY) issue_copy(kt + D + 1);  // into this step's own stage: all its reads ended before the barrier
+        if (COPY) issue_copy(kt + D + 1, Cp{});  // into this step's own stage: all its reads ended before the barrier
         load_frags(smem + stage_of(kt + 1) * STAGE, 0, af0, bf0);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -701,48 +716,58 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
       if (kt + 1 < KT) { fn(kt, F{}, std::integral_constant<int, 0>{}, F{}); ++kt; }
       fn(kt, F{}, std::integral_constant<int, 0>{}, T{});
     };
-    constexpr int VM_STEADY = (D - 1) * CP;
     if (wave < NW / 2) {
       load_frags(smem, 0, af0, bf0);
       int kt = 0;
       if constexpr (STAGES == 4)  // kt stays a multiple of four here: ring position = unrolled position
         for (; kt + D + 3 < KT; kt += 4) { step_at(kt, P0{}); step_at(kt + 1, P1{}); step_at(kt + 2, P2{}); step_at(kt + 3, P3{}); }
-      for (; kt + D < KT; ++kt) step(kt, T{}, std::integral_constant<int, VM_STEADY>{}, F{});
+      for (; kt + D < KT; ++kt) step(kt, T{}, std::integral_constant<int, (D - 1) * CPE>{}, F{});
       // here kt + D >= KT: the copies of every remaining step are already issued
-      if (D >= 4 && kt + 3 < KT) { step(kt, F{}, std::integral_constant<int, 2 * CP>{}, F{}); ++kt; }
-      if (D >= 3 && kt + 2 < KT) { step(kt, F{}, std::integral_constant<int, CP>{}, F{}); ++kt; }
+      if (D >= 4 && kt + 3 < KT) { step(kt, F{}, std::integral_constant<int, 2 * CPE>{}, F{}); ++kt; }
+      if (D >= 3 && kt + 2 < KT) { step(kt, F{}, std::integral_constant<int, CPE>{}, F{}); ++kt; }
       if (kt + 1 < KT) { step(kt, F{}, std::integral_constant<int, 0>{}, F{}); ++kt; }
       step(kt, F{}, std::integral_constant<int, 0>{}, T{});
     } else {
-      if (KT > D) issue_copy(D);
+      if (KT > D) issue_copy(D, Cp{});
       load_frags(smem, 0, af0, bf0);
       int kt = 0;
       if constexpr (STAGES == 4)
         for (; kt + D + 4 < KT; kt += 4) { step_late_at(kt, P0{}); step_late_at(kt + 1, P1{}); step_late_at(kt + 2, P2{}); step_late_at(kt + 3, P3{}); }
-      for (; kt + D + 1 < KT; ++kt) step_late(kt, T{}, std::integral_constant<int, VM_STEADY>{}, F{});
+      for (; kt + D + 1 < KT; ++kt) step_late(kt, T{}, std::integral_constant<int, (D - 1) * CP>{}, F{});
       tail(step_late, kt);
     }
   };
 
   // prologue: copies of the first D steps, then publish step 0
-  issue_copy(0);
-  if (KT > 1) issue_copy(1);
-  if (D >= 3 && KT > 2) issue_copy(2);
-  if (D >= 4 && KT > 3) issue_copy(3);
-  asm volatile("" ::: "memory");
-  if (D >= 4 && KT > 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(3 * CP));
-  else if (D >= 3 && KT > 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * CP));
-  else if (KT > 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(CP));
-  else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  auto prologue = [&](auto cp_tag) {
+    constexpr int CP = decltype(cp_tag)::value;
+    issue_copy(0, cp_tag);
+    if (KT > 1) issue_copy(1, cp_tag);
+    if (D >= 3 && KT > 2) issue_copy(2, cp_tag);
+    if (D >= 4 && KT > 3) issue_copy(3, cp_tag);
+    asm volatile("" ::: "memory");
+    if (D >= 4 && KT > 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(3 * CP));
+    else if (D >= 3 && KT > 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * CP));
+    else if (KT > 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(CP));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  };
+  const bool tall = BM > BM0 && row_end - row_begin > BM0;
+  if (tall && wave < NW / 2) prologue(CpTall{});
+  else prologue(Cp{});
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
-  switch (tm_valid) {
-    case 0: run(std::integral_constant<int, 0>{}); break;
-    case 1: run(std::integral_constant<int, 1>{}); break;
-    case 2: run(std::integral_constant<int, (TM >= 2 ? 2 : TM)>{}); break;
-    case 3: run(std::integral_constant<int, (TM >= 3 ? 3 : TM)>{}); break;
-    default: run(std::integral_constant<int, TM>{}); break;
+  if (tall) {  // at least 2 * TM - 1 sub-tiles
+    if (tm_valid == TM) run(std::integral_constant<int, TM>{}, CpTall{});
+    else run(std::integral_constant<int, (TM > 1 ? TM - 1 : TM)>{}, CpTall{});
+  } else {
+    switch (tm_valid) {
+      case 0: run(std::integral_constant<int, 0>{}, Cp{}); break;
+      case 1: run(std::integral_constant<int, 1>{}, Cp{}); break;
+      case 2: run(std::integral_constant<int, (TM >= 2 ? 2 : TM)>{}, Cp{}); break;
+      case 3: run(std::integral_constant<int, (TM >= 3 ? 3 : TM)>{}, Cp{}); break;
+      default: run(std::integral_constant<int, (TM >= 4 ? 4 : TM)>{}, Cp{}); break;
+    }
   }
 
   // ---- epilogue.  Per 32x32 tile a lane holds, for q = 0..3, the four columns
@@ -753,37 +778,41 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   constexpr int WN_OUT = EPI == EPI_SWIGLU ? WN / 2 : WN;
   static_assert(EPI != EPI_F32, "this kernel stores bf16");
   constexpr int ROWB = WN_OUT * 2 + 8;          // bytes between rows of the wavefront's LDS slice
-  constexpr int SLICE = TM * 32 * ROWB;
+  constexpr int PASS = epilogue_pass(TM, NW, ROWB);  // row sub-tiles that fit the LDS at a time
+  constexpr int SLICE = PASS * 32 * ROWB;
   constexpr int LPR = WN_OUT * 2 / 16;          // lanes per row when reading back
   constexpr int RPI = 64 / LPR;                 // rows per read-back instruction
   __syncthreads();                              // every wavefront is done with the copy stages
   unsigned char* slice = smem + wave * SLICE;
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm) {
-    if (tm >= tm_valid) break;
-#pragma unroll
-    for (int tn = 0; tn < TN_OUT; ++tn) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (EPI == EPI_SWIGLU) v[r] = silu_f32(acc[tm][tn][q * 4 + r]) * acc[tm][tn + TN / 2][q * 4 + r];
-          else v[r] = acc[tm][tn][q * 4 + r];
-        }
-        u32x2 o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-        *reinterpret_cast<u32x2*>(slice + (tm * 32 + (lane & 31)) * ROWB + (tn * 32 + q * 8 + (lane >> 5) * 4) * 2) = o;
-      }
-    }
-  }
-  // read back: lane l takes 16 bytes (8 columns) of row l / LPR of each group of RPI rows
   const int rcol = (lane % LPR) * 8;
   const int col = n0 + wn * WN_OUT + rcol;
-  if (col < g.n_out) {  // n_out is a multiple of 8: a word is entirely inside or outside
 #pragma unroll
-    for (int it = 0; it < TM * 32 / RPI; ++it) {
+  for (int p0 = 0; p0 < TM; p0 += PASS) {
+    if (p0 >= tm_valid) break;
+#pragma unroll
+    for (int tm = p0; tm < p0 + PASS && tm < TM; ++tm) {
+      if (tm >= tm_valid) break;
+#pragma unroll
+      for (int tn = 0; tn < TN_OUT; ++tn) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (EPI == EPI_SWIGLU) v[r] = silu_f32(acc[tm][tn][q * 4 + r]) * acc[tm][tn + TN / 2][q * 4 + r];
+            else v[r] = acc[tm][tn][q * 4 + r];
+          }
+          u32x2 o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+          *reinterpret_cast<u32x2*>(slice + ((tm - p0) * 32 + (lane & 31)) * ROWB + (tn * 32 + q * 8 + (lane >> 5) * 4) * 2) = o;
+        }
+      }
+    }
+    // read back: lane l takes 16 bytes (8 columns) of row l / LPR of each group of RPI rows
+    if (col >= g.n_out) continue;  // n_out is a multiple of 8: a word is entirely inside or outside
+#pragma unroll
+    for (int it = 0; it < PASS * 32 / RPI; ++it) {
       const int lrow = it * RPI + lane / LPR;     // row inside the wavefront's slice
-      const int tm = lrow >> 5;
+      const int tm = p0 + (lrow >> 5);
       if (tm >= tm_valid) break;
       const int row = row_begin + (tm * WAVES_M + wm) * 32 + (lrow & 31);
       if (row < row_end) {
@@ -818,7 +847,8 @@ int launch_gemm_bf16_dma(revive_ctx* ctx, const GemmArgs& p0, int max_m_tiles0, 
                          hipStream_t stream) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WN_OUT_ = (EPI == EPI_SWIGLU ? BN / 2 : BN) / WAVES_N;
-  constexpr size_t lds_epi = static_cast<size_t>(WAVES_M * WAVES_N) * (BM / WAVES_M) * (WN_OUT_ * 2 + 8);
+  constexpr int rowb = WN_OUT_ * 2 + 8;
+  constexpr size_t lds_epi = static_cast<size_t>(WAVES_M * WAVES_N) * epilogue_pass(BM / WAVES_M / 32, WAVES_M * WAVES_N, rowb) * 32 * rowb;
   constexpr size_t lds_ring = STAGES * (BM + BN) * 64;
   constexpr size_t lds = lds_ring > lds_epi ? lds_ring : lds_epi;
   auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, EPI, KID, STAGES>;

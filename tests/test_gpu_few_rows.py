@@ -12,12 +12,15 @@ from paper_2602_21140_amd.binding import pack_expert
 pytestmark = pytest.mark.gpu
 
 EDGES = [1, 0, 16, 15, 17, 32, 33, 64, 0, 65, 2, 127, 128, 129, 256, 257, 300, 0]
+TALL = [257, 0, 288, 289, 319, 320, 321, 256, 577, 304, 272]
 # (H, I, rows of the slots): one group of K up to several, K no multiple of the ring, columns that are half a tile
 CASES = {
     "edges": (256, 192, EDGES + [0] * 90),  # up to 16 rows per slot on average the weights are always streamed
     "short_k": (64, 64, EDGES + [0] * 90),
     "odd_k": (704, 320, EDGES + [3] * 100),
     "tiles": (704, 320, EDGES + [3] * 10),  # above, at this size, the 256-row tiles
+    # one row-tile up to 320 rows, from the shortest K to several turns of the ring
+    "tall": (256, 192, TALL), "tall_short_k": (64, 64, TALL), "tall_long_k": (1088, 448, TALL),
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
