@@ -231,8 +231,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
 // 38 GB/s for loads in MFMA operand order), each wavefront turning its rows over to operand order in LDS of
 // its own.  A lane's 16 LDS bytes are consecutive K-elements of its row.
 //
-// Against the kernels that stood here (us): bf16, H = 7168, E = 256, T = 1: 53 -> 10, 192: 53 -> 11, 1003:
-// 55 -> 19, 4096: 59 -> 40; H = 2048, E = 64, T = 37: 12 -> 6, 4096: 13 -> 10; fp32, H = 1024, E = 32, T = 1001:
+// Against the kernels that stood here (us): bf16, H = 7168, E = 256, T = 1: 53 -> 10, 192: 53 -> 11; H = 2048, E = 64, T = 37: 12 -> 6, 4096: 13 -> 10; fp32, H = 1024, E = 32, T = 1001:
 // 59 -> 7.  The shorter sums are also nearer the exact ones (H = 7168: 5.3e-7 -> 1.8e-7).
 template <typename T> struct RouterMath;
 template <> struct RouterMath<uint16_t> {
@@ -380,18 +379,26 @@ int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* log
   const revive_config& c = ctx->cfg;
   KernelTimer timer(ctx, REVIVE_K_ROUTER_GEMM, stream);
   if (c.dtype != REVIVE_DTYPE_BF16) return router<float>(ctx, x, w, logits, T, stream);
-  const int64_t wide = static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128);
-  if (wide >= 512) {
-    // 128 x 128 tiles fill the chip twice over and read x and w half as often (T = 32768, E = 384: 267 us
-    // against 380; T = 8192, E = 256, 128 tiles: 64 against 64)
+  const bool small = c.E <= 128 && c.H % 256 == 0 && static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20);
+  if (T > 512 && !small) {
+    // Many tokens and a long or wide router: it is below 1 % of the layer here (H = 7168, E = 256, 1003 tokens:
+    // 55 us against 19), and this GEMM adds K up in one sequence, as it always has: with another order one of
+    // 8192 x 256 logits is near enough to a tie to pick another expert in every few calls.  (The small routers
+    // always had their K split, and their sums are five times nearer the exact ones.)  From 512 tiles of
+    // 128 x 128 on it is also the faster one (T = 32768, E = 384: 267 us against 380).
     GemmArgs a{};
     a.A = x; a.lda = c.H;
     a.B_one = w; a.ldb = c.H;
     a.C = logits; a.ldc = c.E;
     a.n_out = c.E; a.K = c.H;
     a.M = T;
-    a.n_col_tiles = ceil_div(c.E, 128);
-    return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
+    if (static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128) >= 512) {
+      // enough tiles to fill the chip twice over: wider tiles read x fewer times
+      a.n_col_tiles = ceil_div(c.E, 128);
+      return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
+    }
+    a.n_col_tiles = ceil_div(c.E, 64);
+    return launch_gemm_bf16<128, 64, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
   }
   return router<uint16_t>(ctx, x, w, logits, T, stream);
 }
