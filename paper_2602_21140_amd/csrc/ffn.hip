@@ -87,7 +87,10 @@ __global__ __launch_bounds__(kMaxP) void ffn_tiles_kernel(const int32_t* __restr
 // 0.32 and 0.18 -> 0.165.  All tiles 320 rows high were slower where 256 does as well: 8192 tokens the same,
 // but 170 rows +4 %, 341 rows +4 %, 607 rows +2.5 % (more rows copied than there are; two tiles of 300 rows
 // against three of 200: +5 %).
-constexpr int kBM = 320, kBN = 256, kWM = 2, kWN = 4;
+// Below 128 rows per slot on average hardly a slot is that full, and the kernel without tall tiles starts sooner
+// (a layer of 84 us: 45 rows per slot, 2 us).
+constexpr int kBN = 256, kWM = 2, kWN = 4;
+constexpr int kTallM_bf16 = 320, kTallRowsPerSlot = 128;
 
 struct Bf16Ffn {  // one SwiGLU FFN: rows of A -> h -> y
   const void* A;
@@ -130,7 +133,7 @@ GemmArgs down_args(const revive_ctx* ctx, const Bf16Ffn& f, int bn_out) {
 
 // Runs one FFN, or two in the same pair of launches (their tiles share the grid, which shortens
 // the partially filled last round of workgroups).  K_GATE_UP / K_DOWN name the launches.
-template <int K_GATE_UP, int K_DOWN>
+template <int BM, int K_GATE_UP, int K_DOWN>
 int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t stream) {
   const int H = ctx->cfg.H;
   const int64_t tiles_big_down = static_cast<int64_t>(f0.max_m_tiles) * ceil_div(H, kBN) +
@@ -145,7 +148,7 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
     } else {
       GemmArgs a0 = gate_up_args(ctx, f0, kBN / 2), a1{};
       if (f1) a1 = gate_up_args(ctx, *f1, kBN / 2);
-      rc = launch_gemm_bf16_dma<kBM, kBN, kWM, kWN, EPI_SWIGLU, K_GATE_UP>(ctx, a0, f0.max_m_tiles, f1 ? &a1 : nullptr,
+      rc = launch_gemm_bf16_dma<BM, kBN, kWM, kWN, EPI_SWIGLU, K_GATE_UP>(ctx, a0, f0.max_m_tiles, f1 ? &a1 : nullptr,
                                                                            f1 ? f1->max_m_tiles : 0, stream);
     }
     if (rc != REVIVE_OK) return rc;
@@ -157,7 +160,7 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
   }
   GemmArgs d0 = down_args(ctx, f0, kBN), d1{};
   if (f1) d1 = down_args(ctx, *f1, kBN);
-  return launch_gemm_bf16_dma<kBM, kBN, kWM, kWN, EPI_BF16, K_DOWN>(ctx, d0, f0.max_m_tiles, f1 ? &d1 : nullptr,
+  return launch_gemm_bf16_dma<BM, kBN, kWM, kWN, EPI_BF16, K_DOWN>(ctx, d0, f0.max_m_tiles, f1 ? &d1 : nullptr,
                                                                     f1 ? f1->max_m_tiles : 0, stream);
 }
 
@@ -287,19 +290,20 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
   if (N <= static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return stream_ffn<GU, DN>(ctx, f, stream);
   MTile* tiles = reinterpret_cast<MTile*>(ctx->d_ws + ctx->ws.off_tiles);
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);
+  const bool tall = N >= static_cast<int64_t>(kTallRowsPerSlot) * ctx->P;
   {
     KernelTimer timer(ctx, REVIVE_K_FFN_TILES, stream);
-    hipLaunchKernelGGL(ffn_tiles_kernel, dim3(1), dim3(kMaxP), 0, stream, slot_offsets, ctx->P, kTileM_bf16, kBM, w_gate_up, w_down, tiles,
-                       tile_count);
+    hipLaunchKernelGGL(ffn_tiles_kernel, dim3(1), dim3(kMaxP), 0, stream, slot_offsets, ctx->P, kTileM_bf16,
+                       tall ? kTallM_bf16 : kTileM_bf16, w_gate_up, w_down, tiles, tile_count);
     REVIVE_HIP(ctx, hipGetLastError());
   }
   Bf16Ffn routed{x_perm, w_gate_up, nullptr, w_down, nullptr, f.h, y_perm, c.I, tiles, tile_count, 0,
                  max_tiles(N, ctx->P, kTileM_bf16), f.N};
-  if (!y_shared) return bf16_ffn<GU, DN>(ctx, routed, nullptr, stream);
   // routed and shared experts in the same two launches
   Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, f.h_shared, y_shared, c.I_shared,
                  nullptr, nullptr, T, ceil_div(T, kTileM_bf16), T};
-  return bf16_ffn<GU, DN>(ctx, routed, &shared, stream);
+  const Bf16Ffn* second = y_shared ? &shared : nullptr;
+  return tall ? bf16_ffn<kTallM_bf16, GU, DN>(ctx, routed, second, stream) : bf16_ffn<kTileM_bf16, GU, DN>(ctx, routed, second, stream);
 }
 
 int launch_shared_ffn(revive_ctx* ctx, const void* x, const void* w_sh_gate_up, const void* w_sh_down, void* y_shared, int T,
@@ -311,7 +315,7 @@ int launch_shared_ffn(revive_ctx* ctx, const void* x, const void* w_sh_gate_up, 
   if (c.dtype != REVIVE_DTYPE_BF16) return f32_ffn<SGU, SDN>(ctx, f, stream);
   if (T <= kStreamDenseRows) return stream_ffn<SGU, SDN>(ctx, f, stream);
   Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, h_shared, y_shared, c.I_shared, nullptr, nullptr, T, ceil_div(T, kTileM_bf16), T};
-  return bf16_ffn<SGU, SDN>(ctx, shared, nullptr, stream);
+  return bf16_ffn<kTileM_bf16, SGU, SDN>(ctx, shared, nullptr, stream);
 }
 
 }  // namespace revive

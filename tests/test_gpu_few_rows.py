@@ -12,7 +12,7 @@ from paper_2602_21140_amd.binding import pack_expert
 pytestmark = pytest.mark.gpu
 
 EDGES = [1, 0, 16, 15, 17, 32, 33, 64, 0, 65, 2, 127, 128, 129, 256, 257, 300, 0]
-TALL = [257, 0, 288, 289, 319, 320, 321, 256, 577, 304, 272]
+TALL = [257, 0, 288, 289, 319, 320, 321, 256, 577, 304, 272]  # 128 rows per slot or more on average
 # (H, I, rows of the slots): one group of K up to several, K no multiple of the ring, columns that are half a tile
 CASES = {
     "edges": (256, 192, EDGES + [0] * 90),  # up to 16 rows per slot on average the weights are always streamed
