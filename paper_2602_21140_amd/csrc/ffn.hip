@@ -5,9 +5,10 @@
 // h = silu(X G_p) * (X U_p), y = h D_p.  Slots without rows (in particular every slot of a failed
 // rank, Sec. 3.5) produce no tile, so their weight pointers are never dereferenced.
 //
-// The row counts exist only on the device, so the launch is shaped by an upper bound: a small
-// kernel turns slot_offsets into a list of row-tiles (slot, first row, end row) and the GEMM
-// grids cover floor(N / tile) + P tiles; workgroups beyond the list's end exit at once.
+// The row counts exist only on the device, so the launch is shaped by an upper bound: the GEMM grids
+// cover floor(N / tile) + P row-tiles, and workgroups beyond the last one exit at once.  Which rows a
+// workgroup owns comes from a list that a small kernel makes of slot_offsets (bf16, many rows per
+// slot), or the workgroup works it out from slot_offsets itself (row_tiles.hpp).
 #include "gemm_bf16.hpp"
 #include "gemm_f32.hpp"
 #include "gemm_stream.hpp"

@@ -8,8 +8,8 @@
 namespace revive {
 
 // Slots' rows are cut into ceil(rows / tile_m) row-tiles each, slots in order.  Every wavefront works out
-// by itself which tile is its own (64 slots at a time, a prefix sum over the lanes; about 2 us, once),
-// which saves the launch that would build a list.
+// by itself which tile is its own (64 slots at a time, a prefix sum over the lanes), which saves the
+// launch of 5 us that would build a list; where workgroups are short the list is the better way.
 
 // Number of row-tiles of all slots.
 __device__ __forceinline__ int count_row_tiles(const int32_t* __restrict__ slot_offsets, int P, int tile_m) {
