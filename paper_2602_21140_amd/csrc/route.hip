@@ -231,8 +231,8 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
 // 38 GB/s for loads in MFMA operand order), each wavefront turning its rows over to operand order in LDS of
 // its own.  A lane's 16 LDS bytes are consecutive K-elements of its row.
 //
-// Against the kernels that stood here (us): bf16, H = 7168, E = 256, T = 1: 53 -> 10, 192: 53 -> 11; H = 2048, E = 64, T = 37: 12 -> 6, 4096: 13 -> 10; fp32, H = 1024, E = 32, T = 1001:
-// 59 -> 7.  The shorter sums are also nearer the exact ones (H = 7168: 5.3e-7 -> 1.8e-7).
+// Against the kernels that stood here (us): bf16, H = 2048, E = 64, T = 37: 12 -> 6, 4096: 13 -> 10; fp32, H = 1024, E = 32, T = 1001:
+// 59 -> 7. 
 template <typename T> struct RouterMath;
 template <> struct RouterMath<uint16_t> {
   static __device__ __forceinline__ f32x4 mac(u32x4 w, u32x4 x, f32x4 acc) {
@@ -361,15 +361,79 @@ int launch_router(revive_ctx* ctx, const void* x, const void* w, float* logits, 
   return check_hip(ctx, hipGetLastError(), "router launch");
 }
 
-// The largest tile that still gives every CU a workgroup: larger tiles read x and w fewer times.  us, all
-// sizes of tile tried: T = 512, E = 256, H = 7168: 17 (16 x 16), 17 (32 x 32); T = 1003: 28, 19; T = 2000:
-// 49, 29, 37 (64 x 64); T = 4096: 95, 52, 40.
+// The same product for few tokens with K summed in one sequence, in the very order of the GEMM that serves
+// more tokens (a token's logits must not depend on how many others are in the call).  16 tokens and 16
+// experts per workgroup; eight wavefronts fetch eight steps of 64 K-elements at a time, two rounds ahead, and
+// the first one multiplies them in order, 224 dependent MFMAs at H = 7168.  Between events, E = 256: 1 token
+// 53 -> 14 us, 192 tokens 53 -> 15 (10 and 11 with K split), 512 tokens 54 -> 21.
+__global__ __launch_bounds__(512, 2) void router_sequence_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+                                                                 float* __restrict__ logits, int T, int E, int H, int n_exp) {
+  constexpr int KS = 8, D = 2;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[D][KS][32 * 128];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t0 = blockIdx.x / n_exp * 16, e0 = blockIdx.x % n_exp * 16;
+  const int64_t row_bytes = static_cast<int64_t>(H) * 2;
+  const unsigned char* xb = reinterpret_cast<const unsigned char*>(x) + t0 * row_bytes;
+  const unsigned char* wb = reinterpret_cast<const unsigned char*>(w) + e0 * row_bytes;
+  const int steps = H >> 6;  // H is a multiple of 64
+  uint32_t off[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {  // rows past the last token or expert: the last one again, not stored
+    const int r = (i & 1) * 8 + (lane >> 3);
+    off[i] = static_cast<uint32_t>((i < 2 ? min(r, T - 1 - t0) : min(r, E - 1 - e0)) * row_bytes + (lane & 7) * 16);
+  }
+  u32x4 buf[D][4];
+  auto load = [&](int round, int d) {
+    const int64_t k = static_cast<int64_t>(min(round * KS + wave, steps - 1)) * 128;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) buf[d][i] = load_global_16B((i < 2 ? xb : wb) + off[i] + k);
+  };
+  const int r16 = lane & 15, quad = lane >> 4;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, d);
+  for (int r0 = 0; r0 * KS < steps; r0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = i * 8 + (lane >> 3);
+        *reinterpret_cast<u32x4*>(lds[d][wave] + r * 128 + (((lane & 7) ^ swz(r)) << 4)) = buf[d][i];
+      }
+      load(r0 + d + D, d);
+      // A buffer is written again two barriers later: the first wavefront has then read it.
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (wave == 0) {
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+          if ((r0 + d) * KS + q < steps) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const unsigned char* p = lds[d][q] + r16 * 128 + (((h * 4 + quad) ^ swz(r16)) << 4);
+              acc = RouterMath<uint16_t>::mac(*reinterpret_cast<const u32x4*>(p + 16 * 128), *reinterpret_cast<const u32x4*>(p), acc);
+            }
+          }
+        }
+      }
+    }
+  }
+  if (wave == 0 && t0 + r16 < T) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (e0 + quad * 4 + i < E) logits[static_cast<int64_t>(t0 + r16) * E + e0 + quad * 4 + i] = acc[i];
+  }
+}
+
+// The larger tile once it gives every CU a workgroup: it reads x and w half as often.  us: T = 512, E = 256,
+// H = 7168: 17 (16 x 16), 17 (32 x 32); T = 1003: 28, 19; T = 2000: 49, 29.  Both split K alike, so that a
+// token's logits do not depend on T.
 template <typename El>
 int router(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
   const int E = ctx->cfg.E;
-  auto blocks = [&](int m, int n) { return static_cast<int64_t>(ceil_div(T, m)) * ceil_div(E, n); };
-  if (E > 32 && blocks(64, 64) >= 256) return launch_router<El, 4, 4, 4, 2>(ctx, x, w, logits, T, stream);
-  if (E > 16 && blocks(32, 32) >= 256) return launch_router<El, 2, 2, 8, 2>(ctx, x, w, logits, T, stream);
+  if (E > 16 && static_cast<int64_t>(ceil_div(T, 32)) * ceil_div(E, 32) >= 256) return launch_router<El, 2, 2, 8, 2>(ctx, x, w, logits, T, stream);
   return launch_router<El, 1, 1, 8, 4>(ctx, x, w, logits, T, stream);
 }
 
@@ -379,28 +443,30 @@ int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* log
   const revive_config& c = ctx->cfg;
   KernelTimer timer(ctx, REVIVE_K_ROUTER_GEMM, stream);
   if (c.dtype != REVIVE_DTYPE_BF16) return router<float>(ctx, x, w, logits, T, stream);
-  const bool small = c.E <= 128 && c.H % 256 == 0 && static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20);
-  if (T > 512 && !small) {
-    // Many tokens and a long or wide router: it is below 1 % of the layer here (H = 7168, E = 256, 1003 tokens:
-    // 55 us against 19), and this GEMM adds K up in one sequence, as it always has: with another order one of
-    // 8192 x 256 logits is near enough to a tie to pick another expert in every few calls.  (The small routers
-    // always had their K split, and their sums are five times nearer the exact ones.)  From 512 tiles of
-    // 128 x 128 on it is also the faster one (T = 32768, E = 384: 267 us against 380).
-    GemmArgs a{};
-    a.A = x; a.lda = c.H;
-    a.B_one = w; a.ldb = c.H;
-    a.C = logits; a.ldc = c.E;
-    a.n_out = c.E; a.K = c.H;
-    a.M = T;
-    if (static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128) >= 512) {
-      // enough tiles to fill the chip twice over: wider tiles read x fewer times
-      a.n_col_tiles = ceil_div(c.E, 128);
-      return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
-    }
-    a.n_col_tiles = ceil_div(c.E, 64);
-    return launch_gemm_bf16<128, 64, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
+  const bool small = c.E <= 128 && c.H % 256 == 0;
+  if (small && static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20)) return router<uint16_t>(ctx, x, w, logits, T, stream);
+  // Many experts: K is summed in one sequence.  A K split is faster (1003 tokens, E = 256, H = 7168: 19 us against
+  // 55, 1 % of the layer) but another order moves one of 8192 x 256 logits across a near tie in every few calls.
+  // (The small routers always had their K split, and their sums are five times nearer the exact ones.)
+  if (!small && T <= 512) {
+    const int n_exp = ceil_div(c.E, 16);
+    hipLaunchKernelGGL(router_sequence_kernel, dim3(ceil_div(T, 16) * n_exp), dim3(512), 0, stream, static_cast<const uint16_t*>(x),
+                       static_cast<const uint16_t*>(w), logits, T, c.E, c.H, n_exp);
+    return check_hip(ctx, hipGetLastError(), "router_sequence launch");
   }
-  return router<uint16_t>(ctx, x, w, logits, T, stream);
+  GemmArgs a{};
+  a.A = x; a.lda = c.H;
+  a.B_one = w; a.ldb = c.H;
+  a.C = logits; a.ldc = c.E;
+  a.n_out = c.E; a.K = c.H;
+  a.M = T;
+  if (static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128) >= 512) {
+    // enough tiles to fill the chip twice over: wider tiles read x fewer times
+    a.n_col_tiles = ceil_div(c.E, 128);
+    return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
+  }
+  a.n_col_tiles = ceil_div(c.E, 64);
+  return launch_gemm_bf16<128, 64, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
 }
 
 int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk_logical, float* topk_weight,

@@ -42,3 +42,20 @@ def test_router_logits(T, E, H, dtype):
     assert ((logits.double() - exact).norm() / exact.norm()).item() < 2e-6
     assert torch.equal(logits, again)
     L.close()
+
+
+# a token's logits do not depend on the other tokens of the call: one, a few, as many as change the kernel
+@pytest.mark.parametrize("dtype,E,H", [("bf16", 256, 7168), ("bf16", 200, 448), ("bf16", 40, 576), ("bf16", 64, 2048), ("fp32", 64, 1000)])
+def test_logits_do_not_depend_on_the_token_count(dtype, E, H):
+    cfg = SimpleNamespace(T=9000, H=H, E=E, k=1, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype=dtype)
+    L = ReviveLayer(cfg)
+    L.set_placement(np.arange(E, dtype=np.int32))
+    L.update_map(np.zeros(1, dtype=np.uint8))
+    gen = torch.Generator(device="cuda").manual_seed(E)
+    x = torch.randn(9000, H, generator=gen, device="cuda").to(L.dtype)
+    w = (torch.randn(E, H, generator=gen, device="cuda") * H ** -0.5).to(L.dtype)
+    whole = L.route(x, w, 9000)[0]
+    for T in (1, 17, 500, 512, 513, 4100):
+        assert torch.equal(L.route(x[:T].contiguous(), w, T)[0], whole[:T]), T
+    L.close()
