@@ -100,6 +100,8 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
 
   if (GROUPED) {
     // Group score = sum of the two best live scores of the group (one if only one is live, -inf if none).
+    // A NaN must not enter the pairs: the smaller of a key and a NaN is the key, which would then count twice.
+    auto number = [NEG](float z) { return z > NEG ? z : NEG; };
     const int gsz = p.E / p.n_group;
     float top = NEG;  // li < HALF: best key of group li; else second best of group li - HALF
     if (gsz >= 8 && (gsz & (gsz - 1)) == 0 && gsz <= 64) {
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
       for (int q = 0; q < TPW; ++q) {
 #pragma unroll
         for (int i = 0; i < VALS; ++i) {
-          float m1 = key[q][i], m2 = NEG;
+          float m1 = number(key[q][i]), m2 = NEG;
           top2_step<0>(m1, m2);
           top2_step<1>(m1, m2);
           top2_step<2>(m1, m2);
@@ -130,7 +132,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
 #pragma unroll
           for (int i = 0; i < VALS; ++i) {
             const int e = lane + 64 * i;
-            const float z = e >= g * gsz && e < (g + 1) * gsz ? key[q][i] : NEG;
+            const float z = e >= g * gsz && e < (g + 1) * gsz ? number(key[q][i]) : NEG;
             m2 = fmaxf(m2, fminf(m1, z));
             m1 = fmaxf(m1, z);
           }

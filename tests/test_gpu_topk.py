@@ -41,3 +41,30 @@ def test_topk(E, n_group, topk_group, k, score_fn, T):
     assert np.array_equal(phys.cpu().numpy(), orc.remap(ref, m))
     assert np.abs(f64(w) - orc.gate_weights(s, ref)).max() < 2e-7  # one rounding to fp32 of a weight below 1
     L.close()
+
+
+# A logit that is not a number belongs to no order: its expert counts as absent, in the scores of its group too.
+@pytest.mark.parametrize("T", [301, 8193])
+@pytest.mark.parametrize("score_fn", ["softmax", "sigmoid"])
+@pytest.mark.parametrize("E,n_group,topk_group,k", [(64, 8, 3, 6), (256, 8, 4, 8), (512, 8, 4, 8), (200, 8, 2, 16), (256, 2, 1, 8), (512, 32, 8, 32)])
+def test_nan_logits_are_absent_from_their_group(E, n_group, topk_group, k, score_fn, T):
+    rng = np.random.default_rng(E + n_group)
+    cfg = SimpleNamespace(T=T, H=64, E=E, k=k, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+                          score_fn=score_fn, n_group=n_group, topk_group=topk_group, dtype="bf16")
+    L = ReviveLayer(cfg)
+    L.set_placement(np.arange(E, dtype=np.int32))
+    L.update_map(np.zeros(1, dtype=np.uint8))
+    z = rng.standard_normal((T, E)).astype(np.float32)
+    gsz = E // n_group
+    for g in range(n_group):  # beside each group's best: the neighbour that a reduction meets it with first
+        best = z[:, g * gsz:(g + 1) * gsz].argmax(axis=1)
+        t = np.arange(T)
+        for d in (best ^ 1, (best + 64) % gsz):
+            on = (d < gsz) & (d != best) & (t % 3 > 0)
+            z[t[on], g * gsz + d[on]] = np.nan
+    _, top, w, _ = L.route(None, None, T, logits=torch.from_numpy(z).cuda(), logits_given=True)
+    s = orc.scores(np.where(np.isnan(z), -np.inf, z.astype(np.float64)), score_fn)
+    ref = orc.select_topk(np.where(np.isnan(z), -np.inf, s), k, n_group, topk_group)
+    assert np.array_equal(top.cpu().numpy(), ref)
+    assert np.abs(f64(w) - orc.gate_weights(s, ref)).max() < 2e-7  # as above
+    L.close()
