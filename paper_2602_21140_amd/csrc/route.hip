@@ -196,6 +196,8 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
     }
   }
 
+  my_e = min(my_e, p.E - 1);  // a row of NaN holds no best key but the -inf of lanes without an expert: its ids stay valid
+
   // weights: score of the chosen expert over the sum of the chosen scores
   const int t = t0 + my_q;
   const double s = li < p.k ? score64(my_z) : 0.0;

@@ -68,3 +68,26 @@ def test_nan_logits_are_absent_from_their_group(E, n_group, topk_group, k, score
     assert np.array_equal(top.cpu().numpy(), ref)
     assert np.abs(f64(w) - orc.gate_weights(s, ref)).max() < 2e-7  # as above
     L.close()
+
+
+# A row of nothing but NaN has no best expert: its weights are NaN, its ids and slots stay those of experts, and the
+# other rows do not notice.
+@pytest.mark.parametrize("T", [5, 8193])
+@pytest.mark.parametrize("E,n_group,k", [(61, 1, 3), (64, 1, 3), (200, 8, 16), (200, 1, 32), (500, 4, 8)])
+def test_row_of_nan_keeps_valid_ids(E, n_group, k, T):
+    cfg = SimpleNamespace(T=T, H=64, E=E, k=k, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+                          score_fn="softmax", n_group=n_group, topk_group=n_group, dtype="bf16")
+    L = ReviveLayer(cfg)
+    L.set_placement(np.arange(E, dtype=np.int32)[::-1].copy())  # expert e in slot E - 1 - e
+    L.update_map(np.zeros(1, dtype=np.uint8))
+    logits = torch.randn(T, E, generator=torch.Generator().manual_seed(E)).cuda()
+    _, top, w, phys = (t.cpu().numpy() for t in L.route(None, None, T, logits=logits, logits_given=True))
+    bad = np.arange(T) % 4 == 2
+    logits[torch.from_numpy(bad).cuda()] = float("nan")
+    _, top2, w2, phys2 = (t.cpu().numpy() for t in L.route(None, None, T, logits=logits, logits_given=True))
+    for a, b in ((top, top2), (w, w2), (phys, phys2)):
+        assert np.array_equal(a[~bad], b[~bad])
+    assert np.isnan(w2[bad]).all()
+    assert (top2[bad] >= 0).all() and (top2[bad] < E).all()
+    assert np.array_equal(phys2, E - 1 - top2)
+    L.close()
