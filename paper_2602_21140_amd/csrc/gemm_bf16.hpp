@@ -107,7 +107,9 @@ __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ float silu_f32(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 
 // KID (the library's kernel id) only gives each use of the kernel its own symbol name in profiles.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID>
+// SLICES > 1: K is summed in SLICES parts, [K/64 * q / SLICES, K/64 * (q+1) / SLICES) steps of 64 elements, and the
+// partial sums are added in their order: the bits of a kernel whose wavefronts share K that way.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID, int SLICES = 1>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmArgs g) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -242,6 +244,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmA
   // workgroup synchronised *before* the last k-step's MFMAs, so that the first fragments of the
   // next stage are in flight while those MFMAs execute.
   const int KT = g.K >> 6;
+  f32x16 sum[TM][TN];  // SLICES > 1: the finished slices
+  int slice = 1, slice_end = KT / SLICES;  // empty slices (KT < SLICES) are passed over
+  if (SLICES > 1) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) sum[tm][tn] = acc[tm][tn];
+    while (slice_end == 0) slice_end = KT * ++slice / SLICES;
+  }
   bf16x8 af0[TM], bf0[TN], af1[TM], bf1[TN];
   load_global(0);
   store_lds(0);
@@ -264,6 +275,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmA
       load_frags(smem + ((kt + 1) & 1) * STAGE, 0, af0, bf0);
     }
     mfma_step(af1, bf1);
+    if (SLICES > 1 && kt + 1 == slice_end) {
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            sum[tm][tn][i] += acc[tm][tn][i];
+            acc[tm][tn][i] = 0.f;
+          }
+      while (slice < SLICES && slice_end == kt + 1) slice_end = KT * ++slice / SLICES;
+    }
+  }
+  if (SLICES > 1) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = sum[tm][tn];
   }
 
   // ---- epilogue.  Lane holds, per 32x32 tile, for q = 0..3 the four columns
@@ -829,11 +858,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
 
 // Launch helpers: grids cover `max_m_tiles` row-tiles per problem (upper bounds; surplus
 // workgroups exit at once).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID, int SLICES = 1>
 int launch_gemm_bf16(revive_ctx* ctx, const GemmArgs& args, int max_m_tiles, hipStream_t stream) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr size_t lds = 2 * (BM + BN) * 128;
-  auto kern = gemm_bf16_kernel<BM, BN, WAVES_M, WAVES_N, EPI, KID>;
+  auto kern = gemm_bf16_kernel<BM, BN, WAVES_M, WAVES_N, EPI, KID, SLICES>;
   REVIVE_HIP(ctx, allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
   const int64_t total = static_cast<int64_t>(max_m_tiles) * args.n_col_tiles;
   if (total <= 0) return REVIVE_OK;

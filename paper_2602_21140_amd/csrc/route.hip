@@ -235,8 +235,8 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
 // 38 GB/s for loads in MFMA operand order), each wavefront turning its rows over to operand order in LDS of
 // its own.  A lane's 16 LDS bytes are consecutive K-elements of its row.
 //
-// Against the kernels that stood here (us): bf16, H = 2048, E = 64, T = 37: 12 -> 6, 4096: 13 -> 10; fp32, H = 1024, E = 32, T = 1001:
-// 59 -> 7. 
+// Against the kernels that stood here, us between events: bf16, H = 2048, E = 64, 37 tokens 12 -> 6, 4096 tokens
+// 13 -> 10; fp32, H = 1024, E = 32, 1001 tokens 59 -> 7.
 template <typename T> struct RouterMath;
 template <> struct RouterMath<uint16_t> {
   static __device__ __forceinline__ f32x4 mac(u32x4 w, u32x4 x, f32x4 acc) {
@@ -431,14 +431,39 @@ __global__ __launch_bounds__(512, 2) void router_sequence_kernel(const uint16_t*
   }
 }
 
-// The larger tile once it gives every CU a workgroup: it reads x and w half as often.  us: T = 512, E = 256,
-// H = 7168: 17 (16 x 16), 17 (32 x 32); T = 1003: 28, 19; T = 2000: 49, 29.  Both split K alike, so that a
-// token's logits do not depend on T.
+// The larger tile once it gives every CU a workgroup: it reads x and w half as often.  us between events, bf16,
+// 16 x 16 against 32 x 32 tiles: E = 64, H = 2048, 2000 tokens (126 workgroups of the larger tile) 8.5 and 8.8, 4096
+// (256) 13.0 and 10.1; E = 128, H = 7168, 1000 tokens (128) 16.6 and 16.9, 2000 (252) 27.3 and 18.6, 4096 (512) 49
+// and 29; E = 32, H = 4096, 4096 tokens (128) 11.8 and 13.2, 8192 (256) 18.7 and 18.9.  Both split K alike.
+constexpr int kRouterSlices = 8;
 template <typename El>
 int router(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
   const int E = ctx->cfg.E;
-  if (E > 16 && static_cast<int64_t>(ceil_div(T, 32)) * ceil_div(E, 32) >= 256) return launch_router<El, 2, 2, 8, 2>(ctx, x, w, logits, T, stream);
-  return launch_router<El, 1, 1, 8, 4>(ctx, x, w, logits, T, stream);
+  if (E > 16 && static_cast<int64_t>(ceil_div(T, 32)) * ceil_div(E, 32) >= 256)
+    return launch_router<El, 2, 2, kRouterSlices, 2>(ctx, x, w, logits, T, stream);
+  return launch_router<El, 1, 1, kRouterSlices, 4>(ctx, x, w, logits, T, stream);
+}
+
+// Many tokens in bf16, K in one sequence or in the router kernel's slices.  128 x 128 tiles read x fewer times where
+// they still fill the chip twice over; with slices the second set of sums leaves them one workgroup per CU
+// (65 536 tokens, E = 64, H = 2048: 72 us against 47 for 128 x 64; E = 128: 81 and 80).
+template <int SLICES>
+int router_gemm(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
+  const revive_config& c = ctx->cfg;
+  GemmArgs a{};
+  a.A = x; a.lda = c.H;
+  a.B_one = w; a.ldb = c.H;
+  a.C = logits; a.ldc = c.E;
+  a.n_out = c.E; a.K = c.H;
+  a.M = T;
+  if constexpr (SLICES == 1) {
+    if (static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128) >= 512) {
+      a.n_col_tiles = ceil_div(c.E, 128);
+      return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
+    }
+  }
+  a.n_col_tiles = ceil_div(c.E, 64);
+  return launch_gemm_bf16<128, 64, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM, SLICES>(ctx, a, ceil_div(T, 128), stream);
 }
 
 }  // namespace
@@ -447,30 +472,25 @@ int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* log
   const revive_config& c = ctx->cfg;
   KernelTimer timer(ctx, REVIVE_K_ROUTER_GEMM, stream);
   if (c.dtype != REVIVE_DTYPE_BF16) return router<float>(ctx, x, w, logits, T, stream);
+  // The order in which K is summed follows from E and H alone, so that a token's logits do not depend on how many
+  // others are in the call.  Small routers: K in slices, in the router kernel or (many tokens, which it reads once
+  // per 32 experts) in the GEMM.  us between events: E = 64, H = 2048, 16 384 tokens (the limit) 23 and 23, 32 768
+  // tokens 38 and 26; E = 128, H = 7168, 8192 tokens 51 and 57, 16 384 tokens 97 and 62.
   const bool small = c.E <= 128 && c.H % 256 == 0;
-  if (small && static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20)) return router<uint16_t>(ctx, x, w, logits, T, stream);
-  // Many experts: K is summed in one sequence.  A K split is faster (1003 tokens, E = 256, H = 7168: 19 us against
-  // 55, 1 % of the layer) but another order moves one of 8192 x 256 logits across a near tie in every few calls.
-  // (The small routers always had their K split, and their sums are five times nearer the exact ones.)
-  if (!small && T <= 512) {
+  if (small) {
+    if (static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20)) return router<uint16_t>(ctx, x, w, logits, T, stream);
+    return router_gemm<kRouterSlices>(ctx, x, w, logits, T, stream);
+  }
+  // Many experts, or an odd K: K is summed in one sequence.  A K split is faster (1003 tokens, E = 256, H = 7168: 19 us
+  // against 71, 1 % of the layer) but another order moves one of 8192 x 256 logits across a near tie in every few
+  // calls.  (The small routers' sums are three times nearer the exact ones.)
+  if (T <= 512) {
     const int n_exp = ceil_div(c.E, 16);
     hipLaunchKernelGGL(router_sequence_kernel, dim3(ceil_div(T, 16) * n_exp), dim3(512), 0, stream, static_cast<const uint16_t*>(x),
                        static_cast<const uint16_t*>(w), logits, T, c.E, c.H, n_exp);
     return check_hip(ctx, hipGetLastError(), "router_sequence launch");
   }
-  GemmArgs a{};
-  a.A = x; a.lda = c.H;
-  a.B_one = w; a.ldb = c.H;
-  a.C = logits; a.ldc = c.E;
-  a.n_out = c.E; a.K = c.H;
-  a.M = T;
-  if (static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128) >= 512) {
-    // enough tiles to fill the chip twice over: wider tiles read x fewer times
-    a.n_col_tiles = ceil_div(c.E, 128);
-    return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
-  }
-  a.n_col_tiles = ceil_div(c.E, 64);
-  return launch_gemm_bf16<128, 64, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
+  return router_gemm<1>(ctx, x, w, logits, T, stream);
 }
 
 int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk_logical, float* topk_weight,

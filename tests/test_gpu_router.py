@@ -11,10 +11,11 @@ from paper_2602_21140_amd import ReviveLayer
 pytestmark = pytest.mark.gpu
 
 
-# (T, E, H): 16 x 16 tiles (one token to several tiles, ragged in both), 32 x 32 and 64 x 64 tiles from 256
-# workgroups on, seven and eight token tiles, fewer steps of K than wavefronts, the 128 x 128 tiles
+# (T, E, H): 16 x 16 tiles (one token to several tiles, ragged in both), 32 x 32 tiles from 256 workgroups on, seven
+# and eight token tiles, fewer steps of K than wavefronts, the GEMM's tiles of 64 and of 128 experts, K in slices there
 SHAPES = [(1, 16, 64), (15, 24, 192), (17, 16, 448), (112, 40, 512), (113, 40, 576), (129, 256, 704), (1000, 256, 320),
-          (1025, 250, 448), (4090, 256, 128), (4100, 130, 1024), (65500, 70, 64), (32700, 200, 128)]
+          (1025, 250, 448), (4090, 256, 128), (4100, 130, 1024), (65500, 70, 64), (32700, 200, 128), (16400, 128, 1024),
+          (65601, 128, 256)]
 F32_H = {64: 8, 192: 40, 448: 1000, 320: 72}
 
 
@@ -45,17 +46,19 @@ def test_router_logits(T, E, H, dtype):
 
 
 # a token's logits do not depend on the other tokens of the call: one, a few, as many as change the kernel
-@pytest.mark.parametrize("dtype,E,H", [("bf16", 256, 7168), ("bf16", 200, 448), ("bf16", 40, 576), ("bf16", 64, 2048), ("fp32", 64, 1000)])
+@pytest.mark.parametrize("dtype,E,H", [("bf16", 256, 7168), ("bf16", 200, 448), ("bf16", 40, 576), ("bf16", 64, 2048),
+                                       ("bf16", 128, 7168), ("bf16", 128, 256), ("fp32", 64, 1000)])
 def test_logits_do_not_depend_on_the_token_count(dtype, E, H):
-    cfg = SimpleNamespace(T=9000, H=H, E=E, k=1, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+    n = 66000 if H == 256 else 9000  # with 128 experts more than 2336 tokens at H = 7168, 65536 at 256, are the GEMM's
+    cfg = SimpleNamespace(T=n, H=H, E=E, k=1, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
                           score_fn="softmax", n_group=1, topk_group=1, dtype=dtype)
     L = ReviveLayer(cfg)
     L.set_placement(np.arange(E, dtype=np.int32))
     L.update_map(np.zeros(1, dtype=np.uint8))
     gen = torch.Generator(device="cuda").manual_seed(E)
-    x = torch.randn(9000, H, generator=gen, device="cuda").to(L.dtype)
+    x = torch.randn(n, H, generator=gen, device="cuda").to(L.dtype)
     w = (torch.randn(E, H, generator=gen, device="cuda") * H ** -0.5).to(L.dtype)
-    whole = L.route(x, w, 9000)[0]
-    for T in (1, 17, 500, 512, 513, 4100):
+    whole = L.route(x, w, n)[0]
+    for T in (1, 17, 500, 512, 513, 2336, 2337, 4100):
         assert torch.equal(L.route(x[:T].contiguous(), w, T)[0], whole[:T]), T
     L.close()
