@@ -197,10 +197,9 @@ __global__ __launch_bounds__(kThreads) void dispatch_small_kernel(const uint4* _
   const int N = T * k, t = blockIdx.x;
   const bool counting = t == T;
   if (counting && blockIdx.y > 0) return;
-  const int stride = gridDim.y * kThreads, c0 = blockIdx.y * kThreads + tid;
-  const uint4* src = x + static_cast<int64_t>(t) * row_words;
+  const int c0 = blockIdx.y * kThreads + tid;  // the one word of the row that this thread copies: the grid covers all
   uint4 word = make_uint4(0, 0, 0, 0);
-  if (!counting && c0 < row_words) word = src[c0];
+  if (!counting && c0 < row_words) word = x[static_cast<int64_t>(t) * row_words + c0];
   int q[kPerThread];
 #pragma unroll
   for (int c = 0; c < kPerThread; ++c) {
@@ -259,11 +258,10 @@ __global__ __launch_bounds__(kThreads) void dispatch_small_kernel(const uint4* _
     }
   }
   __syncthreads();
-  for (int c = c0; c < row_words; c += stride) {
-    const uint4 v = c == c0 ? word : src[c];
+  if (c0 < row_words) {
     for (int j = 0; j < k; ++j) {
       const int d = dst[j];
-      if (d >= 0) x_perm[static_cast<int64_t>(d) * row_words + c] = v;
+      if (d >= 0) x_perm[static_cast<int64_t>(d) * row_words + c0] = word;
     }
   }
 }
