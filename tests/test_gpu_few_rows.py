@@ -114,3 +114,45 @@ def test_fp32_row_tiles(H, I, shared):
     if shared:
         assert rel_err(f64(y_sh), reference(xd, w_sh)) < 1e-5
     L.close()
+
+
+# The kernels that share the work by rows per slot give the same bits: a whole batch and its microbatches may take
+# different ones.  The same slots with other slots beside them: weights streamed, row-tiles of up to 256, of up to 320
+# rows; the shared expert in the same calls and alone.
+@pytest.mark.parametrize("H,I", [(64, 64), (256, 192), (704, 320), (1088, 448), (7168, 2048)])
+def test_kernels_agree_bit_for_bit(H, I):
+    gen = torch.Generator(device="cuda").manual_seed(7)
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(*shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+
+    def expert():
+        return pack_expert(normal(H, I, std=H ** -0.5), normal(H, I, std=H ** -0.5), normal(I, H, std=I ** -0.5))
+
+    own = [expert() if c else (None, None) for c in EDGES]
+    other, sh = expert(), expert()
+    n = sum(EDGES)
+    x = normal(n, H)
+    ref = None
+    for streamed, beside in ((True, [0] * 90), (False, [200] * 8), (False, [320] * 5)):
+        counts = EDGES + beside
+        P, N = len(counts), sum(counts)
+        assert (N <= 16 * P) == streamed and (streamed or N > 96 * P) and (beside[0] < 320 or N >= 128 * P)  # the rules' limits
+        cfg = SimpleNamespace(T=N, H=H, E=P, k=1, I=I, I_shared=I, n_ranks=P, slots_per_rank=1, max_replicas=1,
+                              score_fn="softmax", n_group=1, topk_group=1, dtype="bf16")
+        L = ReviveLayer(cfg)
+        packed = own + [other if c else (None, None) for c in beside]
+        L.set_expert_weights([p[0] for p in packed], [p[1] for p in packed])
+        xs = torch.cat([x, normal(N - n, H)])
+        off = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+        L.set_kernel_timing(True)
+        y, y_sh = L.expert_ffn(xs, off, N, x=xs, w_sh_gate_up=sh[0], w_sh_down=sh[1])
+        assert (L.kernel_times()["ffn_tiles"][1] == 0) == streamed
+        got = [y[:n], y_sh[:n]]
+        if ref is None:
+            ref = got
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b), (streamed, beside[0])
+        for T in (1, 64, 65, 128, 129, 600, n):
+            assert torch.equal(L.shared_ffn(xs[:T].contiguous(), sh[0], sh[1], T), ref[1][:T]), T
+        L.close()

@@ -57,3 +57,24 @@ def test_microbatches_match_the_single_batch(n_micro):
     finally:
         pipe.close()
         g.close()
+
+
+# A whole batch and parts that take other kernels: the expert FFN on row-tiles (100 and 133 rows per slot) against
+# streamed weights, the router on whole tiles against few tokens (400), four tokens to a wavefront in the selection.
+@pytest.mark.parametrize("T,n_micro", [(3600, 2), (4800, 2), (4800, 12), (8400, 3)])
+def test_parts_that_take_other_kernels(T, n_micro):
+    g = GpuLayer(synth.scaled(CFG, T=T), replica_copies=False)
+    pipe = MicrobatchPipeline(g, n_micro)
+    try:
+        r = g.forward()
+        single, logits, phys = r["out"].clone(), r["logits"].clone(), r["topk_phys"].clone()
+        g.buf["out"].zero_()
+        torch.cuda.synchronize()
+        pipe.forward()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.cat([b["logits"] for _L, b, _s, _e in pipe.parts]), logits)
+        assert torch.equal(torch.cat([b["topk_phys"] for _L, b, _s, _e in pipe.parts]), phys)
+        assert torch.equal(g.buf["out"], single)
+    finally:
+        pipe.close()
+        g.close()
