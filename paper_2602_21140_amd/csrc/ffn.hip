@@ -178,6 +178,8 @@ constexpr int kStreamRowsPerSlot = 96, kStreamRowsPerSlotCached = 16;
 constexpr int64_t kCachedWeights = 192ll << 20;
 constexpr int kStreamDenseRows = 128;
 
+bool weights_cached(const revive_ctx* ctx) { return static_cast<int64_t>(ctx->P) * 6 * ctx->cfg.H * ctx->cfg.I <= kCachedWeights; }
+
 // One FFN call: routed experts, shared expert, or both.
 struct FfnArgs {
   const void* x_perm; const int32_t* slot_offsets; const void* const* w_gate_up; const void* const* w_down; void* h; void* y_perm;
@@ -228,13 +230,23 @@ int stream_ffn_as(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
 
 template <int K_GATE_UP, int K_DOWN>
 int stream_ffn(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
+  const revive_config& c = ctx->cfg;
+  const int64_t used = f.N < ctx->P ? f.N : ctx->P;  // slots that can hold a row
   // Above 8 rows per slot some slots hold more than 64: row-tiles of 128 then read those slots' weights once
-  // (28 uneven rows per slot: gate/up 2.95 -> 2.52 ms), at one workgroup less per CU.
-  if (f.N > 8 * ctx->P || f.T > 128) return stream_ffn_as<8, 4, 2, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+  // (28 uneven rows per slot: gate/up 2.95 -> 2.52 ms), at one workgroup less per CU.  Where that leaves a quarter
+  // of the CUs without work and the cache holds the weights, which may then be read again, the small tiles are better:
+  // 16 rows per slot, 32 slots, H = 2048, I = 448 (128 workgroups) 41 us with tiles of 128, 35 with tiles of 64 (38
+  // with the 256-row kernel); with a shared expert of 4 I and 128 tokens 77, 51 (62).  From 192 workgroups of the
+  // smaller launch on either may win (150 slots, H = 256, I = 384, 14 rows: 21 and 25).
+  if (f.N > 8 * ctx->P || f.T > 128) {
+    const int64_t dense = ceil_div(f.T, 128);
+    const int64_t gate_up = used * ceil_div(c.I, stream_tile_n<4, 4, EPI_SWIGLU>) + dense * ceil_div(c.I_shared, stream_tile_n<4, 4, EPI_SWIGLU>);
+    const int64_t down = (used + dense) * ceil_div(c.H, stream_tile_n<4, 4, EPI_BF16>);
+    if (!weights_cached(ctx) || (gate_up >= 192 && down >= 192)) return stream_ffn_as<8, 4, 2, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+  }
   // Fewer than two workgroups per CU: half as large ones spread the streams evenly over the CUs, and a CU
   // alone does not pull more than about 38 GB/s from HBM (one token, 288 -> 576 workgroups: 110 -> 95 us).
-  const int64_t slots = (f.N < ctx->P ? f.N : ctx->P) + (f.T > 0);
-  const int64_t blocks = slots * ceil_div(ctx->cfg.I, stream_tile_n<2, 4, EPI_SWIGLU>);
+  const int64_t blocks = (used + (f.T > 0)) * ceil_div(c.I, stream_tile_n<2, 4, EPI_SWIGLU>);
   if (blocks < 2 * 256) return stream_ffn_as<4, 2, 4, 2, K_GATE_UP, K_DOWN>(ctx, f, stream);
   return stream_ffn_as<4, 2, 4, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
 }
@@ -287,7 +299,7 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
   const FfnArgs f{x_perm, slot_offsets, w_gate_up, w_down, ctx->d_ws + ctx->ws.off_h, y_perm, static_cast<int>(N),
                   x, w_sh_gate_up, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, y_shared ? T : 0};
   if (c.dtype != REVIVE_DTYPE_BF16) return f32_ffn<GU, DN>(ctx, f, stream);
-  const bool cached = static_cast<int64_t>(ctx->P) * 6 * c.H * c.I <= kCachedWeights;
+  const bool cached = weights_cached(ctx);
   if (N <= static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return stream_ffn<GU, DN>(ctx, f, stream);
   MTile* tiles = reinterpret_cast<MTile*>(ctx->d_ws + ctx->ws.off_tiles);
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);

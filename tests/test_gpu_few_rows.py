@@ -21,6 +21,8 @@ CASES = {
     "tiles": (704, 320, EDGES + [3] * 10),  # above, at this size, the 256-row tiles
     # one row-tile up to 320 rows, from the shortest K to several turns of the ring
     "tall": (256, 192, TALL), "tall_short_k": (64, 64, TALL), "tall_long_k": (1088, 448, TALL),
+    # few workgroups and cached weights: row-tiles of 64 above 8 rows per slot and beside many rows of the shared expert
+    "small_tiles": (704, 320, [130, 65, 64, 1, 0, 16, 3] + [0] * 13),
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
