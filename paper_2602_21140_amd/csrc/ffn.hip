@@ -178,6 +178,13 @@ constexpr int kStreamRowsPerSlot = 96, kStreamRowsPerSlotCached = 16;
 constexpr int64_t kCachedWeights = 192ll << 20;
 constexpr int kStreamDenseRows = 128;
 
+// A streaming workgroup looks its row-tile up in all slots' offsets, 256 at a time, and the list of the 256-row kernel
+// does not: above 768 slots that costs more than it saves where a workgroup then has little to stream, cached weights
+// or 128 K-elements and fewer in one of the two products (1000 slots, H = 256, I = 128, 4 rows per slot 56 -> 74 us, 16
+// rows 59 -> 64; 1021 slots, H = 5056, I = 128, 1 row 564 -> 714).  At 640 to 768 slots such layers gain 5 % on
+// average, from 768 to 896 they lose 1 %, beyond 8 %; larger ones gain 10 to 18 % at every number of slots.
+constexpr int kStreamSlotsSmall = 768, kStreamSmallK = 128;
+
 bool weights_cached(const revive_ctx* ctx) { return static_cast<int64_t>(ctx->P) * 6 * ctx->cfg.H * ctx->cfg.I <= kCachedWeights; }
 
 // One FFN call: routed experts, shared expert, or both.
@@ -187,6 +194,13 @@ struct FfnArgs {
   const void* x; const void* w_sh_gate_up; const void* w_sh_down; void* h_shared; void* y_shared;
   int T;  // tokens of the shared expert; 0 = none
 };
+
+bool takes_stream(const revive_ctx* ctx, const FfnArgs& f) {
+  const revive_config& c = ctx->cfg;
+  const bool cached = weights_cached(ctx);
+  if (f.N > static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return false;
+  return ctx->P <= kStreamSlotsSmall || (!cached && c.H > kStreamSmallK && c.I > kStreamSmallK);
+}
 
 // The FFN of few rows per slot: two launches of the streaming kernel.
 template <int TMX, int W, int D, int NW, int EPI, int KID>
@@ -299,8 +313,7 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
   const FfnArgs f{x_perm, slot_offsets, w_gate_up, w_down, ctx->d_ws + ctx->ws.off_h, y_perm, static_cast<int>(N),
                   x, w_sh_gate_up, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, y_shared ? T : 0};
   if (c.dtype != REVIVE_DTYPE_BF16) return f32_ffn<GU, DN>(ctx, f, stream);
-  const bool cached = weights_cached(ctx);
-  if (N <= static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return stream_ffn<GU, DN>(ctx, f, stream);
+  if (takes_stream(ctx, f)) return stream_ffn<GU, DN>(ctx, f, stream);
   MTile* tiles = reinterpret_cast<MTile*>(ctx->d_ws + ctx->ws.off_tiles);
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);
   const bool tall = N >= static_cast<int64_t>(kTallRowsPerSlot) * ctx->P;

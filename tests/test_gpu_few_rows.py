@@ -26,6 +26,7 @@ CASES = {
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
+    "many_slots_streamed": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 48),
 }
 
 
@@ -158,3 +159,25 @@ def test_kernels_agree_bit_for_bit(H, I):
         for T in (1, 64, 65, 128, 129, 600, n):
             assert torch.equal(L.shared_ffn(xs[:T].contiguous(), sh[0], sh[1], T), ref[1][:T]), T
         L.close()
+
+
+# Which kernel a layer takes (the one with 256-row tiles needs a list of them), at both sides of each limit: rows per
+# slot, slots of little work.
+@pytest.mark.parametrize("P,H,I,N,streamed", [
+    (64, 256, 128, 1024, True), (64, 256, 128, 1025, False), (64, 1024, 576, 6144, True), (64, 1024, 576, 6145, False),
+    (768, 256, 128, 800, True), (769, 256, 128, 800, False), (800, 448, 128, 800, False), (800, 448, 192, 800, True)])
+def test_limits_of_the_streaming_kernel(P, H, I, N, streamed):
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    w = [(torch.randn(*s, generator=gen, device="cuda") * s[0] ** -0.5).to(torch.bfloat16) for s in ((H, I), (H, I), (I, H))]
+    gu, dn = pack_expert(*w)
+    cfg = SimpleNamespace(T=N, H=H, E=min(P, 512), k=1, I=I, I_shared=0, n_ranks=P, slots_per_rank=1, max_replicas=2,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype="bf16")
+    L = ReviveLayer(cfg)
+    L.set_expert_weights([gu] * P, [dn] * P)  # one expert everywhere
+    off = torch.linspace(0, N, P + 1, device="cuda").round().to(torch.int32)
+    x = torch.randn(N, H, generator=gen, device="cuda").to(torch.bfloat16)
+    L.set_kernel_timing(True)
+    y = L.expert_ffn(x, off, N)[0]
+    assert (L.kernel_times()["ffn_tiles"][1] == 0) == streamed
+    assert rel_err(f64(y), _reference(x.float().cpu(), w).double().numpy()) < TOL["bf16"]
+    L.close()
