@@ -169,7 +169,8 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
 // weights dominate and it wins whatever the load's shape: against the 256-row-tile kernel, H = 7168, I = 2048,
 // 288 slots, whole layer: 5 rows 4.31 -> 3.80 ms, 28 uneven rows 4.38 -> 3.99, 42 rows 4.71 -> 4.44, 89 rows
 // 5.17 -> 4.87; at 114 rows a slot often needs a second row-tile of 128 and it loses (5.70 -> 5.89).  The
-// shared expert's rows go along in the same launches however many they are (k = 1, 8192 tokens: 5.16 -> 4.85).
+// shared expert's rows go along in the same launches (k = 1, 8192 tokens: 5.16 -> 4.85) unless they are many and
+// weigh more than the slots (takes_stream).
 // Alone, the shared expert streams as long as its rows are one row-tile.
 // Weights that the 256 MB last-level cache holds come in faster than HBM streams; above 16 rows per slot the
 // streaming kernel's set-up then costs more than it saves (141 MB, 61 rows: 84 -> 88 us; 27 MB, 20 rows: 58 ->
@@ -199,7 +200,17 @@ bool takes_stream(const revive_ctx* ctx, const FfnArgs& f) {
   const revive_config& c = ctx->cfg;
   const bool cached = weights_cached(ctx);
   if (f.N > static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return false;
-  return ctx->P <= kStreamSlotsSmall || (!cached && c.H > kStreamSmallK && c.I > kStreamSmallK);
+  if (ctx->P > kStreamSlotsSmall && (cached || c.H <= kStreamSmallK || c.I <= kStreamSmallK)) return false;
+  // Every 128 rows of the shared expert read its weights once more.  That loses against the 256-row kernel once they
+  // are many rows and what is read that way outweighs the slots' weights, sooner where the cache does not hold the
+  // shared expert.  288 slots, H = 7168, I = 2048, one row per token, ms of the 256-row kernel and streamed:
+  // I_shared = 9 I, 2048 tokens 5.60 and 5.40, 4096 (as much as the slots) 6.65 and 7.17, 27 648 21.8 and 30.5;
+  // 2 I (cached), 27 648 tokens (1.5 times the slots) 8.70 and 8.71.  Share of 1500 random layers that lose: up to
+  // 1024 tokens none; above, uncached, from the slots' weights on 66 %; cached, up to 4096 tokens 9 %, above 3 % up to
+  // twice the slots' weights and 54 % from there on.
+  const bool shared_cached = 6ll * c.H * c.I_shared <= kCachedWeights;
+  if (f.T <= (shared_cached ? 4096 : 1024)) return true;
+  return static_cast<int64_t>(ceil_div(f.T, 128)) * c.I_shared < static_cast<int64_t>(shared_cached ? 2 : 1) * ctx->P * c.I;
 }
 
 // The FFN of few rows per slot: two launches of the streaming kernel.

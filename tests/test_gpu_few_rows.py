@@ -162,22 +162,29 @@ def test_kernels_agree_bit_for_bit(H, I):
 
 
 # Which kernel a layer takes (the one with 256-row tiles needs a list of them), at both sides of each limit: rows per
-# slot, slots of little work.
-@pytest.mark.parametrize("P,H,I,N,streamed", [
-    (64, 256, 128, 1024, True), (64, 256, 128, 1025, False), (64, 1024, 576, 6144, True), (64, 1024, 576, 6145, False),
-    (768, 256, 128, 800, True), (769, 256, 128, 800, False), (800, 448, 128, 800, False), (800, 448, 192, 800, True)])
-def test_limits_of_the_streaming_kernel(P, H, I, N, streamed):
+# slot, slots of little work, a shared expert that outweighs the slots (cached and not).
+@pytest.mark.parametrize("P,H,I,I_shared,N,streamed", [
+    (64, 256, 128, 0, 1024, True), (64, 256, 128, 0, 1025, False), (64, 1024, 576, 0, 6144, True), (64, 1024, 576, 0, 6145, False),
+    (768, 256, 128, 0, 800, True), (769, 256, 128, 0, 800, False), (800, 448, 128, 0, 800, False), (800, 448, 192, 0, 800, True),
+    (300, 256, 128, 4096, 4096, True), (300, 256, 128, 2304, 4097, True), (300, 256, 128, 2368, 4097, False),
+    (72, 2048, 256, 16448, 1024, True), (72, 2048, 256, 16448, 1025, False)])
+def test_limits_of_the_streaming_kernel(P, H, I, I_shared, N, streamed):
     gen = torch.Generator(device="cuda").manual_seed(8)
-    w = [(torch.randn(*s, generator=gen, device="cuda") * s[0] ** -0.5).to(torch.bfloat16) for s in ((H, I), (H, I), (I, H))]
+    w, w_sh = ([(torch.randn(*s, generator=gen, device="cuda") * s[0] ** -0.5).to(torch.bfloat16) for s in ((H, n), (H, n), (n, H))]
+               for n in (I, I_shared or 64))
     gu, dn = pack_expert(*w)
-    cfg = SimpleNamespace(T=N, H=H, E=min(P, 512), k=1, I=I, I_shared=0, n_ranks=P, slots_per_rank=1, max_replicas=2,
+    gu_sh, dn_sh = pack_expert(*w_sh) if I_shared else (None, None)
+    cfg = SimpleNamespace(T=N, H=H, E=min(P, 512), k=1, I=I, I_shared=I_shared, n_ranks=P, slots_per_rank=1, max_replicas=2,
                           score_fn="softmax", n_group=1, topk_group=1, dtype="bf16")
     L = ReviveLayer(cfg)
     L.set_expert_weights([gu] * P, [dn] * P)  # one expert everywhere
     off = torch.linspace(0, N, P + 1, device="cuda").round().to(torch.int32)
     x = torch.randn(N, H, generator=gen, device="cuda").to(torch.bfloat16)
     L.set_kernel_timing(True)
-    y = L.expert_ffn(x, off, N)[0]
+    y, y_sh = L.expert_ffn(x, off, N, x=x, w_sh_gate_up=gu_sh, w_sh_down=dn_sh)
     assert (L.kernel_times()["ffn_tiles"][1] == 0) == streamed
     assert rel_err(f64(y), _reference(x.float().cpu(), w).double().numpy()) < TOL["bf16"]
+    if I_shared:
+        assert torch.equal(y_sh, L.shared_ffn(x, gu_sh, dn_sh, N))
+        assert rel_err(f64(y_sh[:64]), _reference(x[:64].float().cpu(), w_sh).double().numpy()) < TOL["bf16"]
     L.close()
