@@ -65,11 +65,6 @@ __device__ __forceinline__ SlotTiles find_slot(const int32_t* __restrict__ slot_
   return t;
 }
 
-#ifndef RV_NW
-#define RV_NW 4
-#endif
-constexpr int kStreamWaves = RV_NW;
-
 // The tile of workgroup b in a grid of (an upper bound on) all slots' row-tiles times n_col column tiles:
 // rows [row_begin, row_end) of `group` and column tile n_idx; group = -1: nothing to do.
 //
