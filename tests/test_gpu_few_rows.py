@@ -23,6 +23,8 @@ CASES = {
     "tall": (256, 192, TALL), "tall_short_k": (64, 64, TALL), "tall_long_k": (1088, 448, TALL),
     # few workgroups and cached weights: row-tiles of 64 above 8 rows per slot and beside many rows of the shared expert
     "small_tiles": (704, 320, [130, 65, 64, 1, 0, 16, 3] + [0] * 13),
+    # the same with enough workgroups for tall tiles
+    "tall_many_short_k": (64, 64, TALL * 12), "tall_many": (192, 320, TALL * 12), "tall_wide": (2880, 1472, TALL),
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
@@ -137,7 +139,7 @@ def test_kernels_agree_bit_for_bit(H, I):
     n = sum(EDGES)
     x = normal(n, H)
     ref = None
-    for streamed, beside in ((True, [0] * 90), (False, [200] * 8), (False, [320] * 5)):
+    for streamed, beside in ((True, [0] * 90), (False, [200] * 8), (False, [320] * 120)):
         counts = EDGES + beside
         P, N = len(counts), sum(counts)
         assert (N <= 16 * P) == streamed and (streamed or N > 96 * P) and (beside[0] < 320 or N >= 128 * P)  # the rules' limits
