@@ -50,7 +50,8 @@ struct GemmF32Args {
 
 constexpr int kTileN_f32 = 64;
 
-template <bool SWIGLU, int D>
+// SLICES > 1: the K-steps are summed in SLICES parts that are added in their order (see gemm_bf16_kernel).
+template <bool SWIGLU, int D, int SLICES = 1>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   constexpr int BM = kTileM_f32, BN = kTileN_f32, W = SWIGLU ? 2 : 1;
@@ -124,6 +125,27 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
     for (int s = 0; s < W; ++s)
 #pragma unroll
       for (int i = 0; i < TM; ++i) acc[s][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 sum[W][TM];  // SLICES > 1: the finished slices
+    int slice = 1, slice_end = KT / SLICES;  // empty slices (KT < SLICES) are passed over
+    if (SLICES > 1) {
+#pragma unroll
+      for (int s = 0; s < W; ++s)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) sum[s][i] = acc[s][i];
+      while (slice_end == 0) slice_end = KT * ++slice / SLICES;
+    }
+    auto end_step = [&](int kt) {
+      if (SLICES > 1 && kt + 1 == slice_end) {
+#pragma unroll
+        for (int s = 0; s < W; ++s)
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            sum[s][i] += acc[s][i];
+            acc[s][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+        while (slice < SLICES && slice_end == kt + 1) slice_end = KT * ++slice / SLICES;
+      }
+    };
     auto mac = [&](int buf) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -152,6 +174,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
       for (int d = 0; d < D; ++d) {
         stage(kt + d + 1, (d + 1) % D, (d + 1) & 1);
         mac(d & 1);
+        end_step(kt + d);
         load(min(kt + D + d, KT - 1), d);
         publish();
         __builtin_amdgcn_sched_barrier(0);
@@ -160,8 +183,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       if (d + 1 < D) stage(kt + d + 1, d + 1, (d + 1) & 1);
-      if (kt + d < KT) mac(d & 1);
+      if (kt + d < KT) {
+        mac(d & 1);
+        end_step(kt + d);
+      }
       if (d + 1 < D) publish();
+    }
+    if (SLICES > 1) {
+#pragma unroll
+      for (int s = 0; s < W; ++s)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[s][i] = sum[s][i];
     }
     // a lane holds four consecutive output columns of activation row lane % 16
     const int col = n0 + wave * 16 + quad * 4;
@@ -184,11 +216,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
 }
 
 // Either problem may be absent (blocks == 0).
-template <bool SWIGLU>
+template <bool SWIGLU, int SLICES = 1>
 int launch_gemm_f32(revive_ctx* ctx, const GemmF32Args& args, hipStream_t stream) {
   const int grid = args.dense.blocks + args.grouped.blocks;
   if (grid <= 0) return REVIVE_OK;
-  hipLaunchKernelGGL((gemm_f32_kernel<SWIGLU, 2>), dim3(grid), dim3(256), 0, stream, args);
+  hipLaunchKernelGGL((gemm_f32_kernel<SWIGLU, 2, SLICES>), dim3(grid), dim3(256), 0, stream, args);
   return check_hip(ctx, hipGetLastError(), "gemm_f32 launch");
 }
 

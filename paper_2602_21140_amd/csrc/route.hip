@@ -4,7 +4,10 @@
 // Paper: Sec. 2.1 (gating scores, top-k), Sec. 3.4 "Missing experts" and Sec. 4.2 (experts with
 // no replica left are masked to -inf immediately before the top-k), Sec. 3.4 "Redundant experts"
 // (the logical-to-physical map decides which replica serves a token).
+#include <algorithm>
+
 #include "gemm_bf16.hpp"
+#include "gemm_f32.hpp"
 
 namespace revive {
 
@@ -466,12 +469,36 @@ int router_gemm(revive_ctx* ctx, const void* x, const void* w, float* logits, in
   return launch_gemm_bf16<128, 64, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM, SLICES>(ctx, a, ceil_div(T, 128), stream);
 }
 
+// Many tokens in fp32, K in the router kernel's slices.  The number of experts is a multiple of 4.
+int router_gemm_f32(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
+  const revive_config& c = ctx->cfg;
+  GemmF32Args a{};
+  GemmF32Problem& p = a.dense;
+  p.A = static_cast<const float*>(x); p.lda = c.H;
+  p.B_one = static_cast<const float*>(w); p.ldb = c.H;
+  p.C = logits; p.ldc = c.E;
+  p.n_out = c.E; p.K = c.H;
+  p.n_col_tiles = ceil_div(c.E, kTileN_f32);
+  p.blocks = ceil_div(T, kTileM_f32) * p.n_col_tiles;
+  p.M = T;
+  return launch_gemm_f32<false, kRouterSlices>(ctx, a, stream);
+}
+
 }  // namespace
 
 int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
   const revive_config& c = ctx->cfg;
   KernelTimer timer(ctx, REVIVE_K_ROUTER_GEMM, stream);
-  if (c.dtype != REVIVE_DTYPE_BF16) return router<float>(ctx, x, w, logits, T, stream);
+  if (c.dtype != REVIVE_DTYPE_BF16) {
+    // Beyond one or two rounds of the router kernel's workgroups the GEMM's larger tiles win, later for a longer K, which
+    // its one workgroup per tile walks alone.  us between events, router kernel and GEMM: 512 experts, H = 128, 8192
+    // tokens 58 and 20; 64 experts, H = 128 (the line: 512 workgroups), 4096 tokens (256) 8.2 and 10.0, 8192 (512) 11.1
+    // and 9.6; 192 experts, H = 256 (768), 2048 tokens (384) 11.1 and 13.2, 4096 (768) 15.8 and 14.1; 192 experts,
+    // H = 1536 (2048), 8192 tokens (1536) 69 and 73, 16 384 (3072) 137 and 109.
+    const int64_t workgroups = static_cast<int64_t>(ceil_div(T, 32)) * ceil_div(c.E, 32);
+    if (c.E % 4 == 0 && workgroups >= 256 + c.H + std::min(c.H, 256)) return router_gemm_f32(ctx, x, w, logits, T, stream);
+    return router<float>(ctx, x, w, logits, T, stream);
+  }
   // The order in which K is summed follows from E and H alone, so that a token's logits do not depend on how many
   // others are in the call.  Small routers: K in slices, in the router kernel or (many tokens, which it reads once
   // per 32 experts) in the GEMM.  us between events: E = 64, H = 2048, 16 384 tokens (the limit) 23 and 23, 32 768

@@ -47,7 +47,8 @@ def test_router_logits(T, E, H, dtype):
 
 # a token's logits do not depend on the other tokens of the call: one, a few, as many as change the kernel
 @pytest.mark.parametrize("dtype,E,H", [("bf16", 256, 7168), ("bf16", 200, 448), ("bf16", 40, 576), ("bf16", 64, 2048),
-                                       ("bf16", 128, 7168), ("bf16", 128, 256), ("fp32", 64, 1000)])
+                                       ("bf16", 128, 7168), ("bf16", 128, 256), ("fp32", 64, 1000),
+                                       ("fp32", 256, 392), ("fp32", 512, 40)])
 def test_logits_do_not_depend_on_the_token_count(dtype, E, H):
     n = 66000 if H == 256 else 9000  # with 128 experts more than 2336 tokens at H = 7168, 65536 at 256, are the GEMM's
     cfg = SimpleNamespace(T=n, H=H, E=E, k=1, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
