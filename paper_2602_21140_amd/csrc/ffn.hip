@@ -175,7 +175,8 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
 // 5.17 -> 4.87; at 114 rows a slot often needs a second row-tile of 128 and it loses (5.70 -> 5.89).  The
 // shared expert's rows go along in the same launches (k = 1, 8192 tokens: 5.16 -> 4.85) unless they are many and
 // weigh more than the slots (takes_stream).
-// Alone, the shared expert streams as long as its rows are one row-tile.
+// Alone, the shared expert streams up to 128 tokens (H = 7168, I_shared = 2048, 1 token 76 -> 29 us, 128 tokens 98 ->
+// 56; more have not been compared).
 // Weights that the 256 MB last-level cache holds come in faster than HBM streams; above 16 rows per slot the
 // streaming kernel's set-up then costs more than it saves (141 MB, 61 rows: 84 -> 88 us; 27 MB, 20 rows: 58 ->
 // 59; 226 MB, 40 rows: 108 -> 104; 113 MB, 14 rows: 71 -> 65).
