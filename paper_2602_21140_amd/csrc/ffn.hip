@@ -9,6 +9,8 @@
 // cover floor(N / tile) + P row-tiles, and workgroups beyond the last one exit at once.  Which rows a
 // workgroup owns comes from a list that a small kernel makes of slot_offsets (bf16, many rows per
 // slot), or the workgroup works it out from slot_offsets itself (row_tiles.hpp).
+#include <algorithm>
+
 #include "gemm_bf16.hpp"
 #include "gemm_f32.hpp"
 #include "gemm_stream.hpp"
@@ -184,12 +186,8 @@ constexpr int kStreamRowsPerSlot = 96, kStreamRowsPerSlotCached = 16;
 constexpr int64_t kCachedWeights = 192ll << 20;
 constexpr int kStreamDenseRows = 128;
 
-// A streaming workgroup looks its row-tile up in all slots' offsets, 256 at a time, and the list of the 256-row kernel
-// does not: above 768 slots that costs more than it saves where a workgroup then has little to stream, cached weights
-// or 128 K-elements and fewer in one of the two products (1000 slots, H = 256, I = 128, 4 rows per slot 56 -> 74 us, 16
-// rows 59 -> 64; 1021 slots, H = 5056, I = 128, 1 row 564 -> 714).  At 640 to 768 slots such layers gain 5 % on
-// average, from 768 to 896 they lose 1 %, beyond 8 %; larger ones gain 10 to 18 % at every number of slots.
-constexpr int kStreamSlotsSmall = 768, kStreamSmallK = 128;
+// A streaming workgroup looks its row-tile up in all slots' offsets, 256 at a time; the 256-row kernel has a list.
+constexpr int kStreamSlotsCached = 640, kStreamSlots = 768;
 
 bool weights_cached(const revive_ctx* ctx) { return static_cast<int64_t>(ctx->P) * 6 * ctx->cfg.H * ctx->cfg.I <= kCachedWeights; }
 
@@ -205,7 +203,15 @@ bool takes_stream(const revive_ctx* ctx, const FfnArgs& f) {
   const revive_config& c = ctx->cfg;
   const bool cached = weights_cached(ctx);
   if (f.N > static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return false;
-  if (ctx->P > kStreamSlotsSmall && (cached || c.H <= kStreamSmallK || c.I <= kStreamSmallK)) return false;
+  // With many slots that search costs more than it saves where a workgroup has little to stream.  us of the 256-row
+  // kernel and streamed: cached, 1000 slots, H = 256, I = 128, 4 rows per slot 54 and 73, 16 rows 57 and 64.  Geometric
+  // mean of the gain over random layers.  Cached: up to 64 rows in all, 513 to 640 slots 1.00, to 768 0.91, beyond
+  // 0.78; more than 256 rows, to 768 slots 1.05, beyond 0.90.  Larger weights beyond 768 slots: up to 64 rows, products
+  // of 640 columns and less 0.88, more 1.18; more rows, 128 K-elements and less in one of the products 0.84 to 0.95
+  // (but I = 64 1.03: half of the other kernel's columns are idle then), more 1.05 to 1.15.
+  if (cached && (ctx->P > kStreamSlots || (ctx->P > kStreamSlotsCached && f.N <= 256))) return false;
+  if (ctx->P > kStreamSlots && f.N <= 256 && std::max(c.H, c.I) <= 640) return false;
+  if (ctx->P > kStreamSlots && f.N > 64 && std::min(c.H, c.I) <= 128 && c.I > 64) return false;
   // Every 128 rows of the shared expert read its weights once more.  That loses against the 256-row kernel once they
   // are many rows and what is read that way outweighs the slots' weights, sooner where the cache does not hold the
   // shared expert.  288 slots, H = 7168, I = 2048, one row per token, ms of the 256-row kernel and streamed:

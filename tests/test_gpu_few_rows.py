@@ -28,7 +28,7 @@ CASES = {
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
-    "many_slots_streamed": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 48),
+    "many_slots_streamed": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 40),
 }
 
 
@@ -167,7 +167,9 @@ def test_kernels_agree_bit_for_bit(H, I):
 # slot, slots of little work, a shared expert that outweighs the slots (cached and not).
 @pytest.mark.parametrize("P,H,I,I_shared,N,streamed", [
     (64, 256, 128, 0, 1024, True), (64, 256, 128, 0, 1025, False), (64, 1024, 576, 0, 6144, True), (64, 1024, 576, 0, 6145, False),
-    (768, 256, 128, 0, 800, True), (769, 256, 128, 0, 800, False), (800, 448, 128, 0, 800, False), (800, 448, 192, 0, 800, True),
+    (640, 256, 128, 0, 256, True), (641, 256, 128, 0, 256, False), (768, 256, 128, 0, 257, True), (769, 256, 128, 0, 800, False),
+    (768, 448, 128, 0, 800, True), (800, 448, 128, 0, 800, False), (800, 704, 64, 0, 800, True),
+    (800, 448, 192, 0, 800, True), (800, 448, 192, 0, 256, False), (800, 704, 128, 0, 64, True), (800, 704, 128, 0, 65, False),
     (300, 256, 128, 4096, 4096, True), (300, 256, 128, 2304, 4097, True), (300, 256, 128, 2368, 4097, False),
     (72, 2048, 256, 16448, 1024, True), (72, 2048, 256, 16448, 1025, False)])
 def test_limits_of_the_streaming_kernel(P, H, I, I_shared, N, streamed):
