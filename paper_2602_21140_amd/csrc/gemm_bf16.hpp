@@ -1,4 +1,4 @@
-// Grouped bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulate.
+// Grouped bf16 GEMM on the gfx950 matrix cores, fp32 accumulate.
 //
 //   C[rows of tile, n] = sum_k A[row, k] * B_group[n, k]        ("NT": both operands K-contiguous)
 //
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmA
   if (g.tiles) {
     const MTile t = g.tiles[m_idx];
     group = t.group;
-    tile_span(t.group_begin, t.group_end, t.pad >> 16, t.pad & 0xFFFF, BM, row_begin, row_end);
+    tile_span(t.group_begin, t.group_end, t.pad >> 16, t.pad & 0xFFFF, row_begin, row_end);
   } else {
     row_begin = m_idx * BM;
     row_end = min(g.M, row_begin + BM);
@@ -339,14 +339,27 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmA
 }
 
 // ---------------------------------------------------------------------------------------------
-// Variant with asynchronous global->LDS copies (global_load_lds_dwordx4) and a four-stage ring.
+// Variant with asynchronous global->LDS copies (global_load_lds_dwordx4), a four-stage ring and
+// 16x16x32 MFMAs.
 //
 // Same contract and output layout as gemm_bf16_kernel.  K is walked in steps of 32; a stage holds
 // a BM x 32 tile of A and a BN x 32 tile of B (64-byte rows).  The copy of K-step t+3 is issued
 // while step t is being multiplied, so three steps (about 1.3 us of MFMA work at full rate) are
 // in flight to cover HBM latency, and no register is spent on staging.  Per K-step there is one
-// workgroup barrier, placed before the last 16-wide half-step's MFMAs so that the first fragment
-// reads of the next stage overlap them.
+// workgroup barrier, placed before the second half of the row sub-tiles' MFMAs so that the first
+// fragment reads of the next stage overlap them.
+//
+// What bounds it on large problems is power: the clock falls to 1.4 to 1.6 GHz under it.  Hence the
+// MFMA that costs least for a product, 16x16x32 (it reads and writes half the accumulators of
+// 32x32x16 per multiplication; the sums are the same bits), and an order in which each MFMA shares
+// an operand with the one before.  And sub-tiles of 16 rows pad a ragged row-tile less.  TFLOP/s of
+// 32x32x16, of 16x16x32, of that to and fro, and with sub-tiles of 16 rows and slots cut evenly:
+// dense 8192 x 7168 x 4096 with SwiGLU 1289, 1400, 1429 (1318 and 1476 in another run); gate/up of
+// 414 slots of 640 to 740 rows, K = 7168, 1111, 1124, 1162, 1196, down 1068, 1095, 1130, 1154; of 261
+// slots of 230 to 290 rows 986 and 1025, 964 and 1000; of 63 slots of 350 to 430 rows, K = 2048 and
+// 1408, 865 and 887, 800 and 838.  4 x 2 wavefronts (64 x 128 each) are 1 % faster on the dense shape
+// and 2 to 4 % slower on slots; 2 x 2 wavefronts 10 % slower; weights kept over the row sub-tiles
+// beat activations kept over the column tiles by 1 %.
 //
 // LDS layout of a stage: row r at r*64 bytes, its four 16-byte chunks stored at chunk ^ ((r>>2)&3):
 // a copy instruction writes lane l's 16 bytes to (its 1 KiB window) + 16*l, i.e. 16 rows per
@@ -355,22 +368,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmA
 // s_waitcnt immediate (gfx9 encoding) for "vmcnt(vm) lgkmcnt(0)", export counter ignored.
 __host__ __device__ constexpr int waitcnt_vm_lgkm0(int vm) { return (vm & 0xF) | ((vm >> 4) << 14) | (0x7 << 4) | (0 << 8); }
 
-// Row sub-tiles of 32 rows whose outputs all wavefronts can hold in LDS at a time.
+// Row sub-tiles of 16 rows whose outputs all wavefronts can hold in LDS at a time.
 constexpr int epilogue_pass(int tm, int waves, int row_bytes) {
   int pass = tm;
-  while (waves * pass * 32 * row_bytes > 160 * 1024) pass = (pass + 1) / 2;
+  while (waves * pass * 16 * row_bytes > 160 * 1024) pass = (pass + 1) / 2;
   return pass;
 }
 
 __device__ __forceinline__ int swz32(int row) { return (row >> 2) & 3; }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID, int STAGES = 4>
+constexpr int kStages = 4;
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(GemmArgs2 a2) {
   constexpr int NT = 64 * WAVES_M * WAVES_N, NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int BN_OUT = EPI == EPI_SWIGLU ? BN / 2 : BN;
-  constexpr int D = STAGES - 1;  // copies run D K-steps ahead of the MFMAs
+  constexpr int D = kStages - 1;  // copies run D K-steps ahead of the MFMAs
   constexpr int STAGE = (BM + BN) * 64;       // bytes
   // Row-tiles are BM0 rows high; BM may be higher by a quarter, for a slot that overflows one row-tile by less
   // than that (see tiles_of).  Copy instructions per wavefront and stage: CP_B + CP_A, and in such a tall tile
@@ -378,14 +393,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   constexpr int BM0 = BM > kTileM_bf16 ? kTileM_bf16 : BM;
   constexpr int CP_B = BN / 16 / NW, CP_A = BM0 / 16 / NW, CP = CP_A + CP_B, CPT = CP + (BM > BM0);
   static_assert(BM0 % (16 * NW) == 0 && BN % (16 * NW) == 0 && (BM == BM0 || BM - BM0 == NW / 2 * 16), "copy split");
-  static_assert(BM0 / WAVES_M / 32 <= 4, "row sub-tile dispatch below covers up to four");
-  static_assert(STAGES >= 3 && STAGES <= 5, "prologue and tail are written for 2 to 4 steps of copy-ahead");
+  constexpr int TM0 = BM0 / WAVES_M / 16;
+  static_assert(TM0 == 8 && (BM == BM0 || TM == TM0 + 2), "row sub-tile dispatch below");
   static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
   typedef __attribute__((address_space(1))) const void* gptr;
   typedef __attribute__((address_space(3))) void* lptr;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  auto stage_of = [](int kt) { return (STAGES & (STAGES - 1)) == 0 ? (kt & (STAGES - 1)) : kt % STAGES; };
+  auto stage_of = [](int kt) { return kt & (kStages - 1); };
 
   // Tile -> workgroup map.  Workgroup i runs on XCD i % 8; each XCD takes a contiguous eighth of
   // every problem's tiles (neighbouring tiles share activations / weights in that XCD's L2), and
@@ -455,7 +470,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
         j = r - n_idx * in_group;
       }
     }
-    tile_span(t.group_begin, t.group_end, in_group, j, BM0, row_begin, row_end);
+    tile_span(t.group_begin, t.group_end, in_group, j, row_begin, row_end);
     Bbase = static_cast<const unsigned char*>(g.b_sel >= 0 ? t.w[g.b_sel] : (g.B_tab ? g.B_tab[t.group] : g.B_one));
   } else {
     row_begin = m_idx * BM0;
@@ -558,152 +573,167 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   using Cp = std::integral_constant<int, CP>;
   using CpTall = std::integral_constant<int, CPT>;
 
-  // ---- per-lane fragment addresses.  32-row sub-tiles are dealt round-robin to the wavefront
+  // ---- per-lane fragment addresses.  16-row sub-tiles are dealt round-robin to the wavefront
   // rows (sub-tile tm*WAVES_M + wm), so a ragged row-tile keeps every wavefront equally busy.
-  // Every fragment row of a lane is (a multiple of 32) + lane % 32, so the swizzle term depends on
-  // the lane only: the lane keeps one loop-invariant byte offset per operand and half-step, and
-  // the individual fragments are reached with immediate offsets from it.
-  const int lrow = lane & 31;
-  int a_off[2], b_off[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int sw = ((ks * 2 + (lane >> 5)) ^ swz32(lrow)) << 4;
-    a_off[ks] = (wm * 32 + lrow) * 64 + sw;
-    b_off[ks] = (BM + (EPI == EPI_SWIGLU ? wn * (WN / 2) : wn * WN) + lrow) * 64 + sw;
-  }
+  // Every fragment row of a lane is (a multiple of 16) + lane % 16, so the swizzle term depends on
+  // the lane only: the lane keeps one loop-invariant byte offset per operand, and the individual
+  // fragments are reached with immediate offsets from it.
+  const int lrow = lane & 15;
+  const int sw = ((lane >> 4) ^ swz32(lrow)) << 4;
+  const int a_off = (wm * 16 + lrow) * 64 + sw;
+  const int b_off = (BM + (EPI == EPI_SWIGLU ? wn * (WN / 2) : wn * WN) + lrow) * 64 + sw;
   // The same bases two stages further on: with the ring position known at compile time every
   // fragment of every stage is an immediate offset below 64 KiB away from one of the two.
-  int a_off2[2], b_off2[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    a_off2[ks] = a_off[ks] + 2 * STAGE;
-    b_off2[ks] = b_off[ks] + 2 * STAGE;
-  }
-  constexpr int A_STEP = WAVES_M * 32 * 64;  // bytes between a wavefront's successive row sub-tiles
+  const int a_off2 = a_off + 2 * STAGE, b_off2 = b_off + 2 * STAGE;
+  constexpr int A_STEP = WAVES_M * 16 * 64;  // bytes between a wavefront's successive row sub-tiles
   auto b_imm = [](int tn) {                   // byte offset of column tile tn from the lane's base
-    if (EPI == EPI_SWIGLU) return ((tn >= TN / 2 ? BN / 2 : 0) + (tn % (TN / 2 > 0 ? TN / 2 : 1)) * 32) * 64;
-    return tn * 32 * 64;
+    if (EPI == EPI_SWIGLU) return ((tn >= TN / 2 ? BN / 2 : 0) + (tn % (TN / 2)) * 16) * 64;
+    return tn * 16 * 64;
   };
-  f32x16 acc[TM][TN];
+  auto frag = [](const unsigned char* p) { return *reinterpret_cast<const bf16x8*>(p); };
+  f32x4 acc[TM][TN];
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0.f;
+    for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // A ragged row-tile leaves some 32-row sub-tiles of a wavefront without any valid row; the
+  // A ragged row-tile leaves some 16-row sub-tiles of a wavefront without any valid row; the
   // main loop is instantiated for each count of valid sub-tiles so that those MFMAs (and their
   // fragment reads) are not issued at all.  The wavefront still takes part in copies and barriers.
   const int KT = g.K >> 5;
-  const int n_sub = (row_end - row_begin + 31) >> 5;  // sub-tiles holding at least one valid row
+  const int n_sub = (row_end - row_begin + 15) >> 4;  // sub-tiles holding at least one valid row
   const int tm_valid = min(TM, max(0, (n_sub - wm + WAVES_M - 1) / WAVES_M));
 
   // early_tag: copies per stage of the first half of the wavefronts.
   auto run = [&](auto tmv_tag, auto early_tag) {
     constexpr int TMV = decltype(tmv_tag)::value, CPE = decltype(early_tag)::value;
-    auto load_frags = [&](const unsigned char* base, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
+    // A K-step has two phases: the first half of the row sub-tiles (H0 of them) times all column tiles, then the
+    // rest (H1).  The fragments that a phase does not have yet are read while the phase before it multiplies: phase
+    // 0 reads the second half's activations; phase 1, which comes after the barrier, reads the next stage's first
+    // half and its weights, each weight fragment in the place of the one whose last MFMA has just been issued.
+    constexpr int H0 = (TMV + 1) / 2, H1 = TMV / 2;
+    bf16x8 af0[TM], af1[TM], bf[TN];
+    // MFMA idx of a phase of HM row sub-tiles: to and fro over the sub-tiles, so that each MFMA shares one operand
+    // with the one before it.
+    auto mfma = [&](int idx, int HM, const bf16x8* a, int base) {
+      const int tn = idx / HM, tm = (tn & 1) ? HM - 1 - idx % HM : idx % HM;
+      acc[base + tm][tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[tn], a[tm], acc[base + tm][tn], 0, 0, 0);
+    };
+    // The reads are dealt between the MFMAs and their order is pinned with scheduling groups (0x008: MFMA, 0x100:
+    // LDS read): they then issue in the shadow of the matrix pipe instead of in a block ahead of it.
+    auto phase0 = [&](const unsigned char* pa) {
       if (TMV == 0) return;
-      const unsigned char* pa = base + a_off[ks];
-      const unsigned char* pb = base + b_off[ks];
 #pragma unroll
-      for (int tm = 0; tm < TMV; ++tm) af[tm] = *reinterpret_cast<const bf16x8*>(pa + tm * A_STEP);
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) bfr[tn] = *reinterpret_cast<const bf16x8*>(pb + b_imm(tn));
-    };
-    auto mfma_step = [&](const bf16x8 (&af)[TM], const bf16x8 (&bfr)[TN]) {
-#pragma unroll
-      for (int tm = 0; tm < TMV; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-          acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[tn], af[tm], acc[tm][tn], 0, 0, 0);
-    };
-    // One K-step.  COPY: issue the copy of step kt+3.  VM: copies that may stay pending at the
-    // barrier (those of the steps after kt+1).  LAST: no next stage to publish.
-    bf16x8 af0[TM], bf0[TN], af1[TM], bf1[TN];
-    auto step = [&](int kt, auto copy_tag, auto vm_tag, auto last_tag) {
-      constexpr bool COPY = decltype(copy_tag)::value, LAST = decltype(last_tag)::value;
-      constexpr int VM = decltype(vm_tag)::value;
-      const unsigned char* cur = smem + stage_of(kt) * STAGE;
-      // stage (kt+3)%4 held step kt-1, which every wavefront finished reading before the last barrier
-      if (COPY) issue_copy(kt + D, early_tag);
-      load_frags(cur, 1, af1, bf1);
-      __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the MFMAs they overlap with
-      mfma_step(af0, bf0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (!LAST) {
-        // this wavefront's copies of step kt+1 have landed once only VM newer copies are pending;
-        // all its fragment reads of the current stage have returned (lgkmcnt 0)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(VM));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        load_frags(smem + stage_of(kt + 1) * STAGE, 0, af0, bf0);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int idx = 0; idx < H0 * TN; ++idx) {
+        mfma(idx, H0, af0, 0);
+        if (idx < H1) af1[idx] = frag(pa + (H0 + idx) * A_STEP);
       }
-      mfma_step(af1, bf1);
-      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < H1; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, H0 * TN - H1, 0);
     };
-    // The MFMAs of one half-step with the fragment reads of the next half-step dealt in between
-    // them (one read after each of the first MFMAs; the order is pinned with scheduling groups):
-    // the reads then issue in the shadow of the matrix pipe instead of in a block ahead of it.
-    auto mfma_reads_at = [&](const bf16x8 (&af)[TM], const bf16x8 (&bfr)[TN], auto ph_tag, int ks, bf16x8 (&naf)[TM],
-                             bf16x8 (&nbf)[TN]) {
-      constexpr int PH = decltype(ph_tag)::value;
+    auto phase1 = [&](const unsigned char* pa, const unsigned char* pb, auto last_tag) {
+      constexpr bool LAST = decltype(last_tag)::value;  // no next stage
       if (TMV == 0) return;
-      const unsigned char* pa = smem + (PH >= 2 ? a_off2[ks] : a_off[ks]) + (PH & 1) * STAGE;
-      const unsigned char* pb = smem + (PH >= 2 ? b_off2[ks] : b_off[ks]) + (PH & 1) * STAGE;
-      constexpr int NR = TMV + TN, NM = TMV * TN;  // reads, MFMAs
 #pragma unroll
-      for (int tm = 0; tm < TMV; ++tm)
+      for (int tn = 0; tn < TN; ++tn) {
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) {
-          acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[tn], af[tm], acc[tm][tn], 0, 0, 0);
-          const int idx = tm * TN + tn;
-          if (idx < TMV) naf[idx] = *reinterpret_cast<const bf16x8*>(pa + idx * A_STEP);
-          else if (idx < NR) nbf[idx - TMV] = *reinterpret_cast<const bf16x8*>(pb + b_imm(idx - TMV));
+        for (int tm = 0; tm < H1; ++tm) {
+          mfma(tn * H1 + tm, H1, af1, H0);
+          if (!LAST && tn == 0) af0[tm] = frag(pa + tm * A_STEP);
         }
-#pragma unroll
-      for (int idx = NM; idx < NR; ++idx) {  // fewer MFMAs than reads: the remaining reads follow
-        if (idx < TMV) naf[idx] = *reinterpret_cast<const bf16x8*>(pa + idx * A_STEP);
-        else nbf[idx - TMV] = *reinterpret_cast<const bf16x8*>(pb + b_imm(idx - TMV));
+        if (!LAST && tn == 0 && H0 > H1) af0[H0 - 1] = frag(pa + (H0 - 1) * A_STEP);
+        if (!LAST) bf[tn] = frag(pb + b_imm(tn));
       }
-      constexpr int PAIRS = NR < NM ? NR : NM;
+      if (!LAST) {
 #pragma unroll
-      for (int i = 0; i < PAIRS; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
+        for (int i = 0; i < H1; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        if (H0 > H1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+#pragma unroll
+        for (int i = 1; i < TN; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          if (H1 > 0) __builtin_amdgcn_sched_group_barrier(0x008, H1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-      if (NM > PAIRS) __builtin_amdgcn_sched_group_barrier(0x008, NM - PAIRS, 0);
-      if (NR > PAIRS) __builtin_amdgcn_sched_group_barrier(0x100, NR - PAIRS, 0);
     };
-    // Steady-state forms of the two steps (the late group's is described below) for a four-stage
-    // ring, with the ring position PH = kt % 4 known at compile time: stage addresses fold into
-    // immediates and the K loop, unrolled by four, carries no vector ALU instruction at all.
-    auto step_at = [&](int kt, auto ph_tag) {
-      constexpr int PH = decltype(ph_tag)::value;
-      issue_copy_at(kt + D, std::integral_constant<int, (PH + D) & 3>{}, early_tag);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_reads_at(af0, bf0, ph_tag, 1, af1, bf1);
-      __builtin_amdgcn_sched_barrier(0);
+    auto load_first = [&]() {
+      if (TMV == 0) return;
+#pragma unroll
+      for (int tm = 0; tm < H0; ++tm) af0[tm] = frag(smem + a_off + tm * A_STEP);
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) bf[tn] = frag(smem + b_off + b_imm(tn));
+    };
+    // This wavefront's copies of the next step have landed once only vm newer ones are pending; all its fragment
+    // reads of the current stage have returned (lgkmcnt 0).
+    auto wait_barrier = [&](auto vm_tag) {
       asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((D - 1) * CPE));
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(decltype(vm_tag)::value));
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      mfma_reads_at(af1, bf1, std::integral_constant<int, (PH + 1) & 3>{}, 0, af0, bf0);
+    };
+    // One K-step.  COPY: issue the copy of step kt + D, into the stage that held step kt - 1 (every wavefront
+    // finished reading it before the last barrier).  vm: copies that may stay pending at the barrier (those of the
+    // steps after kt + 1).  LAST: no next stage to publish.
+    auto step = [&](int kt, auto copy_tag, auto vm_tag, auto last_tag) {
+      if (decltype(copy_tag)::value) issue_copy(kt + D, early_tag);
+      __builtin_amdgcn_sched_barrier(0);
+      phase0(smem + stage_of(kt) * STAGE + a_off);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!decltype(last_tag)::value) wait_barrier(vm_tag);
+      const unsigned char* next = smem + stage_of(kt + 1) * STAGE;
+      phase1(next + a_off, next + b_off, last_tag);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // Skewed schedule.  Both wavefronts of a SIMD (w and w + NW/2) would otherwise leave the
+    // barrier in lockstep and do their non-MFMA work (copy issue, address arithmetic) at the same
+    // time, leaving the matrix pipe idle.  The late group issues its copy right after the barrier
+    // (one step further ahead, into this step's own stage: all its reads ended before the barrier)
+    // instead of after the second phase, so one group's overhead always runs under the other
+    // group's MFMAs.
+    auto step_late = [&](int kt, auto copy_tag, auto vm_tag, auto last_tag) {
+      phase0(smem + stage_of(kt) * STAGE + a_off);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!decltype(last_tag)::value) {
+        wait_barrier(vm_tag);
+        if (decltype(copy_tag)::value) issue_copy(kt + D + 1, Cp{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const unsigned char* next = smem + stage_of(kt + 1) * STAGE;
+      phase1(next + a_off, next + b_off, last_tag);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // Steady-state forms of the two with the ring position PH = kt % 4 known at compile time: stage
+    // addresses fold into immediates and the K loop, unrolled by four, carries no vector ALU
+    // instruction at all.
+    auto a_at = [&](auto ph_tag) { constexpr int PH = decltype(ph_tag)::value; return smem + (PH >= 2 ? a_off2 : a_off) + (PH & 1) * STAGE; };
+    auto b_at = [&](auto ph_tag) { constexpr int PH = decltype(ph_tag)::value; return smem + (PH >= 2 ? b_off2 : b_off) + (PH & 1) * STAGE; };
+    auto step_at = [&](int kt, auto ph_tag) {
+      constexpr int PH = decltype(ph_tag)::value;
+      using Next = std::integral_constant<int, (PH + 1) & 3>;
+      issue_copy_at(kt + D, std::integral_constant<int, (PH + D) & 3>{}, early_tag);
+      __builtin_amdgcn_sched_barrier(0);
+      phase0(a_at(ph_tag));
+      __builtin_amdgcn_sched_barrier(0);
+      wait_barrier(std::integral_constant<int, (D - 1) * CPE>{});
+      phase1(a_at(Next{}), b_at(Next{}), std::false_type{});
       __builtin_amdgcn_sched_barrier(0);
     };
     auto step_late_at = [&](int kt, auto ph_tag) {
       constexpr int PH = decltype(ph_tag)::value;
-      mfma_reads_at(af0, bf0, ph_tag, 1, af1, bf1);
+      using Next = std::integral_constant<int, (PH + 1) & 3>;
+      phase0(a_at(ph_tag));
       __builtin_amdgcn_sched_barrier(0);
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((D - 1) * CP));
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      issue_copy_at(kt + D + 1, ph_tag, Cp{});  // (PH + 4) % 4: into this step's own stage
+      wait_barrier(std::integral_constant<int, (D - 1) * CP>{});
+      issue_copy_at(kt + D + 1, ph_tag, Cp{});  // (PH + 4) % 4
       __builtin_amdgcn_sched_barrier(0);
-      mfma_reads_at(af1, bf1, std::integral_constant<int, (PH + 1) & 3>{}, 0, af0, bf0);
+      phase1(a_at(Next{}), b_at(Next{}), std::false_type{});
       __builtin_amdgcn_sched_barrier(0);
     };
     using T = std::true_type;
@@ -712,58 +742,25 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
     using P1 = std::integral_constant<int, 1>;
     using P2 = std::integral_constant<int, 2>;
     using P3 = std::integral_constant<int, 3>;
-    // Skewed schedule.  Both wavefronts of a SIMD (w and w + NW/2) would otherwise leave the
-    // barrier in lockstep and do their non-MFMA work (copy issue, address arithmetic) at the same
-    // time, leaving the matrix pipe idle.  The late group issues its copy right after the barrier
-    // (one step further ahead) instead of after the second half-step's MFMAs, so one group's
-    // overhead always runs under the other group's MFMAs.
-    auto step_late = [&](int kt, auto copy_tag, auto vm_tag, auto last_tag) {
-      constexpr bool COPY = decltype(copy_tag)::value, LAST = decltype(last_tag)::value;
-      constexpr int VM = decltype(vm_tag)::value;
-      const unsigned char* cur = smem + stage_of(kt) * STAGE;
-      load_frags(cur, 1, af1, bf1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_step(af0, bf0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (!LAST) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(VM));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (COPY) issue_copy(kt + D + 1, Cp{});  // into this step's own stage: all its reads ended before the barrier
-        load_frags(smem + stage_of(kt + 1) * STAGE, 0, af0, bf0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      mfma_step(af1, bf1);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    // Tail: with j copies-ahead steps left, (j - 1) * CP copies may stay pending at the barrier.
-    auto tail = [&](auto& fn, int& kt) {
-      if (D >= 4 && kt + 4 < KT) { fn(kt, F{}, std::integral_constant<int, 3 * CP>{}, F{}); ++kt; }
-      if (D >= 3 && kt + 3 < KT) { fn(kt, F{}, std::integral_constant<int, 2 * CP>{}, F{}); ++kt; }
-      if (D >= 2 && kt + 2 < KT) { fn(kt, F{}, std::integral_constant<int, CP>{}, F{}); ++kt; }
-      if (kt + 1 < KT) { fn(kt, F{}, std::integral_constant<int, 0>{}, F{}); ++kt; }
-      fn(kt, F{}, std::integral_constant<int, 0>{}, T{});
-    };
+    int kt = 0;  // a multiple of four in the unrolled loops: ring position = unrolled position
     if (wave < NW / 2) {
-      load_frags(smem, 0, af0, bf0);
-      int kt = 0;
-      if constexpr (STAGES == 4)  // kt stays a multiple of four here: ring position = unrolled position
-        for (; kt + D + 3 < KT; kt += 4) { step_at(kt, P0{}); step_at(kt + 1, P1{}); step_at(kt + 2, P2{}); step_at(kt + 3, P3{}); }
+      load_first();
+      for (; kt + D + 3 < KT; kt += 4) { step_at(kt, P0{}); step_at(kt + 1, P1{}); step_at(kt + 2, P2{}); step_at(kt + 3, P3{}); }
       for (; kt + D < KT; ++kt) step(kt, T{}, std::integral_constant<int, (D - 1) * CPE>{}, F{});
       // here kt + D >= KT: the copies of every remaining step are already issued
-      if (D >= 4 && kt + 3 < KT) { step(kt, F{}, std::integral_constant<int, 2 * CPE>{}, F{}); ++kt; }
-      if (D >= 3 && kt + 2 < KT) { step(kt, F{}, std::integral_constant<int, CPE>{}, F{}); ++kt; }
+      if (kt + 2 < KT) { step(kt, F{}, std::integral_constant<int, CPE>{}, F{}); ++kt; }
       if (kt + 1 < KT) { step(kt, F{}, std::integral_constant<int, 0>{}, F{}); ++kt; }
       step(kt, F{}, std::integral_constant<int, 0>{}, T{});
     } else {
       if (KT > D) issue_copy(D, Cp{});
-      load_frags(smem, 0, af0, bf0);
-      int kt = 0;
-      if constexpr (STAGES == 4)
-        for (; kt + D + 4 < KT; kt += 4) { step_late_at(kt, P0{}); step_late_at(kt + 1, P1{}); step_late_at(kt + 2, P2{}); step_late_at(kt + 3, P3{}); }
+      load_first();
+      for (; kt + D + 4 < KT; kt += 4) { step_late_at(kt, P0{}); step_late_at(kt + 1, P1{}); step_late_at(kt + 2, P2{}); step_late_at(kt + 3, P3{}); }
       for (; kt + D + 1 < KT; ++kt) step_late(kt, T{}, std::integral_constant<int, (D - 1) * CP>{}, F{});
-      tail(step_late, kt);
+      // with j steps of copies ahead left, (j - 1) * CP copies may stay pending at the barrier
+      if (kt + 3 < KT) { step_late(kt, F{}, std::integral_constant<int, 2 * CP>{}, F{}); ++kt; }
+      if (kt + 2 < KT) { step_late(kt, F{}, std::integral_constant<int, CP>{}, F{}); ++kt; }
+      if (kt + 1 < KT) { step_late(kt, F{}, std::integral_constant<int, 0>{}, F{}); ++kt; }
+      step_late(kt, F{}, std::integral_constant<int, 0>{}, T{});
     }
   };
 
@@ -772,11 +769,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
     constexpr int CP = decltype(cp_tag)::value;
     issue_copy(0, cp_tag);
     if (KT > 1) issue_copy(1, cp_tag);
-    if (D >= 3 && KT > 2) issue_copy(2, cp_tag);
-    if (D >= 4 && KT > 3) issue_copy(3, cp_tag);
+    if (KT > 2) issue_copy(2, cp_tag);
     asm volatile("" ::: "memory");
-    if (D >= 4 && KT > 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(3 * CP));
-    else if (D >= 3 && KT > 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * CP));
+    if (KT > 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(2 * CP));
     else if (KT > 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(CP));
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
   };
@@ -786,64 +781,65 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 
-  if (tall) {  // at least 2 * TM - 1 sub-tiles
+  if (tall) {  // more than BM0 rows: at least TM0 sub-tiles
     if (tm_valid == TM) run(std::integral_constant<int, TM>{}, CpTall{});
-    else run(std::integral_constant<int, (TM > 1 ? TM - 1 : TM)>{}, CpTall{});
+    else if (tm_valid == TM - 1) run(std::integral_constant<int, TM - 1>{}, CpTall{});
+    else run(std::integral_constant<int, TM0>{}, CpTall{});
   } else {
     switch (tm_valid) {
       case 0: run(std::integral_constant<int, 0>{}, Cp{}); break;
       case 1: run(std::integral_constant<int, 1>{}, Cp{}); break;
-      case 2: run(std::integral_constant<int, (TM >= 2 ? 2 : TM)>{}, Cp{}); break;
-      case 3: run(std::integral_constant<int, (TM >= 3 ? 3 : TM)>{}, Cp{}); break;
-      default: run(std::integral_constant<int, (TM >= 4 ? 4 : TM)>{}, Cp{}); break;
+      case 2: run(std::integral_constant<int, 2>{}, Cp{}); break;
+      case 3: run(std::integral_constant<int, 3>{}, Cp{}); break;
+      case 4: run(std::integral_constant<int, 4>{}, Cp{}); break;
+      case 5: run(std::integral_constant<int, 5>{}, Cp{}); break;
+      case 6: run(std::integral_constant<int, 6>{}, Cp{}); break;
+      case 7: run(std::integral_constant<int, 7>{}, Cp{}); break;
+      default: run(std::integral_constant<int, TM0>{}, Cp{}); break;
     }
   }
 
-  // ---- epilogue.  Per 32x32 tile a lane holds, for q = 0..3, the four columns
-  // q*8 + (lane/32)*4 + {0..3} of activation row lane % 32.  Each wavefront transposes its
-  // outputs through its own slice of LDS (padded rows: conflict-free 8-byte writes) and stores
-  // them to global memory as full 16-byte words, a whole row segment per group of lanes.
+  // ---- epilogue.  Per 16x16 tile a lane holds the four columns (lane/16)*4 + {0..3} of activation
+  // row lane % 16.  Each wavefront transposes its outputs through its own slice of LDS (padded rows)
+  // and stores them to global memory as full 16-byte words, a whole row segment per group of lanes.
   constexpr int TN_OUT = EPI == EPI_SWIGLU ? TN / 2 : TN;
   constexpr int WN_OUT = EPI == EPI_SWIGLU ? WN / 2 : WN;
   static_assert(EPI != EPI_F32, "this kernel stores bf16");
   constexpr int ROWB = WN_OUT * 2 + 8;          // bytes between rows of the wavefront's LDS slice
   constexpr int PASS = epilogue_pass(TM, NW, ROWB);  // row sub-tiles that fit the LDS at a time
-  constexpr int SLICE = PASS * 32 * ROWB;
+  constexpr int SLICE = PASS * 16 * ROWB;
   constexpr int LPR = WN_OUT * 2 / 16;          // lanes per row when reading back
-  constexpr int RPI = 64 / LPR;                 // rows per read-back instruction
+  constexpr int RPI = 64 / LPR;                 // rows per read-back instruction, inside one sub-tile
+  static_assert(RPI <= 16, "read-back");
   __syncthreads();                              // every wavefront is done with the copy stages
   unsigned char* slice = smem + wave * SLICE;
   const int rcol = (lane % LPR) * 8;
   const int col = n0 + wn * WN_OUT + rcol;
 #pragma unroll
   for (int p0 = 0; p0 < TM; p0 += PASS) {
-    if (p0 >= tm_valid) break;
 #pragma unroll
-    for (int tm = p0; tm < p0 + PASS && tm < TM; ++tm) {
-      if (tm >= tm_valid) break;
+    for (int tm = p0; tm < (p0 + PASS < TM ? p0 + PASS : TM); ++tm) {
+      if (tm >= tm_valid) continue;
 #pragma unroll
       for (int tn = 0; tn < TN_OUT; ++tn) {
+        float v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float v[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            if (EPI == EPI_SWIGLU) v[r] = silu_f32(acc[tm][tn][q * 4 + r]) * acc[tm][tn + TN / 2][q * 4 + r];
-            else v[r] = acc[tm][tn][q * 4 + r];
-          }
-          u32x2 o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-          *reinterpret_cast<u32x2*>(slice + ((tm - p0) * 32 + (lane & 31)) * ROWB + (tn * 32 + q * 8 + (lane >> 5) * 4) * 2) = o;
+        for (int r = 0; r < 4; ++r) {
+          if (EPI == EPI_SWIGLU) v[r] = silu_f32(acc[tm][tn][r]) * acc[tm][tn + TN / 2][r];
+          else v[r] = acc[tm][tn][r];
         }
+        u32x2 o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        *reinterpret_cast<u32x2*>(slice + ((tm - p0) * 16 + (lane & 15)) * ROWB + (tn * 16 + (lane >> 4) * 4) * 2) = o;
       }
     }
     // read back: lane l takes 16 bytes (8 columns) of row l / LPR of each group of RPI rows
     if (col >= g.n_out) continue;  // n_out is a multiple of 8: a word is entirely inside or outside
 #pragma unroll
-    for (int it = 0; it < PASS * 32 / RPI; ++it) {
+    for (int it = 0; it < PASS * 16 / RPI; ++it) {
       const int lrow = it * RPI + lane / LPR;     // row inside the wavefront's slice
-      const int tm = p0 + (lrow >> 5);
+      const int tm = p0 + (it * RPI >> 4);
       if (tm >= tm_valid) break;
-      const int row = row_begin + (tm * WAVES_M + wm) * 32 + (lrow & 31);
+      const int row = row_begin + (tm * WAVES_M + wm) * 16 + (lrow & 15);
       if (row < row_end) {
         const u32x4 o = *reinterpret_cast<const u32x4*>(slice + lrow * ROWB + rcol * 2);
         uint16_t* dst = static_cast<uint16_t*>(g.C);
@@ -871,16 +867,16 @@ int launch_gemm_bf16(revive_ctx* ctx, const GemmArgs& args, int max_m_tiles, hip
   return check_hip(ctx, hipGetLastError(), "gemm_bf16 launch");
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID, int STAGES = 4>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID>
 int launch_gemm_bf16_dma(revive_ctx* ctx, const GemmArgs& p0, int max_m_tiles0, const GemmArgs* p1, int max_m_tiles1,
                          hipStream_t stream) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WN_OUT_ = (EPI == EPI_SWIGLU ? BN / 2 : BN) / WAVES_N;
   constexpr int rowb = WN_OUT_ * 2 + 8;
-  constexpr size_t lds_epi = static_cast<size_t>(WAVES_M * WAVES_N) * epilogue_pass(BM / WAVES_M / 32, WAVES_M * WAVES_N, rowb) * 32 * rowb;
-  constexpr size_t lds_ring = STAGES * (BM + BN) * 64;
+  constexpr size_t lds_epi = static_cast<size_t>(WAVES_M * WAVES_N) * epilogue_pass(BM / WAVES_M / 16, WAVES_M * WAVES_N, rowb) * 16 * rowb;
+  constexpr size_t lds_ring = kStages * (BM + BN) * 64;
   constexpr size_t lds = lds_ring > lds_epi ? lds_ring : lds_epi;
-  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, EPI, KID, STAGES>;
+  auto kern = gemm_bf16_dma_kernel<BM, BN, WAVES_M, WAVES_N, EPI, KID>;
   REVIVE_HIP(ctx, allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
   GemmArgs2 a{};
   a.p0 = p0;

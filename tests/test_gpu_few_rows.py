@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 
 EDGES = [1, 0, 16, 15, 17, 32, 33, 64, 0, 65, 2, 127, 128, 129, 256, 257, 300, 0]
 TALL = [257, 0, 288, 289, 319, 320, 321, 256, 577, 304, 272]  # 128 rows per slot or more on average
+SUB_TILES = [16 * i + d for i in range(20) for d in (1, 16)] + [321, 513, 767, 1025, 1300]
 # (H, I, rows of the slots): one group of K up to several, K no multiple of the ring, columns that are half a tile
 CASES = {
     "edges": (256, 192, EDGES + [0] * 90),  # up to 16 rows per slot on average the weights are always streamed
@@ -25,6 +26,8 @@ CASES = {
     "small_tiles": (704, 320, [130, 65, 64, 1, 0, 16, 3] + [0] * 13),
     # the same with enough workgroups for tall tiles
     "tall_many_short_k": (64, 64, TALL * 12), "tall_many": (192, 320, TALL * 12), "tall_wide": (2880, 1472, TALL),
+    # every number of 16-row sub-tiles that a wavefront may have, full and by one row, and slots of several row-tiles
+    "sub_tiles": (256, 192, SUB_TILES), "sub_tiles_tall": (1088, 448, SUB_TILES),
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
