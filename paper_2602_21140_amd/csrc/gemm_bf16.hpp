@@ -3,20 +3,15 @@
 //   C[rows of tile, n] = sum_k A[row, k] * B_group[n, k]        ("NT": both operands K-contiguous)
 //
 // A is one tall activation matrix whose rows are split into row-tiles that each belong to one
-// group (physical expert slot); B is that group's output-major weight matrix.  Three epilogues:
-//   EPI_F32     store fp32                         (router logits)
+// group (physical expert slot); B is that group's output-major weight matrix.  Two epilogues:
 //   EPI_BF16    round to bf16 and store            (down projection)
 //   EPI_SWIGLU  B holds gate rows [0, n_out) and up rows [n_out, 2 n_out); store
 //               bf16(silu(gate) * up)              (gate/up projection of a SwiGLU expert)
 //
 // Work decomposition: one workgroup computes a BM x BN tile with WAVES_M x WAVES_N wavefronts of
-// 64 lanes; each wavefront owns (BM/WAVES_M) x (BN/WAVES_N) outputs as 32x32 MFMA tiles.  K is
-// walked in steps of 64: the next step's global loads are issued into registers before the MFMAs
-// of the current step and written to the other half of a double-buffered LDS tile afterwards, one
-// barrier per step.  LDS rows are 128 bytes (64 bf16); the 16-byte chunk index is XOR-ed with
-// ((row >> 1) & 7) so that both the 16-byte writes and the per-lane 16-byte fragment reads are
-// conflict-free on the 64-bank LDS.  The weights go in as the MFMA's first operand so that each lane ends up with
-// four consecutive output columns of one activation row, which it stores as one 8/16-byte word.
+// 64 lanes; each wavefront owns (BM/WAVES_M) x (BN/WAVES_N) outputs as 16x16 MFMA tiles.  The
+// weights go in as the MFMA's first operand so that each lane ends up with four consecutive output
+// columns of one activation row.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,7 +23,6 @@
 namespace revive {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -40,7 +34,7 @@ __device__ __forceinline__ u32x4 load_global_16B(const unsigned char* p) {
   return *reinterpret_cast<gptr_u32x4>(reinterpret_cast<uintptr_t>(p));
 }
 
-enum { EPI_F32 = 0, EPI_BF16 = 1, EPI_SWIGLU = 2 };
+enum { EPI_BF16 = 1, EPI_SWIGLU = 2 };
 
 // Tiled weight layout: a [rows, K] output-major matrix is stored as [rows/128][K/32][128][32]
 // (rows zero-padded to a multiple of 128), so the 128 x 32 block a workgroup fetches per K-step is
@@ -54,7 +48,7 @@ struct GemmArgs {
   const void* const* B_tab;  // device table: group -> [n_rows_B, K] bf16, or null
   const void* B_one;         // used for every group when B_tab is null
   int64_t ldb;               // elements between rows of B
-  void* C;                   // [rows, n_out] fp32 or bf16
+  void* C;                   // [rows, n_out] bf16
   int64_t ldc;
   int n_out;                 // output columns (SwiGLU: I, with B holding 2*I rows)
   int K;                     // multiple of 64
@@ -68,7 +62,7 @@ struct GemmArgs {
   int a_rows;                // > 0: A is stored K-panel-major, [K/32][a_rows][32]: the 32 K-elements of a row that one
                              // K-step needs are 64 contiguous bytes and consecutive rows follow each other, so the
                              // copies of a row-tile read one contiguous run per K-step (used for the intermediate h)
-  int c_rows;                // > 0 (bf16 epilogues): C is written in the same layout, [n_out/32][c_rows][32]
+  int c_rows;                // > 0: C is written in the same layout, [n_out/32][c_rows][32]
 };
 
 // Up to two independent problems served by one launch (e.g. the routed experts' grouped GEMM and
@@ -77,15 +71,6 @@ struct GemmArgs2 {
   GemmArgs p0, p1;
   int two;  // 0: only p0 is valid
 };
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
-
-// Round-to-nearest-even fp32 -> bf16 bits (finite inputs).
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
 
 // Two fp32 -> one word of two bf16 (round-to-nearest-even), one v_cvt_pk_bf16_f32.
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
@@ -106,243 +91,11 @@ __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 // exp overflows to +inf for z < -88, where the product is the correct -0.
 __device__ __forceinline__ float silu_f32(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 
-// KID (the library's kernel id) only gives each use of the kernel its own symbol name in profiles.
-// SLICES > 1: K is summed in SLICES parts, [K/64 * q / SLICES, K/64 * (q+1) / SLICES) steps of 64 elements, and the
-// partial sums are added in their order: the bits of a kernel whose wavefronts share K that way.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID, int SLICES = 1>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_kernel(GemmArgs g) {
-  constexpr int NT = 64 * WAVES_M * WAVES_N;
-  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int ITER_A = BM * 8 / NT, ITER_B = BN * 8 / NT;
-  constexpr int BN_OUT = EPI == EPI_SWIGLU ? BN / 2 : BN;  // output columns per workgroup
-  constexpr int STAGE = (BM + BN) * 128;                   // bytes of one LDS stage
-  static_assert(BM % (32 * WAVES_M) == 0 && BN % (32 * WAVES_N) == 0, "tile shape");
-  static_assert((BM * 8) % NT == 0 && (BN * 8) % NT == 0, "load split");
-  static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-  // ---- which tile is mine: spread the valid tiles evenly over the 8 XCDs (workgroup i runs on
-  // XCD i % 8) so that each XCD's L2 sees a contiguous run of tiles sharing activations/weights.
-  const int n_m_tiles = g.tiles ? *g.tile_count : (g.M + BM - 1) / BM;
-  const int total = n_m_tiles * g.n_col_tiles;
-  const int per_xcd = (total + 7) >> 3;
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const int logical = xcd * per_xcd + local;
-  if (local >= per_xcd || logical >= total) return;
-  const int m_idx = logical / g.n_col_tiles;
-  const int n_idx = logical - m_idx * g.n_col_tiles;
-
-  int group = 0, row_begin, row_end;
-  if (g.tiles) {
-    const MTile t = g.tiles[m_idx];
-    group = t.group;
-    tile_span(t.group_begin, t.group_end, t.pad >> 16, t.pad & 0xFFFF, row_begin, row_end);
-  } else {
-    row_begin = m_idx * BM;
-    row_end = min(g.M, row_begin + BM);
-  }
-  const unsigned char* Bbase = static_cast<const unsigned char*>(g.B_tab ? g.B_tab[group] : g.B_one);
-  const unsigned char* Abase = static_cast<const unsigned char*>(g.A);
-  const int n0 = n_idx * BN_OUT;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-
-  // ---- per-thread global sources and LDS destinations of the cooperative tile loads
-  const unsigned char* a_src[ITER_A];
-  const unsigned char* b_src[ITER_B];
-  int a_dst[ITER_A], b_dst[ITER_B];
-#pragma unroll
-  for (int it = 0; it < ITER_A; ++it) {
-    const int idx = it * NT + tid, row = idx >> 3, chunk = idx & 7;
-    const int grow = min(row_begin + row, row_end - 1);  // rows past the tile re-read its last row
-    a_src[it] = Abase + (static_cast<int64_t>(grow) * g.lda + chunk * 8) * 2;
-    a_dst[it] = row * 128 + ((chunk ^ swz(row)) << 4);
-  }
-#pragma unroll
-  for (int it = 0; it < ITER_B; ++it) {
-    const int idx = it * NT + tid, row = idx >> 3, chunk = idx & 7;
-    int brow;
-    if (EPI == EPI_SWIGLU) {
-      const int half = row >= BN / 2;
-      const int col = min(n0 + row - half * (BN / 2), g.n_out - 1);
-      brow = col + half * g.n_out;
-    } else {
-      brow = min(n0 + row, g.n_out - 1);
-    }
-    b_src[it] = Bbase + (static_cast<int64_t>(brow) * g.ldb + chunk * 8) * 2;
-    b_dst[it] = BM * 128 + row * 128 + ((chunk ^ swz(row)) << 4);
-  }
-
-  // ---- per-lane LDS fragment addresses (without the k-step part)
-  int a_frag[TM], b_frag[TN];
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm) a_frag[tm] = wm * WM + tm * 32 + (lane & 31);
-#pragma unroll
-  for (int tn = 0; tn < TN; ++tn) {
-    int r;
-    if (EPI == EPI_SWIGLU) {
-      const int half = tn >= TN / 2;
-      r = half * (BN / 2) + wn * (WN / 2) + (tn - half * (TN / 2)) * 32 + (lane & 31);
-    } else {
-      r = wn * WN + tn * 32 + (lane & 31);
-    }
-    b_frag[tn] = BM + r;
-  }
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0.f;
-
-  u32x4 a_reg[ITER_A], b_reg[ITER_B];
-  auto load_global = [&](int kt) {
-    const int64_t koff = static_cast<int64_t>(kt) * 128;  // 64 bf16
-#pragma unroll
-    for (int it = 0; it < ITER_A; ++it) a_reg[it] = load_global_16B(a_src[it] + koff);
-#pragma unroll
-    for (int it = 0; it < ITER_B; ++it) b_reg[it] = load_global_16B(b_src[it] + koff);
-  };
-  auto store_lds = [&](int stage) {
-    unsigned char* base = smem + stage * STAGE;
-#pragma unroll
-    for (int it = 0; it < ITER_A; ++it) *reinterpret_cast<u32x4*>(base + a_dst[it]) = a_reg[it];
-#pragma unroll
-    for (int it = 0; it < ITER_B; ++it) *reinterpret_cast<u32x4*>(base + b_dst[it]) = b_reg[it];
-  };
-
-  // Fragment loads of one 16-wide k-step from an LDS stage.
-  auto load_frags = [&](const unsigned char* base, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
-    const int chunk = ks * 2 + (lane >> 5);
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm) {
-      const int r = a_frag[tm];
-      af[tm] = *reinterpret_cast<const bf16x8*>(base + r * 128 + ((chunk ^ swz(r)) << 4));
-    }
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
-      const int r = b_frag[tn];
-      bfr[tn] = *reinterpret_cast<const bf16x8*>(base + r * 128 + ((chunk ^ swz(r)) << 4));
-    }
-  };
-  auto mfma_step = [&](const bf16x8 (&af)[TM], const bf16x8 (&bfr)[TN]) {
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-        acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[tn], af[tm], acc[tm][tn], 0, 0, 0);
-  };
-
-  // Software pipeline: the fragments of k-step s+1 are read from LDS while the MFMAs of step s
-  // run; the next K-tile (already in registers) is written to the other LDS stage and the
-  // workgroup synchronised *before* the last k-step's MFMAs, so that the first fragments of the
-  // next stage are in flight while those MFMAs execute.
-  const int KT = g.K >> 6;
-  f32x16 sum[TM][TN];  // SLICES > 1: the finished slices
-  int slice = 1, slice_end = KT / SLICES;  // empty slices (KT < SLICES) are passed over
-  if (SLICES > 1) {
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) sum[tm][tn] = acc[tm][tn];
-    while (slice_end == 0) slice_end = KT * ++slice / SLICES;
-  }
-  bf16x8 af0[TM], bf0[TN], af1[TM], bf1[TN];
-  load_global(0);
-  store_lds(0);
-  __syncthreads();
-  if (KT > 1) load_global(1);
-  load_frags(smem, 0, af0, bf0);
-
-  for (int kt = 0; kt < KT; ++kt) {
-    const unsigned char* cur = smem + (kt & 1) * STAGE;
-    load_frags(cur, 1, af1, bf1);
-    mfma_step(af0, bf0);
-    load_frags(cur, 2, af0, bf0);
-    mfma_step(af1, bf1);
-    load_frags(cur, 3, af1, bf1);
-    mfma_step(af0, bf0);
-    if (kt + 1 < KT) {
-      store_lds((kt + 1) & 1);
-      if (kt + 2 < KT) load_global(kt + 2);
-      __syncthreads();
-      load_frags(smem + ((kt + 1) & 1) * STAGE, 0, af0, bf0);
-    }
-    mfma_step(af1, bf1);
-    if (SLICES > 1 && kt + 1 == slice_end) {
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            sum[tm][tn][i] += acc[tm][tn][i];
-            acc[tm][tn][i] = 0.f;
-          }
-      while (slice < SLICES && slice_end == kt + 1) slice_end = KT * ++slice / SLICES;
-    }
-  }
-  if (SLICES > 1) {
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = sum[tm][tn];
-  }
-
-  // ---- epilogue.  Lane holds, per 32x32 tile, for q = 0..3 the four columns
-  // q*8 + (lane/32)*4 + {0..3} of activation row lane % 32.
-  constexpr int TN_OUT = EPI == EPI_SWIGLU ? TN / 2 : TN;
-  constexpr int WN_OUT = EPI == EPI_SWIGLU ? WN / 2 : WN;
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm) {
-    const int row = row_begin + wm * WM + tm * 32 + (lane & 31);
-    if (row >= row_end) continue;
-#pragma unroll
-    for (int tn = 0; tn < TN_OUT; ++tn) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = n0 + wn * WN_OUT + tn * 32 + q * 8 + (lane >> 5) * 4;
-        if (col >= g.n_out) continue;
-        float v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (EPI == EPI_SWIGLU) v[r] = silu_f32(acc[tm][tn][q * 4 + r]) * acc[tm][tn + TN / 2][q * 4 + r];
-          else v[r] = acc[tm][tn][q * 4 + r];
-        }
-        const int64_t off = static_cast<int64_t>(row) * g.ldc + col;
-        if (col + 3 < g.n_out && (g.ldc & 3) == 0) {
-          if (EPI == EPI_F32) {
-            f32x4 o = {v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + off) = o;
-          } else {
-            u32x2 o = {f32_to_bf16_bits(v[0]) | (f32_to_bf16_bits(v[1]) << 16),
-                       f32_to_bf16_bits(v[2]) | (f32_to_bf16_bits(v[3]) << 16)};
-            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(g.C) + off) = o;
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            if (col + r >= g.n_out) break;
-            if (EPI == EPI_F32) static_cast<float*>(g.C)[off + r] = v[r];
-            else static_cast<uint16_t*>(g.C)[off + r] = static_cast<uint16_t>(f32_to_bf16_bits(v[r]));
-          }
-        }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Variant with asynchronous global->LDS copies (global_load_lds_dwordx4), a four-stage ring and
-// 16x16x32 MFMAs.
+// Operands reach LDS by asynchronous copies (global_load_lds_dwordx4) through a four-stage ring.
 //
-// Same contract and output layout as gemm_bf16_kernel.  K is walked in steps of 32; a stage holds
+// KID (the library's kernel id) only gives each use of the kernel its own symbol name in profiles.
+//
+// K is walked in steps of 32; a stage holds
 // a BM x 32 tile of A and a BN x 32 tile of B (64-byte rows).  The copy of K-step t+3 is issued
 // while step t is being multiplied, so three steps (about 1.3 us of MFMA work at full rate) are
 // in flight to cover HBM latency, and no register is spent on staging.  Per K-step there is one
@@ -804,7 +557,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   // and stores them to global memory as full 16-byte words, a whole row segment per group of lanes.
   constexpr int TN_OUT = EPI == EPI_SWIGLU ? TN / 2 : TN;
   constexpr int WN_OUT = EPI == EPI_SWIGLU ? WN / 2 : WN;
-  static_assert(EPI != EPI_F32, "this kernel stores bf16");
   constexpr int ROWB = WN_OUT * 2 + 8;          // bytes between rows of the wavefront's LDS slice
   constexpr int PASS = epilogue_pass(TM, NW, ROWB);  // row sub-tiles that fit the LDS at a time
   constexpr int SLICE = PASS * 16 * ROWB;
@@ -854,19 +606,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
 
 // Launch helpers: grids cover `max_m_tiles` row-tiles per problem (upper bounds; surplus
 // workgroups exit at once).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID, int SLICES = 1>
-int launch_gemm_bf16(revive_ctx* ctx, const GemmArgs& args, int max_m_tiles, hipStream_t stream) {
-  constexpr int NT = 64 * WAVES_M * WAVES_N;
-  constexpr size_t lds = 2 * (BM + BN) * 128;
-  auto kern = gemm_bf16_kernel<BM, BN, WAVES_M, WAVES_N, EPI, KID, SLICES>;
-  REVIVE_HIP(ctx, allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
-  const int64_t total = static_cast<int64_t>(max_m_tiles) * args.n_col_tiles;
-  if (total <= 0) return REVIVE_OK;
-  const int grid = static_cast<int>((total + 7) / 8 * 8);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, stream, args);
-  return check_hip(ctx, hipGetLastError(), "gemm_bf16 launch");
-}
-
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KID>
 int launch_gemm_bf16_dma(revive_ctx* ctx, const GemmArgs& p0, int max_m_tiles0, const GemmArgs* p1, int max_m_tiles1,
                          hipStream_t stream) {

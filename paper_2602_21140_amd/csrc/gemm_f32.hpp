@@ -50,7 +50,7 @@ struct GemmF32Args {
 
 constexpr int kTileN_f32 = 64;
 
-// SLICES > 1: the K-steps are summed in SLICES parts that are added in their order (see gemm_bf16_kernel).
+// SLICES > 1: the K-steps are summed in SLICES parts that are added in their order (see router_tile_kernel).
 template <bool SWIGLU, int D, int SLICES = 1>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   typedef __attribute__((ext_vector_type(4))) float f32x4;

@@ -6,8 +6,8 @@
 // (the logical-to-physical map decides which replica serves a token).
 #include <algorithm>
 
-#include "gemm_bf16.hpp"
 #include "gemm_f32.hpp"
+#include "router_sequence.hpp"
 
 namespace revive {
 
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
 template <typename T> struct RouterMath;
 template <> struct RouterMath<uint16_t> {
   static __device__ __forceinline__ f32x4 mac(u32x4 w, u32x4 x, f32x4 acc) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
+    return mfma_16x16x32(w, x, acc);
   }
 };
 template <> struct RouterMath<float> {
@@ -368,72 +368,6 @@ int launch_router(revive_ctx* ctx, const void* x, const void* w, float* logits, 
   return check_hip(ctx, hipGetLastError(), "router launch");
 }
 
-// The same product for few tokens with K summed in one sequence, in the very order of the GEMM that serves
-// more tokens (a token's logits must not depend on how many others are in the call).  16 tokens and 16
-// experts per workgroup; eight wavefronts fetch eight steps of 64 K-elements at a time, two rounds ahead, and
-// the first one multiplies them in order, 224 dependent MFMAs at H = 7168.  Between events, E = 256: 1 token
-// 53 -> 14 us, 192 tokens 53 -> 15 (10 and 11 with K split), 512 tokens 54 -> 21.
-__global__ __launch_bounds__(512, 2) void router_sequence_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
-                                                                 float* __restrict__ logits, int T, int E, int H, int n_exp) {
-  constexpr int KS = 8, D = 2;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[D][KS][32 * 128];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t0 = blockIdx.x / n_exp * 16, e0 = blockIdx.x % n_exp * 16;
-  const int64_t row_bytes = static_cast<int64_t>(H) * 2;
-  const unsigned char* xb = reinterpret_cast<const unsigned char*>(x) + t0 * row_bytes;
-  const unsigned char* wb = reinterpret_cast<const unsigned char*>(w) + e0 * row_bytes;
-  const int steps = H >> 6;  // H is a multiple of 64
-  uint32_t off[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {  // rows past the last token or expert: the last one again, not stored
-    const int r = (i & 1) * 8 + (lane >> 3);
-    off[i] = static_cast<uint32_t>((i < 2 ? min(r, T - 1 - t0) : min(r, E - 1 - e0)) * row_bytes + (lane & 7) * 16);
-  }
-  u32x4 buf[D][4];
-  auto load = [&](int round, int d) {
-    const int64_t k = static_cast<int64_t>(min(round * KS + wave, steps - 1)) * 128;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) buf[d][i] = load_global_16B((i < 2 ? xb : wb) + off[i] + k);
-  };
-  const int r16 = lane & 15, quad = lane >> 4;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int d = 0; d < D; ++d) load(d, d);
-  for (int r0 = 0; r0 * KS < steps; r0 += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = i * 8 + (lane >> 3);
-        *reinterpret_cast<u32x4*>(lds[d][wave] + r * 128 + (((lane & 7) ^ swz(r)) << 4)) = buf[d][i];
-      }
-      load(r0 + d + D, d);
-      // A buffer is written again two barriers later: the first wavefront has then read it.
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      if (wave == 0) {
-#pragma unroll
-        for (int q = 0; q < KS; ++q) {
-          if ((r0 + d) * KS + q < steps) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const unsigned char* p = lds[d][q] + r16 * 128 + (((h * 4 + quad) ^ swz(r16)) << 4);
-              acc = RouterMath<uint16_t>::mac(*reinterpret_cast<const u32x4*>(p + 16 * 128), *reinterpret_cast<const u32x4*>(p), acc);
-            }
-          }
-        }
-      }
-    }
-  }
-  if (wave == 0 && t0 + r16 < T) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (e0 + quad * 4 + i < E) logits[static_cast<int64_t>(t0 + r16) * E + e0 + quad * 4 + i] = acc[i];
-  }
-}
-
 // The larger tile once it gives every CU a workgroup: it reads x and w half as often.  us between events, bf16,
 // 16 x 16 against 32 x 32 tiles: E = 64, H = 2048, 2000 tokens (126 workgroups of the larger tile) 8.5 and 8.8, 4096
 // (256) 13.0 and 10.1; E = 128, H = 7168, 1000 tokens (128) 16.6 and 16.9, 2000 (252) 27.3 and 18.6, 4096 (512) 49
@@ -447,26 +381,43 @@ int router(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, 
   return launch_router<El, 1, 1, kRouterSlices, 4>(ctx, x, w, logits, T, stream);
 }
 
-// Many tokens in bf16, K in one sequence or in the router kernel's slices.  128 x 128 tiles read x fewer times where
-// they still fill the chip twice over; with slices the second set of sums leaves them one workgroup per CU
-// (65 536 tokens, E = 64, H = 2048: 72 us against 47 for 128 x 64; E = 128: 81 and 80).
-template <int SLICES>
-int router_gemm(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
-  const revive_config& c = ctx->cfg;
-  GemmArgs a{};
-  a.A = x; a.lda = c.H;
-  a.B_one = w; a.ldb = c.H;
-  a.C = logits; a.ldc = c.E;
-  a.n_out = c.E; a.K = c.H;
-  a.M = T;
-  if constexpr (SLICES == 1) {
-    if (static_cast<int64_t>(ceil_div(T, 128)) * ceil_div(c.E, 128) >= 512) {
-      a.n_col_tiles = ceil_div(c.E, 128);
-      return launch_gemm_bf16<128, 128, 2, 2, EPI_F32, REVIVE_K_ROUTER_GEMM>(ctx, a, ceil_div(T, 128), stream);
-    }
-  }
-  a.n_col_tiles = ceil_div(c.E, 64);
-  return launch_gemm_bf16<128, 64, 4, 1, EPI_F32, REVIVE_K_ROUTER_GEMM, SLICES>(ctx, a, ceil_div(T, 128), stream);
+template <int XR, int WR>
+int router_sequence(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
+  const int E = ctx->cfg.E, n_exp = ceil_div(E, WR);
+  hipLaunchKernelGGL((router_sequence_kernel<XR, WR, 2>), dim3(ceil_div(T, XR) * n_exp), dim3(512), 0, stream,
+                     static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), logits, T, E, ctx->cfg.H, n_exp);
+  return check_hip(ctx, hipGetLastError(), "router_sequence launch");
+}
+
+template <int BM, int BN, int WM, int WN, int BK, int S, int SLICES = 1>
+int router_tile(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
+  constexpr size_t lds = static_cast<size_t>(S) * (BM + BN) * BK * 2;
+  auto kern = router_tile_kernel<BM, BN, WM, WN, BK, S, SLICES>;
+  REVIVE_HIP(ctx, allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
+  const int E = ctx->cfg.E, n_tok = ceil_div(T, BM), n_exp = ceil_div(E, BN);
+  hipLaunchKernelGGL(kern, dim3(ceil_div(n_tok, 8) * 8 * n_exp), dim3(64 * WM * WN), lds, stream, static_cast<const uint16_t*>(x),
+                     static_cast<const uint16_t*>(w), logits, T, E, ctx->cfg.H, n_tok, n_exp);
+  return check_hip(ctx, hipGetLastError(), "router_tile launch");
+}
+
+// K in one sequence: the smallest tiles of which 256 cover the logits, one per CU.  us with cold caches, E = 256,
+// H = 7168, of a 128 x 64 register-staged GEMM and of the tile taken: 512 tokens 73 and 19 (seq. 16 x 16: 20), 1003
+// tokens 74 and 21 (32 x 64 tiles 25), 2048 74 and 26 (32 x 32 tiles 32, 64 x 64 36), 4096 77 and 36 (32 x 64 49, 64 x 128
+// 50), 8192 81 and 54 (64 x 64 68, 128 x 128 73), 16 384 95 and 79 (64 x 128 102), 32 768 163 and 129 (128 x 128 156);
+// 32 768 tokens and E = 384 247 and 187 (128 x 128 219).
+int router_one_sequence(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
+  const int E = ctx->cfg.E;
+  auto fits = [&](int bm, int bn) { return static_cast<int64_t>(ceil_div(T, bm)) * ceil_div(E, bn) <= 256; };
+  if (fits(8, 8)) return router_sequence<8, 8>(ctx, x, w, logits, T, stream);
+  if (fits(16, 16) || ctx->cfg.H < 128) return router_sequence<16, 16>(ctx, x, w, logits, T, stream);
+  if (fits(32, 32)) return router_tile<32, 32, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
+  if (fits(32, 64)) return router_tile<32, 64, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
+  if (fits(64, 64)) return router_tile<64, 64, 4, 2, 128, 4>(ctx, x, w, logits, T, stream);
+  if (fits(64, 128)) return router_tile<64, 128, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
+  const int wide = ceil_div(E, 256), each = ceil_div(E, wide);  // column tiles of up to 256 experts, and their experts
+  if (static_cast<int64_t>(ceil_div(T, 128)) * wide < 256) return router_tile<128, 128, 2, 4, 64, 4>(ctx, x, w, logits, T, stream);
+  if (each <= 192) return router_tile<128, 192, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
+  return router_tile<128, 256, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
 }
 
 // Many tokens in fp32, K in the router kernel's slices.  The number of experts is a multiple of 4.
@@ -506,18 +457,13 @@ int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* log
   const bool small = c.E <= 128 && c.H % 256 == 0;
   if (small) {
     if (static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20)) return router<uint16_t>(ctx, x, w, logits, T, stream);
-    return router_gemm<kRouterSlices>(ctx, x, w, logits, T, stream);
+    return c.E <= 64 ? router_tile<128, 64, 4, 2, 64, 4, kRouterSlices>(ctx, x, w, logits, T, stream)
+                     : router_tile<128, 128, 2, 4, 64, 4, kRouterSlices>(ctx, x, w, logits, T, stream);
   }
-  // Many experts, or an odd K: K is summed in one sequence.  A K split is faster (1003 tokens, E = 256, H = 7168: 19 us
-  // against 71, 1 % of the layer) but another order moves one of 8192 x 256 logits across a near tie in every few
+  // Many experts, or an odd K: K is summed in one sequence.  A K split is faster for a middling number of tokens (1003
+  // tokens, E = 256, H = 7168: 19 us) but another order moves one of 8192 x 256 logits across a near tie in every few
   // calls.  (The small routers' sums are three times nearer the exact ones.)
-  if (T <= 512) {
-    const int n_exp = ceil_div(c.E, 16);
-    hipLaunchKernelGGL(router_sequence_kernel, dim3(ceil_div(T, 16) * n_exp), dim3(512), 0, stream, static_cast<const uint16_t*>(x),
-                       static_cast<const uint16_t*>(w), logits, T, c.E, c.H, n_exp);
-    return check_hip(ctx, hipGetLastError(), "router_sequence launch");
-  }
-  return router_gemm<1>(ctx, x, w, logits, T, stream);
+  return router_one_sequence(ctx, x, w, logits, T, stream);
 }
 
 int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk_logical, float* topk_weight,

@@ -63,3 +63,25 @@ def test_logits_do_not_depend_on_the_token_count(dtype, E, H):
     for T in (1, 17, 500, 512, 513, 2336, 2337, 4100):
         assert torch.equal(L.route(x[:T].contiguous(), w, T)[0], whole[:T]), T
     L.close()
+
+
+# K in one sequence: every tile size of the router (the limits are those of E = 256), a K that does not fill the last step
+# of 128 elements, one shorter than it, ragged experts; 192 and 256 experts per column tile
+@pytest.mark.parametrize("E,H", [(256, 192), (300, 448), (130, 128), (200, 64), (384, 320)])
+def test_every_tile_gives_the_same_bits(E, H):
+    n = 33000
+    cfg = SimpleNamespace(T=n, H=H, E=E, k=1, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype="bf16")
+    L = ReviveLayer(cfg)
+    L.set_placement(np.arange(E, dtype=np.int32))
+    L.update_map(np.zeros(1, dtype=np.uint8))
+    gen = torch.Generator(device="cuda").manual_seed(E)
+    x = torch.randn(n, H, generator=gen, device="cuda").to(L.dtype)
+    w = (torch.randn(E, H, generator=gen, device="cuda") * H ** -0.5).to(L.dtype)
+    whole = L.route(x, w, n)[0]
+    exact = x.double() @ w.double().T
+    assert (whole.double() - exact).abs().max().item() < 2e-5  # as in test_router_logits
+    for T in (1, 8, 9, 64, 65, 256, 257, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16000, 32640, 32641):
+        logits = torch.full((T, E), float("nan"), device="cuda")
+        assert torch.equal(L.route(x[:T].contiguous(), w, T, logits=logits)[0], whole[:T]), T
+    L.close()
