@@ -56,6 +56,22 @@ __device__ __forceinline__ void top2_step(float& m1, float& m2) {
   m2 = lo;
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {  // v of another lane
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(static_cast<long long>(hi) << 32 | static_cast<uint32_t>(lo));
+}
+
+// Slot of token t's expert e, which has `count` copies: the (batch index of t mod count)-th surviving one, ascending slot id.
+__device__ __forceinline__ int replica(const RouteParams& p, int t, int e, int count) {
+  if (count <= 0) return -1;
+  const unsigned long long b = static_cast<unsigned long long>(p.t_offset) + t;
+  const int r = p.t_offset + p.T <= 0x7fffffffll ? static_cast<int>(static_cast<uint32_t>(b) % static_cast<uint32_t>(count)) : static_cast<int>(b % count);
+  return p.l2p_table[e * p.max_replicas + r];
+}
+
 // A wavefront selects for TPW tokens.  Lane l holds the logits of experts l, l+64, l+128, ... (VALS of them)
 // of each; a masked or excluded expert's key is -inf.  Expert order is decided on the fp32 logits themselves
 // (softmax and sigmoid are increasing, so this is the order of the scores); group scores, which add two
@@ -215,16 +231,139 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
   }
   if (li < p.k && t < p.T) {
     const int64_t o = static_cast<int64_t>(t) * p.k + li;
-    // replica of this token: the (batch index of t mod count)-th surviving slot, ascending slot id
-    int phys = -1;
-    if (c > 0) {
-      const unsigned long long b = static_cast<unsigned long long>(p.t_offset) + t;
-      const int r = p.t_offset + p.T <= 0x7fffffffll ? static_cast<int>(static_cast<uint32_t>(b) % static_cast<uint32_t>(c)) : static_cast<int>(b % c);
-      phys = p.l2p_table[my_e * p.max_replicas + r];
-    }
     p.topk_logical[o] = my_e;
     p.topk_weight[o] = static_cast<float>(s / sum * static_cast<double>(p.route_scale));
-    p.topk_phys[o] = phys;
+    p.topk_phys[o] = replica(p, t, my_e, c);
+  }
+}
+
+// The same selection with 16 lanes, one DPP row, per token: four tokens to a wavefront, every instruction for all four.
+// Lane l of a row holds experts [l n, (l + 1) n), n = ceil(E / 16) <= V.  Groups are then whole runs of 16 / n_group
+// lanes (n_group a power of two up to 8, E a multiple of 16), a reduction is four steps instead of six, and ties go to
+// the lower lane and the lower place in it.  The kernel above gives a token 64 lanes and works on one after the other; it
+// is bound by the ALU from a few thousand tokens on (launch_route_topk has the figures).  WIDE: E is a multiple of 64, logits come in 16-byte words.
+template <int V, bool GROUPED, bool WIDE>
+__global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
+  static_assert(!WIDE || V % 4 == 0, "16-byte loads");
+  struct Choice { int e; float z; };
+  __shared__ Choice chosen[4][4][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane >> 4, li = lane & 15;
+  const int t0 = (blockIdx.x * 4 + wave) * 4, t = t0 + row;
+  if (t0 >= p.T) return;  // whole wavefront leaves together
+  const float NEG = -__builtin_inff();
+  const int n = (p.E + 15) >> 4, e0 = li * n;
+  const float* z = p.logits + static_cast<int64_t>(min(t, p.T - 1)) * p.E;
+
+  float key[V];
+  if (WIDE) {
+#pragma unroll
+    for (int i = 0; i < V; i += 4) {
+      if (i < n) {  // n is a multiple of 4
+        const f32x4 v = *reinterpret_cast<const f32x4*>(z + e0 + i);
+        const int4 c = *reinterpret_cast<const int4*>(p.l2p_count + e0 + i);
+        key[i] = c.x > 0 ? v[0] : NEG; key[i + 1] = c.y > 0 ? v[1] : NEG;  // failure mask
+        key[i + 2] = c.z > 0 ? v[2] : NEG; key[i + 3] = c.w > 0 ? v[3] : NEG;
+      } else {
+        key[i] = key[i + 1] = key[i + 2] = key[i + 3] = NEG;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const int e = min(e0 + i, p.E - 1);
+      const float v = z[e];
+      const int c = p.l2p_count[e];
+      key[i] = i < n && e0 + i < p.E && c > 0 ? v : NEG;
+    }
+  }
+  auto lane_max = [&]() {
+    float m = NEG;
+#pragma unroll
+    for (int i = 0; i < V; ++i) m = fmaxf(m, key[i]);
+    return m;
+  };
+  auto row_max = [&](float m) {
+    m = fmaxf(m, dpp_step<0>(m, NEG));
+    m = fmaxf(m, dpp_step<1>(m, NEG));
+    m = fmaxf(m, dpp_step<2>(m, NEG));
+    return fmaxf(m, dpp_step<3>(m, NEG));
+  };
+  // largest live logit of the token: common shift of the exponentials (the best chosen score is exactly 1)
+  const double shift = p.score_fn == REVIVE_SCORE_SIGMOID ? 0.0 : static_cast<double>(row_max(lane_max()));
+  auto score64 = [&](float v) -> double {  // unnormalised gating score of a live expert
+    const double d = static_cast<double>(v);
+    return p.score_fn == REVIVE_SCORE_SIGMOID ? 1.0 / (1.0 + exp(-d)) : exp(d - shift);
+  };
+
+  if (GROUPED) {
+    // Group score = sum of the two best live scores of the group (one if only one is live, -inf if none).  A NaN does
+    // not enter the pairs (see above).
+    const int lg = 16 / p.n_group;  // lanes of a group: 2, 4 or 8
+    float m1 = NEG, m2 = NEG;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const float v = key[i] > NEG ? key[i] : NEG;
+      m2 = fmaxf(m2, fminf(m1, v));
+      m1 = fmaxf(m1, v);
+    }
+    top2_step<0>(m1, m2);
+    if (lg >= 4) top2_step<1>(m1, m2);
+    if (lg >= 8) top2_step<2>(m1, m2);
+    const float mine = li & 1 ? m2 : m1;  // an even lane evaluates the group's best score, its neighbour the second
+    const double s = mine > NEG ? score64(mine) : 0.0;
+    const double both = s + dpp_f64<0xB1>(s);
+    const double gs = m1 > NEG ? both : -__builtin_inf();
+    // rank of my group among all groups of the token (better score first, ties to the lower group id)
+    int rank = 0;
+    double o = gs;
+    int h = li;
+    for (int r = 1; r < p.n_group; ++r) {
+      if (lg == 2) { o = dpp_f64<0x122>(o); h = __builtin_amdgcn_mov_dpp(h, 0x122, 0xF, 0xF, false); }       // rotate the row by a group
+      else if (lg == 4) { o = dpp_f64<0x124>(o); h = __builtin_amdgcn_mov_dpp(h, 0x124, 0xF, 0xF, false); }
+      else { o = dpp_f64<0x128>(o); h = __builtin_amdgcn_mov_dpp(h, 0x128, 0xF, 0xF, false); }
+      rank += (o > gs) || (o == gs && h < li);
+    }
+    const bool kept = rank < p.topk_group;
+#pragma unroll
+    for (int i = 0; i < V; ++i) key[i] = kept ? key[i] : NEG;
+  }
+
+  // k rounds of arg-max (largest key, ties to the lower expert id)
+#pragma unroll 1
+  for (int j = 0; j < p.k; ++j) {
+    const float m = lane_max(), best = row_max(m);
+    bool holds = m == best;
+    if (__any(!(best > NEG))) {  // no live expert left in some row: of absent experts, NaN are not equal to -inf
+      holds = false;
+#pragma unroll
+      for (int i = 0; i < V; ++i) holds = holds || key[i] == best;
+    }
+    const uint32_t holders = static_cast<uint32_t>(__ballot(holds) >> (row * 16)) & 0xFFFFu;
+    const bool winner = li == (holders ? __builtin_ctz(holders) : 0);
+    int at = V;  // the winner's lowest place of the key
+#pragma unroll
+    for (int i = 0; i < V; ++i) at = min(at, key[i] == best ? i : V);
+    at = winner ? at : V;
+#pragma unroll
+    for (int i = 0; i < V; ++i) key[i] = i == at ? NEG : key[i];
+    if (winner) chosen[wave][row][j] = {min(e0 + at % V, p.E - 1), best};  // V: a row of NaN holds no best key
+  }
+  __builtin_amdgcn_wave_barrier();  // the wavefront's own LDS accesses are in order
+
+  // weights: score of the chosen expert over the sum of the chosen scores, added as in the kernel above
+  Choice c = {0, 0.f};
+  if (li < p.k) c = chosen[wave][row][li];
+  const int count = p.l2p_count[c.e];
+  const double s = li < p.k ? score64(c.z) : 0.0;
+  double sum = s + dpp_f64<0x128>(s);  // lanes 8 apart
+  sum += dpp_f64<0x124>(sum);          // 4 apart: lanes 8 apart are equal by now
+  sum += dpp_f64<0x4E>(sum);
+  sum += dpp_f64<0xB1>(sum);
+  if (li < p.k && t < p.T) {
+    const int64_t o = static_cast<int64_t>(t) * p.k + li;
+    p.topk_logical[o] = c.e;
+    p.topk_weight[o] = static_cast<float>(s / sum * static_cast<double>(p.route_scale));
+    p.topk_phys[o] = replica(p, t, c.e, count);
   }
 }
 
@@ -481,16 +620,40 @@ int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk
   p.route_scale = c.route_scale;
   p.t_offset = ctx->token_offset;
   KernelTimer timer(ctx, REVIVE_K_ROUTE_TOPK, stream);
-  // Four tokens to a wavefront do less work in all but take longer one by one: E = 256, 8 groups, k = 8, with the
-  // counts and launches around it, 4096 tokens 17.0 us (one) and 17.9 (four), 8192: 21.2 and 21.1, 32768: 58 and 51
-  // (shuffles through LDS, one token: 22.0, 32.5, 94).
+  const int n = ceil_div(c.E, 16);
+  const bool rows = c.k <= 16 && (c.n_group == 1 || (c.E % 16 == 0 && (c.n_group == 2 || c.n_group == 4 || c.n_group == 8)));
+  // A row of 16 lanes per token does a quarter of the work, but its lanes have four times as many experts to go through
+  // one after the other.  us (kernel trace), a wavefront per token and a row per token: E = 256, 8 groups, k = 8, 1003
+  // tokens 7.3 and 7.6, 2048 8.1 and 7.7, 8192 16.8 and 9.3, 32 768 44 and 22; E = 384, one group, 1003 6.1 and 6.8, 2048
+  // 6.7 and 6.9, 8192 12.8 and 10.2; E = 512, 2048 11.1 and 11.1, 8192 24.0 and 14.9; E = 192, k = 2, 64 tokens 6.1 and
+  // 4.2; E = 64, k = 6, 1 token 2.4 and 2.8, 64 3.9 and 3.5, 256 4.1 and 4.2, 8192 8.1 and 4.8.
+  if (rows && T > (n <= 12 ? 16 : 2048)) {
+    const dim3 grid(ceil_div(T, 16)), block(256);
+    const bool wide = c.E % 64 == 0;
+#define REVIVE_ROUTE_LAUNCH(V)                                                                                                      \
+  do {                                                                                                                              \
+    if (c.n_group > 1 && wide) hipLaunchKernelGGL((route_topk_rows_kernel<V, true, true>), grid, block, 0, stream, p);              \
+    else if (c.n_group > 1) hipLaunchKernelGGL((route_topk_rows_kernel<V, true, false>), grid, block, 0, stream, p);                \
+    else if (wide) hipLaunchKernelGGL((route_topk_rows_kernel<V, false, true>), grid, block, 0, stream, p);                         \
+    else hipLaunchKernelGGL((route_topk_rows_kernel<V, false, false>), grid, block, 0, stream, p);                                  \
+  } while (0)
+    if (n <= 4) REVIVE_ROUTE_LAUNCH(4);
+    else if (n <= 8) REVIVE_ROUTE_LAUNCH(8);
+    else if (n <= 16) REVIVE_ROUTE_LAUNCH(16);
+    else if (n <= 24) REVIVE_ROUTE_LAUNCH(24);
+    else REVIVE_ROUTE_LAUNCH(32);
+#undef REVIVE_ROUTE_LAUNCH
+    return check_hip(ctx, hipGetLastError(), "route_topk launch");
+  }
+  // Few tokens, other groups, more choices.  Four tokens to a wavefront do less work in all but take longer one by one:
+  // E = 256, 8 groups, k = 8, with the counts and launches around it, 4096 tokens 17.0 us (one) and 17.9 (four), 8192:
+  // 21.2 and 21.1, 32768: 58 and 51.
   const bool four = T > 8192 && c.k <= 16 && c.n_group <= 8;
   const dim3 grid(ceil_div(T, four ? 16 : 4)), block(256);
   const int vals = ceil_div(c.E, 64);
 #define REVIVE_ROUTE_LAUNCH(V)                                                                                       \
   do {                                                                                                               \
-    if (four && c.n_group > 1) hipLaunchKernelGGL((route_topk_kernel<V, 4, true>), grid, block, 0, stream, p);       \
-    else if (four) hipLaunchKernelGGL((route_topk_kernel<V, 4, false>), grid, block, 0, stream, p);                  \
+    if (four) hipLaunchKernelGGL((route_topk_kernel<V, 4, true>), grid, block, 0, stream, p);                        \
     else if (c.n_group > 1) hipLaunchKernelGGL((route_topk_kernel<V, 1, true>), grid, block, 0, stream, p);          \
     else hipLaunchKernelGGL((route_topk_kernel<V, 1, false>), grid, block, 0, stream, p);                            \
   } while (0)

@@ -43,6 +43,16 @@ def test_topk(E, n_group, topk_group, k, score_fn, T):
     L.close()
 
 
+# 16 lanes per token: as many experts per lane as a form of the kernel holds, one more and fewer, experts that are no
+# multiple of 4 or of 16, groups of 2, 4 and 8 lanes, one choice and sixteen; both sides of the limits in tokens
+@pytest.mark.parametrize("T", [16, 17, 19, 2048, 2049])
+@pytest.mark.parametrize("E,n_group,topk_group,k", [(2, 1, 1, 1), (30, 1, 1, 16), (80, 1, 1, 4), (112, 1, 1, 8), (144, 1, 1, 8), (192, 1, 1, 6),
+                                                    (48, 2, 1, 8), (48, 4, 2, 3), (48, 8, 3, 2), (128, 4, 1, 16), (208, 2, 1, 16),
+                                                    (256, 8, 4, 8), (320, 4, 3, 7), (400, 1, 1, 2), (512, 2, 2, 16), (511, 1, 1, 5)])
+def test_a_row_of_lanes_per_token(E, n_group, topk_group, k, T):
+    test_topk(E, n_group, topk_group, k, "sigmoid" if k % 2 else "softmax", T)
+
+
 # A logit that is not a number belongs to no order: its expert counts as absent, in the scores of its group too.
 @pytest.mark.parametrize("T", [301, 8193])
 @pytest.mark.parametrize("score_fn", ["softmax", "sigmoid"])
