@@ -10,11 +10,16 @@
 // K-elements of its row and feed four MFMAs (both operands permute K alike).  The matrix cores are what
 // bounds a full tile (16 MFMAs of 32 cycles per 16 K-elements and wavefront against 160 to 192 cycles of
 // LDS for the whole workgroup); a tile of few rows is bound by latency.  D = 4 was 5 % slower on full tiles
-// (224 registers, one workgroup per CU less) and no faster on the others.
+// (224 registers, one workgroup per CU less) and no faster on the others; loads issued a step earlier gained nothing.
+// Vector instructions between the MFMAs cost as well: a thread keeps 32-bit offsets from wavefront-uniform bases and
+// LDS addresses that are the same in every step, and copies only as many rows as the tile has sub-tiles.  Routed and
+// shared expert, H = 1024, I = 512, 32 experts, k = 4: 200 tokens 91 -> 82 us, 1001 tokens 199 -> 184, 4000 tokens
+// 580 -> 557 (113 TFLOP/s).  What is left at 1001 tokens is balance: a CU's three workgroups hold 7 to 13 sub-tiles.
+// Narrower workgroups spread better and lose more by reading the activations twice as often (1001 tokens 195 us; of
+// two wavefronts, 239, since they load the SIMDs unevenly).
 //
-// Against the vector-FMA kernel that stood here (64 x 64 tiles, no load ahead of its use): gate/up and down
-// of routed and shared expert, H = 1024, I = 512, 32 experts, k = 4: 1 token 288 -> 45 us, 1001 tokens
-// 408 -> 204 us, 4000 tokens 920 -> 589 us (42 GFLOP of gate/up in 386 us: 109 TFLOP/s of 157).
+// Against the vector-FMA kernel that stood here (64 x 64 tiles, no load ahead of its use): the same
+// layer, 1 token 288 -> 45 us, 1001 tokens 408 -> 204 us, 4000 tokens 920 -> 589 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -51,11 +56,15 @@ struct GemmF32Args {
 constexpr int kTileN_f32 = 64;
 
 // SLICES > 1: the K-steps are summed in SLICES parts that are added in their order (see router_tile_kernel).
-template <bool SWIGLU, int D, int SLICES = 1>
+// Off: bytes between the first of a tile's 64 rows and any element of them.
+template <bool SWIGLU, int D, int SLICES, typename Off>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
+  // Known to address HBM: global loads.  A pointer out of the weight table made flat ones, which every LDS wait drains.
+  typedef const __attribute__((address_space(1))) unsigned char* gptr;
+  typedef const __attribute__((address_space(1))) f32x4* gptr_f32x4;
   constexpr int BM = kTileM_f32, BN = kTileN_f32, W = SWIGLU ? 2 : 1;
-  constexpr int NA = BM * 8 / 256, NB = W * BN * 8 / 256;  // 16-byte words per thread and K-step
+  constexpr int NB = W * BN * 8 / 256;  // 16-byte words of weights per thread and K-step
   static_assert(D % 2 == 0, "the LDS buffer of a step is its position in the register ring modulo 2");
   __shared__ __attribute__((aligned(16))) unsigned char lds[2][(BM + W * BN) * 128];
   const bool dense = blockIdx.x < static_cast<unsigned>(a.dense.blocks);
@@ -80,36 +89,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
   const int n0 = n_idx * BN, rows = row_end - row_begin;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // 16 rows further on the swizzle is the same
   auto swizzle = [](int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); };
 
-  // copy plan: 16-byte word w of a step is K-chunk w % 8 of row w / 8
-  const int c = tid & 7;
-  const float* a_src[NA];
-  const float* b_src[NB];
-#pragma unroll
-  for (int i = 0; i < NA; ++i)  // rows past the tile read its last row again
-    a_src[i] = g.A + static_cast<int64_t>(row_begin + min(i * 32 + (tid >> 3), rows - 1)) * g.lda;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int r = i * 32 + (tid >> 3);
-    b_src[i] = B + static_cast<int64_t>(min(n0 + r % BN, g.n_out - 1) + r / BN * g.n_out) * g.ldb;
-  }
-  f32x4 af[D][NA], bf[D][NB];
-  auto load = [&](int kt, int d) {  // past the last K-element: the last four again, zeroed when staged
-    const int k = kt * 32 + c * 4, kc = min(k, g.K - 4);
-#pragma unroll
-    for (int i = 0; i < NA; ++i) af[d][i] = *reinterpret_cast<const f32x4*>(a_src[i] + kc);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) bf[d][i] = *reinterpret_cast<const f32x4*>(b_src[i] + kc);
-  };
-  auto stage = [&](int kt, int d, int buf) {
-    const bool in = kt * 32 + c * 4 < g.K;
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < NA; ++i) *reinterpret_cast<f32x4*>(lds[buf] + swizzle(i * 32 + (tid >> 3), c)) = in ? af[d][i] : zero;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x4*>(lds[buf] + BM * 128 + swizzle(i * 32 + (tid >> 3), c)) = in ? bf[d][i] : zero;
-  };
   auto publish = [&]() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -118,8 +100,36 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
 
   const int KT = (g.K + 31) >> 5;
   const int r16 = lane & 15, quad = lane >> 4;
+  const int get[2] = {swizzle(r16, quad), swizzle(r16, 4 + quad)};
+  auto base = [](const float* p) { return reinterpret_cast<gptr>(reinterpret_cast<uintptr_t>(p)); };
+  const gptr a_base = base(g.A + static_cast<int64_t>(row_begin) * g.lda);
+  const gptr b_base[2] = {base(B + n0 * g.ldb), base(B + (static_cast<int64_t>(n0) + g.n_out) * g.ldb)};
   auto run = [&](auto tm_tag) {
     constexpr int TM = decltype(tm_tag)::value;
+    // copy plan: 16-byte word w of a step is K-chunk w % 8 of row w / 8
+    constexpr int NA = (TM + 1) / 2;  // words of activations per thread and K-step: no more rows than the tile's sub-tiles hold
+    const int c = tid & 7, r0 = tid >> 3, put = swizzle(r0, c);
+    Off a_off[NA], b_off[BN / 32];  // bytes from the uniform bases
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a_off[i] = static_cast<Off>(min(i * 32 + r0, rows - 1)) * static_cast<Off>(g.lda * 4);  // rows past the tile read its last row again
+#pragma unroll
+    for (int i = 0; i < BN / 32; ++i) b_off[i] = static_cast<Off>(min(i * 32 + r0, g.n_out - 1 - n0)) * static_cast<Off>(g.ldb * 4);
+    f32x4 af[D][NA], bf[D][NB];
+    auto load = [&](int kt, int d) {  // past the last K-element: the last four again, zeroed when staged
+      const Off k = static_cast<Off>(min(kt * 32 + c * 4, g.K - 4)) * 4;
+#pragma unroll
+      for (int i = 0; i < NA; ++i) af[d][i] = *reinterpret_cast<gptr_f32x4>(a_base + (a_off[i] + k));
+#pragma unroll
+      for (int i = 0; i < NB; ++i) bf[d][i] = *reinterpret_cast<gptr_f32x4>(b_base[i / (BN / 32)] + (b_off[i % (BN / 32)] + k));
+    };
+    auto stage = [&](int kt, int d, int buf) {
+      const bool in = kt * 32 + c * 4 < g.K;
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NA; ++i) *reinterpret_cast<f32x4*>(lds[buf] + put + i * (32 * 128)) = in ? af[d][i] : zero;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) *reinterpret_cast<f32x4*>(lds[buf] + BM * 128 + put + i * (32 * 128)) = in ? bf[d][i] : zero;
+    };
     f32x4 acc[W][TM];
 #pragma unroll
     for (int s = 0; s < W; ++s)
@@ -151,9 +161,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
       for (int h = 0; h < 2; ++h) {
         f32x4 x[TM], w[W];
 #pragma unroll
-        for (int s = 0; s < W; ++s) w[s] = *reinterpret_cast<const f32x4*>(lds[buf] + BM * 128 + swizzle(s * BN + wave * 16 + r16, h * 4 + quad));
+        for (int s = 0; s < W; ++s) w[s] = *reinterpret_cast<const f32x4*>(lds[buf] + BM * 128 + get[h] + (wave * 16 + s * BN) * 128);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) x[i] = *reinterpret_cast<const f32x4*>(lds[buf] + swizzle(i * 16 + r16, h * 4 + quad));
+        for (int i = 0; i < TM; ++i) x[i] = *reinterpret_cast<const f32x4*>(lds[buf] + get[h] + i * (16 * 128));
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -220,7 +230,10 @@ template <bool SWIGLU, int SLICES = 1>
 int launch_gemm_f32(revive_ctx* ctx, const GemmF32Args& args, hipStream_t stream) {
   const int grid = args.dense.blocks + args.grouped.blocks;
   if (grid <= 0) return REVIVE_OK;
-  hipLaunchKernelGGL((gemm_f32_kernel<SWIGLU, 2, SLICES>), dim3(grid), dim3(256), 0, stream, args);
+  constexpr int64_t kNarrow = 1 << 24;  // 64 rows of as many floats are 4 GiB
+  const bool narrow = args.dense.lda < kNarrow && args.grouped.lda < kNarrow;  // ldb = lda
+  const auto kernel = narrow ? gemm_f32_kernel<SWIGLU, 2, SLICES, uint32_t> : gemm_f32_kernel<SWIGLU, 2, SLICES, uint64_t>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, args);
   return check_hip(ctx, hipGetLastError(), "gemm_f32 launch");
 }
 

@@ -195,3 +195,30 @@ def test_limits_of_the_streaming_kernel(P, H, I, I_shared, N, streamed):
         assert torch.equal(y_sh, L.shared_ffn(x, gu_sh, dn_sh, N))
         assert rel_err(f64(y_sh[:64]), _reference(x[:64].float().cpu(), w_sh).double().numpy()) < TOL["bf16"]
     L.close()
+
+
+def test_fp32_rows_of_64_mib():
+    """Tiles whose 64 rows reach 4 GiB and further take 64-bit offsets.  x holds four elements of a row, so that every sum
+    has four products and 1e-5 is fp32's error; they lie at the ends and in the middle."""
+    H, I, counts = 1 << 24, 4, [64, 0, 17]
+    N, at = sum(counts), torch.tensor([0, 5, (1 << 23) + 3, (1 << 24) - 1], device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    cfg = SimpleNamespace(T=N, H=H, E=3, k=1, I=I, I_shared=0, n_ranks=3, slots_per_rank=1, max_replicas=2, score_fn="softmax",
+                          n_group=1, topk_group=1, dtype="fp32")
+    L = ReviveLayer(cfg)
+    weights = [(torch.randn(2 * I, H, generator=gen, device="cuda"), torch.randn(H, I, generator=gen, device="cuda")) if c else (None, None)
+               for c in counts]
+    L.set_expert_weights([w[0] for w in weights], [w[1] for w in weights])
+    x = torch.zeros(N, H, device="cuda")
+    x[:, at] = torch.randn(N, len(at), generator=gen, device="cuda")
+    y = L.empty(N, H).fill_(float("nan"))
+    off = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    L.expert_ffn(x, off, N, out=(y, None))
+    torch.cuda.synchronize()
+    for p, c in enumerate(counts):
+        rows = slice(int(off[p]), int(off[p]) + c)
+        if not c:
+            continue
+        h = x[rows][:, at] @ weights[p][0][:, at].T
+        ref = (torch.nn.functional.silu(h[:, :I]) * h[:, I:]) @ weights[p][1].T
+        assert float((y[rows] - ref).abs().max() / ref.abs().max()) < 1e-5
