@@ -34,6 +34,15 @@ __device__ __forceinline__ u32x4 load_global_16B(const unsigned char* p) {
   return *reinterpret_cast<gptr_u32x4>(reinterpret_cast<uintptr_t>(p));
 }
 
+// Asynchronous copy of 16 bytes per lane to LDS: lane l's from src + off to dst + 16 l (dst and src wavefront-uniform).
+// Inline assembly on purpose: the compiler's wait-count bookkeeping treats a global_load_lds it knows about as "may touch
+// both memory and LDS" and from then on turns every LDS wait into a full drain, which would undo a software pipeline.
+// Issued this way the copies are invisible to that bookkeeping and have to be waited for explicitly before the barrier
+// that publishes them.  So is the wait state that the hardware needs between a write of M0 and the copy that uses it.
+__device__ __forceinline__ void copy_to_lds_16B(uint32_t dst, uint64_t src, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src), "s"(dst) : "memory", "m0");
+}
+
 enum { EPI_BF16 = 1, EPI_SWIGLU = 2 };
 
 // Tiled weight layout: a [rows, K] output-major matrix is stored as [rows/128][K/32][128][32]
@@ -282,10 +291,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
       cp_dst[i] = BM * 64 + blk * 1024;
     }
   }
-  // The copy is written as inline assembly on purpose: the compiler's wait-count bookkeeping treats
-  // a global_load_lds it knows about as "may touch both memory and LDS" and from then on turns
-  // every LDS wait into a full drain, which would undo the software pipeline.  Issued this way the
-  // copies are invisible to that bookkeeping and are waited for explicitly before each barrier.
   const uint32_t smem_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)smem));
   auto uniform64 = [](uint64_t v) {
     // the builtin returns a signed int: widen both halves as unsigned
@@ -304,9 +309,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
 #pragma unroll
     for (int i = 0; i < decltype(cp_tag)::value; ++i) {
       const uint32_t dst = __builtin_amdgcn_readfirstlane(stage + cp_dst[i]);
-      const uint32_t off = cp_off[i];
-      const uint64_t src = i < CP_B ? src_b : src_a;
-      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src), "s"(dst) : "memory", "m0");
+      copy_to_lds_16B(dst, i < CP_B ? src_b : src_a, cp_off[i]);
     }
   };
 
@@ -318,9 +321,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
 #pragma unroll
     for (int i = 0; i < decltype(cp_tag)::value; ++i) {
       const uint32_t dst = __builtin_amdgcn_readfirstlane(smem_lds + cp_dst[i] + PH * STAGE);
-      const uint32_t off = cp_off[i];
-      const uint64_t src = i < CP_B ? src_b : src_a;
-      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src), "s"(dst) : "memory", "m0");
+      copy_to_lds_16B(dst, i < CP_B ? src_b : src_a, cp_off[i]);
     }
   };
   using Cp = std::integral_constant<int, CP>;

@@ -136,8 +136,7 @@ __global__ __launch_bounds__(64 * WM * WN) void router_tile_kernel(const uint16_
   // H is a multiple of 64 and not below BK.  A last step that K does not fill takes K's last BK elements, of which
   // only the second half is new.
   const int KT = (H + BK - 1) / BK;
-  // Written as inline assembly, with explicit waits, as in gemm_bf16_dma_kernel.  Past the last step the last one is
-  // copied again (not multiplied), so that the count of copies in flight stays exact.
+  // Past the last step the last one is copied again (not multiplied), so that the count of copies in flight stays exact.
   auto issue_copy = [&](int kt) {
     const uint32_t stage = smem_lds + kt % S * STAGE;
     const uint64_t k = min(static_cast<uint32_t>(kt) * ROWB, row_bytes - ROWB);
@@ -146,8 +145,7 @@ __global__ __launch_bounds__(64 * WM * WN) void router_tile_kernel(const uint16_
       const int blk = i * NW + wave;
       const uint64_t src = (blk * RPC < BM ? base_x : base_w) + k;
       const uint32_t dst = __builtin_amdgcn_readfirstlane(stage + blk * 1024);
-      const uint32_t off = cp_off[i];
-      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(src), "s"(dst) : "memory", "m0");
+      copy_to_lds_16B(dst, src, cp_off[i]);
     }
   };
   f32x4 acc[TM][TN], sum[TM][TN];  // sum: the finished slices
