@@ -298,9 +298,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
     return (static_cast<uint64_t>(hi) << 32) | lo;
   };
-  const uint64_t base_a = uniform64(reinterpret_cast<uint64_t>(Abase) + static_cast<uint64_t>(row_begin) * (g.a_rows > 0 ? 32 : g.lda) * 2);
+  uint64_t base_a = uniform64(reinterpret_cast<uint64_t>(Abase) + static_cast<uint64_t>(row_begin) * (g.a_rows > 0 ? 32 : g.lda) * 2);
   const uint64_t kstep_a = g.a_rows > 0 ? static_cast<uint64_t>(g.a_rows) * 64 : 64;
-  const uint64_t base_b = uniform64(reinterpret_cast<uint64_t>(Bbase));
+  uint64_t base_b = uniform64(reinterpret_cast<uint64_t>(Bbase));
+  // Five wait states before a copy may read a scalar register that a vector instruction wrote.
+  asm volatile("s_nop 4" : "+s"(base_a), "+s"(base_b));
   const uint32_t kstep_b = g.b_tiled ? kWeightTileRows * kWeightTileK * 2 : 64;  // bytes between K-steps of B
   auto issue_copy = [&](int kt, auto cp_tag) {
     const uint32_t stage = smem_lds + stage_of(kt) * STAGE;
