@@ -37,11 +37,14 @@ __host__ __device__ inline int tiles_of(int rows, int tile_m, int tall_m) {
   return rows <= 0 ? 0 : rows <= tall_m ? 1 : (rows + tile_m - 1) / tile_m;
 }
 
-// Rows [row_begin, row_end) of tile j of a group with rows [begin, end) cut into G tiles (tiles_of): all of the same
-// height, in whole 16-row sub-tiles.  They then take equally long, and the workgroups that read the same weights stay
-// near one another, so that L2 fetches them once; a tile of a few rows would stream the whole weight matrix for almost
-// no work, out of step with its neighbours.  Down projection, 414 slots of 640 to 740 rows, K = 2048: 6.88 -> 6.73 ms
-// against tiles of 256 rows with the rest cut in two; 63 slots of 350 to 430 rows 150 -> 148 us.
+// Rows [row_begin, row_end) of tile j of a group with rows [begin, end) cut into G tiles (tiles_of): all of one height, in
+// whole 16-row sub-tiles, but the last, which has what is left.  Tiles of one height take equally long, and the workgroups
+// that read the same weights stay near one another, so that L2 fetches them once.  Down projection, 414 slots of 640 to
+// 740 rows, K = 2048: 6.88 -> 6.73 ms against tiles of 256 rows with the rest cut in two; 63 slots of 350 to 430 rows 150
+// -> 148 us.  With many tiles the rounding up leaves the last one up to 15 G rows fewer (4097 rows: 16 tiles of 256 and
+// one of 1).  That is the better way of cutting all the same, since full tiles do most per copied byte: FFN, H = 7168,
+// I = 2048, us, against sub-tiles dealt out so that two tiles differ by one at most: 8 slots of 4097 rows 2364 and 2403,
+// 8 of 3601 2086 and 2107, 16 of 2305 2570 and 2591, 3 of 8200 1684 and 1726.
 // No tile is empty: a tile's height is at most tile_m, and rows > (G - 1) * tile_m for G > 1.
 __host__ __device__ inline void tile_span(int begin, int end, int G, int j, int& row_begin, int& row_end) {
   const int each = ((end - begin + G - 1) / G + 15) & ~15;

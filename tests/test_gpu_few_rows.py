@@ -28,6 +28,8 @@ CASES = {
     "tall_many_short_k": (64, 64, TALL * 12), "tall_many": (192, 320, TALL * 12), "tall_wide": (2880, 1472, TALL),
     # every number of 16-row sub-tiles that a wavefront may have, full and by one row, and slots of several row-tiles
     "sub_tiles": (256, 192, SUB_TILES), "sub_tiles_tall": (1088, 448, SUB_TILES),
+    # slots of many row-tiles, which a common height would leave with a row or a sub-tile in the last; the same streamed
+    "many_tiles": (256, 192, [4097, 3601, 513, 0, 1]), "many_tiles_streamed": (704, 320, [4097, 1041] + [0] * 330),
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
