@@ -7,6 +7,7 @@
 #include <algorithm>
 
 #include "gemm_f32.hpp"
+#include "route_rules.hpp"
 #include "router_sequence.hpp"
 
 namespace revive {
@@ -57,10 +58,12 @@ __device__ __forceinline__ void top2_step(float& m1, float& m2) {
 }
 
 template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {  // v of another lane
+__device__ __forceinline__ int dpp_int(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, false); }  // v of another lane
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
   const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xF, 0xF, false);
+  const int lo = dpp_int<CTRL>(static_cast<int>(b)), hi = dpp_int<CTRL>(static_cast<int>(b >> 32));
   return __longlong_as_double(static_cast<long long>(hi) << 32 | static_cast<uint32_t>(lo));
 }
 
@@ -238,10 +241,13 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
 }
 
 // The same selection with 16 lanes, one DPP row, per token: four tokens to a wavefront, every instruction for all four.
-// Lane l of a row holds experts [l n, (l + 1) n), n = ceil(E / 16) <= V.  Groups are then whole runs of 16 / n_group
-// lanes (n_group a power of two up to 8, E a multiple of 16), a reduction is four steps instead of six, and ties go to
-// the lower lane and the lower place in it.  The kernel above gives a token 64 lanes and works on one after the other; it
-// is bound by the ALU from a few thousand tokens on (launch_route_topk has the figures).  WIDE: E is a multiple of 64, logits come in 16-byte words.
+// A group of experts (all of them in a layer without groups) is a run of lg = 16 / n_group lanes (n_group a power of two
+// up to 8, E a multiple of 16), and a lane holds n = ceil(E / 16) <= V of its experts, dealt so that the run's loads are
+// contiguous: lane j of the run holds the group's experts j, j + lg, ..., or with WIDE (E a multiple of 64, 16-byte loads)
+// its words of four j, j + lg, ...  A reduction is four steps instead of six, and ties go to the lowest expert id.  The
+// kernel above gives a token 64 lanes and works on one after the other; it is bound by the ALU from a few thousand
+// tokens on (selects_by_rows has the figures).  With a lane's experts side by side instead each load touched four times
+// as many lines and more: 65 536 tokens, one choice, 512 experts 52 us (27 as it is), 500 experts 320 (23).
 template <int V, bool GROUPED, bool WIDE>
 __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
   static_assert(!WIDE || V % 4 == 0, "16-byte loads");
@@ -250,8 +256,11 @@ __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane >> 4, li = lane & 15;
   const int t0 = (blockIdx.x * 4 + wave) * 4, t = t0 + row;
   if (t0 >= p.T) return;  // whole wavefront leaves together
-  const float NEG = -__builtin_inff();
-  const int n = (p.E + 15) >> 4, e0 = li * n;
+  const float NEG = -__builtin_inff(), NONE = __builtin_nanf("");  // NONE: no expert in this place, equal to no key
+  const int n = (p.E + 15) >> 4;
+  const int lg = GROUPED ? 16 / p.n_group : 16, lj = li & (lg - 1);  // lanes of a group, this one's place among them
+  const int e0 = GROUPED ? li / lg * (p.E / p.n_group) : 0;          // the group's first expert
+  auto expert = [&](int i) { return e0 + (WIDE ? (i >> 2) * 4 * lg + lj * 4 + (i & 3) : i * lg + lj); };  // place i
   const float* z = p.logits + static_cast<int64_t>(min(t, p.T - 1)) * p.E;
 
   float key[V];
@@ -259,21 +268,21 @@ __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
 #pragma unroll
     for (int i = 0; i < V; i += 4) {
       if (i < n) {  // n is a multiple of 4
-        const f32x4 v = *reinterpret_cast<const f32x4*>(z + e0 + i);
-        const int4 c = *reinterpret_cast<const int4*>(p.l2p_count + e0 + i);
+        const f32x4 v = *reinterpret_cast<const f32x4*>(z + expert(i));
+        const int4 c = *reinterpret_cast<const int4*>(p.l2p_count + expert(i));
         key[i] = c.x > 0 ? v[0] : NEG; key[i + 1] = c.y > 0 ? v[1] : NEG;  // failure mask
         key[i + 2] = c.z > 0 ? v[2] : NEG; key[i + 3] = c.w > 0 ? v[3] : NEG;
       } else {
-        key[i] = key[i + 1] = key[i + 2] = key[i + 3] = NEG;
+        key[i] = key[i + 1] = key[i + 2] = key[i + 3] = NONE;
       }
     }
   } else {
 #pragma unroll
     for (int i = 0; i < V; ++i) {
-      const int e = min(e0 + i, p.E - 1);
+      const int e = min(expert(i), p.E - 1);
       const float v = z[e];
       const int c = p.l2p_count[e];
-      key[i] = i < n && e0 + i < p.E && c > 0 ? v : NEG;
+      key[i] = i < n && expert(i) < p.E ? c > 0 ? v : NEG : NONE;
     }
   }
   auto lane_max = [&]() {
@@ -298,7 +307,6 @@ __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
   if (GROUPED) {
     // Group score = sum of the two best live scores of the group (one if only one is live, -inf if none).  A NaN does
     // not enter the pairs (see above).
-    const int lg = 16 / p.n_group;  // lanes of a group: 2, 4 or 8
     float m1 = NEG, m2 = NEG;
 #pragma unroll
     for (int i = 0; i < V; ++i) {
@@ -318,9 +326,9 @@ __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
     double o = gs;
     int h = li;
     for (int r = 1; r < p.n_group; ++r) {
-      if (lg == 2) { o = dpp_f64<0x122>(o); h = __builtin_amdgcn_mov_dpp(h, 0x122, 0xF, 0xF, false); }       // rotate the row by a group
-      else if (lg == 4) { o = dpp_f64<0x124>(o); h = __builtin_amdgcn_mov_dpp(h, 0x124, 0xF, 0xF, false); }
-      else { o = dpp_f64<0x128>(o); h = __builtin_amdgcn_mov_dpp(h, 0x128, 0xF, 0xF, false); }
+      if (lg == 2) { o = dpp_f64<0x122>(o); h = dpp_int<0x122>(h); }       // rotate the row by a group
+      else if (lg == 4) { o = dpp_f64<0x124>(o); h = dpp_int<0x124>(h); }
+      else { o = dpp_f64<0x128>(o); h = dpp_int<0x128>(h); }
       rank += (o > gs) || (o == gs && h < li);
     }
     const bool kept = rank < p.topk_group;
@@ -329,24 +337,29 @@ __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
   }
 
   // k rounds of arg-max (largest key, ties to the lower expert id)
+  constexpr int kNone = 1 << 16;
+  auto row_min = [&](int v) {
+    v = min(v, dpp_int<0xB1>(v));   // lanes 1 apart
+    v = min(v, dpp_int<0x4E>(v));   // 2 apart
+    v = min(v, dpp_int<0x124>(v));  // 4 apart: lanes of four are equal by now
+    return min(v, dpp_int<0x128>(v));
+  };
 #pragma unroll 1
   for (int j = 0; j < p.k; ++j) {
-    const float m = lane_max(), best = row_max(m);
-    bool holds = m == best;
-    if (__any(!(best > NEG))) {  // no live expert left in some row: of absent experts, NaN are not equal to -inf
-      holds = false;
+    const float best = row_max(lane_max());
+    int at = V;  // the lowest place of the key in this lane; four short chains of minima
+    {
+      int part[4] = {V, V, V, V};
 #pragma unroll
-      for (int i = 0; i < V; ++i) holds = holds || key[i] == best;
+      for (int i = 0; i < V; ++i) part[i & 3] = min(part[i & 3], key[i] == best ? i : V);
+      at = min(min(part[0], part[1]), min(part[2], part[3]));
     }
-    const uint32_t holders = static_cast<uint32_t>(__ballot(holds) >> (row * 16)) & 0xFFFFu;
-    const bool winner = li == (holders ? __builtin_ctz(holders) : 0);
-    int at = V;  // the winner's lowest place of the key
-#pragma unroll
-    for (int i = 0; i < V; ++i) at = min(at, key[i] == best ? i : V);
-    at = winner ? at : V;
+    const int mine = at < V ? expert(at) : kNone, e = row_min(mine);
+    // No key is the best one in a row of NaN: its ids stay valid.
+    if (mine == e) chosen[wave][row][j] = {min(e, p.E - 1), best};
+    at = mine == e ? at : V;
 #pragma unroll
     for (int i = 0; i < V; ++i) key[i] = i == at ? NEG : key[i];
-    if (winner) chosen[wave][row][j] = {min(e0 + at % V, p.E - 1), best};  // V: a row of NaN holds no best key
   }
   __builtin_amdgcn_wave_barrier();  // the wavefront's own LDS accesses are in order
 
@@ -620,14 +633,8 @@ int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk
   p.route_scale = c.route_scale;
   p.t_offset = ctx->token_offset;
   KernelTimer timer(ctx, REVIVE_K_ROUTE_TOPK, stream);
-  const int n = ceil_div(c.E, 16);
-  const bool rows = c.k <= 16 && (c.n_group == 1 || (c.E % 16 == 0 && (c.n_group == 2 || c.n_group == 4 || c.n_group == 8)));
-  // A row of 16 lanes per token does a quarter of the work, but its lanes have four times as many experts to go through
-  // one after the other.  us (kernel trace), a wavefront per token and a row per token: E = 256, 8 groups, k = 8, 1003
-  // tokens 7.3 and 7.6, 2048 8.1 and 7.7, 8192 16.8 and 9.3, 32 768 44 and 22; E = 384, one group, 1003 6.1 and 6.8, 2048
-  // 6.7 and 6.9, 8192 12.8 and 10.2; E = 512, 2048 11.1 and 11.1, 8192 24.0 and 14.9; E = 192, k = 2, 64 tokens 6.1 and
-  // 4.2; E = 64, k = 6, 1 token 2.4 and 2.8, 64 3.9 and 3.5, 256 4.1 and 4.2, 8192 8.1 and 4.8.
-  if (rows && T > (n <= 12 ? 16 : 2048)) {
+  if (selects_by_rows(T, c.E, c.n_group, c.k)) {
+    const int n = ceil_div(c.E, 16);
     const dim3 grid(ceil_div(T, 16)), block(256);
     const bool wide = c.E % 64 == 0;
 #define REVIVE_ROUTE_LAUNCH(V)                                                                                                      \

@@ -53,6 +53,21 @@ def test_a_row_of_lanes_per_token(E, n_group, topk_group, k, T):
     test_topk(E, n_group, topk_group, k, "sigmoid" if k % 2 else "softmax", T)
 
 
+# the same from the token counts on at which layers without groups, and wide ones with few lanes per load, take this kernel
+@pytest.mark.parametrize("T", [2560, 4099])
+@pytest.mark.parametrize("E,n_group,topk_group,k", [(2, 1, 1, 1), (30, 1, 1, 16), (80, 1, 1, 4), (112, 1, 1, 8), (130, 1, 1, 2), (144, 1, 1, 8),
+                                                    (192, 1, 1, 6), (300, 1, 1, 8), (400, 2, 1, 8), (448, 1, 1, 16), (500, 1, 1, 1),
+                                                    (511, 1, 1, 5), (512, 1, 1, 1), (512, 2, 2, 16)])
+def test_a_row_of_lanes_per_token_many_tokens(E, n_group, topk_group, k, T):
+    test_topk(E, n_group, topk_group, k, "softmax" if k % 2 else "sigmoid", T)
+
+
+# places of a lane that hold no expert are never chosen, not even where all the token's logits are NaN
+@pytest.mark.parametrize("E,n_group,k", [(48, 1, 8), (48, 2, 8), (400, 4, 16), (500, 1, 8), (511, 1, 16)])
+def test_row_of_nan_with_a_row_of_lanes(E, n_group, k):
+    test_row_of_nan_keeps_valid_ids(E, n_group, k, 8193)
+
+
 # A logit that is not a number belongs to no order: its expert counts as absent, in the scores of its group too.
 @pytest.mark.parametrize("T", [301, 8193])
 @pytest.mark.parametrize("score_fn", ["softmax", "sigmoid"])

@@ -1,0 +1,61 @@
+"""The rules that choose the gate's kernels (csrc/route_rules.hpp), built by a plain C++ compiler, against times that were
+measured on both sides of their lines."""
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2602_21140_amd import build
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
+
+DRIVER = """
+#include <iostream>
+#include <string>
+#include "route_rules.hpp"
+int main() {
+  std::string op;
+  int T, E, a, b;
+  while (std::cin >> op >> T >> E >> a >> b)
+    if (op == "select") std::cout << revive::selects_by_rows(T, E, a, b) << '\\n';
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "driver.cpp").write_text(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I" + build.CSRC, str(d / "driver.cpp"), "-o", str(d / "driver")],
+                   check=True, capture_output=True, text=True)
+
+    def run(op, calls):
+        text = "\n".join(" ".join(map(str, (op, *c))) for c in calls)
+        return subprocess.run([str(d / "driver")], input=text, check=True, capture_output=True, text=True).stdout.split()
+
+    return run
+
+
+# (T, E, n_group, k): us with a wavefront per token and with a row of 16 lanes per token
+SELECTION = {
+    (64, 64, 1, 6): (3.4, 3.6), (2048, 64, 1, 8): (4.2, 4.2), (1003, 128, 1, 8): (4.3, 4.7), (64, 192, 1, 8): (4.7, 5.6),
+    (64, 192, 1, 16): (6.4, 8.4), (256, 16, 1, 16): (4.3, 5.7), (1003, 112, 1, 16): (5.5, 6.7), (1003, 384, 1, 6): (5.0, 6.2),
+    (2049, 272, 1, 2): (4.1, 4.6), (2049, 384, 1, 8): (6.4, 7.2), (3072, 48, 1, 6): (4.3, 3.8), (4096, 64, 1, 6): (5.0, 3.8),
+    (4096, 384, 1, 8): (7.9, 7.3), (8192, 512, 1, 8): (16.3, 11.1), (65536, 512, 1, 1): (26.6, 26.7), (65536, 500, 1, 1): (26.5, 23.2),
+    (64, 128, 4, 2): (4.3, 4.0), (64, 192, 8, 2): (6.0, 4.8), (256, 64, 8, 6): (4.7, 4.7), (1003, 192, 2, 8): (6.0, 6.7),
+    (1003, 112, 2, 16): (6.7, 7.4), (1003, 256, 8, 8): (6.6, 7.2), (2049, 256, 8, 8): (7.9, 7.3), (2049, 512, 2, 16): (13.9, 14.5),
+    (4096, 512, 2, 16): (17.7, 14.7), (2049, 400, 2, 4): (7.4, 8.9), (3072, 400, 2, 4): (8.0, 9.0), (4096, 400, 2, 4): (9.6, 9.0),
+}
+
+
+def test_selection_takes_the_faster_kernel(ask):
+    for (call, us), rows in zip(SELECTION.items(), ask("select", SELECTION)):
+        assert us[int(rows)] <= 1.03 * min(us), call  # the two runs of a call differ by 3 %
+
+
+def test_selection_by_rows_only_where_its_lanes_fit(ask):
+    calls = [(T, E, g, k) for T in (1, 16, 17, 70000) for E in (8, 24, 60, 64, 120, 360, 512) for g in (1, 2, 3, 4, 5, 8, 16) if E % g == 0
+             for k in (1, 8, 16, 17, 32)]
+    for (T, E, g, k), rows in zip(calls, ask("select", calls)):
+        fits = k <= 16 and (g == 1 or (g in (2, 4, 8) and E % 16 == 0))
+        assert fits or rows == "0", (T, E, g, k)
