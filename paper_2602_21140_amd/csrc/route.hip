@@ -552,24 +552,22 @@ int router_tile(revive_ctx* ctx, const void* x, const void* w, float* logits, in
   return check_hip(ctx, hipGetLastError(), "router_tile launch");
 }
 
-// K in one sequence: the smallest tiles of which 256 cover the logits, one per CU.  us with cold caches, E = 256,
-// H = 7168, of a 128 x 64 register-staged GEMM and of the tile taken: 512 tokens 73 and 19 (seq. 16 x 16: 20), 1003
-// tokens 74 and 21 (32 x 64 tiles 25), 2048 74 and 26 (32 x 32 tiles 32, 64 x 64 36), 4096 77 and 36 (32 x 64 49, 64 x 128
-// 50), 8192 81 and 54 (64 x 64 68, 128 x 128 73), 16 384 95 and 79 (64 x 128 102), 32 768 163 and 129 (128 x 128 156);
-// 32 768 tokens and E = 384 247 and 187 (128 x 128 219).
+// K in one sequence.
 int router_one_sequence(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
-  const int E = ctx->cfg.E;
-  auto fits = [&](int bm, int bn) { return static_cast<int64_t>(ceil_div(T, bm)) * ceil_div(E, bn) <= 256; };
-  if (fits(8, 8)) return router_sequence<8, 8>(ctx, x, w, logits, T, stream);
-  if (fits(16, 16) || ctx->cfg.H < 128) return router_sequence<16, 16>(ctx, x, w, logits, T, stream);
-  if (fits(32, 32)) return router_tile<32, 32, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
-  if (fits(32, 64)) return router_tile<32, 64, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
-  if (fits(64, 64)) return router_tile<64, 64, 4, 2, 128, 4>(ctx, x, w, logits, T, stream);
-  if (fits(64, 128)) return router_tile<64, 128, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
-  const int wide = ceil_div(E, 256), each = ceil_div(E, wide);  // column tiles of up to 256 experts, and their experts
-  if (static_cast<int64_t>(ceil_div(T, 128)) * wide < 256) return router_tile<128, 128, 2, 4, 64, 4>(ctx, x, w, logits, T, stream);
-  if (each <= 192) return router_tile<128, 192, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
-  return router_tile<128, 256, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
+  switch (router_form(T, ctx->cfg.E, ctx->cfg.H)) {
+    case kSeq8x8: return router_sequence<8, 8>(ctx, x, w, logits, T, stream);
+    case kSeq16x16: return router_sequence<16, 16>(ctx, x, w, logits, T, stream);
+    case k32x32x64s2: return router_tile<32, 32, 2, 2, 64, 2>(ctx, x, w, logits, T, stream);
+    case k128x64x64s2: return router_tile<128, 64, 4, 2, 64, 2>(ctx, x, w, logits, T, stream);
+    case k32x32x128s4: return router_tile<32, 32, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
+    case k32x64x128s4: return router_tile<32, 64, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
+    case k64x64x128s4: return router_tile<64, 64, 4, 2, 128, 4>(ctx, x, w, logits, T, stream);
+    case k64x128x64s3: return router_tile<64, 128, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
+    case k128x128x64s4: return router_tile<128, 128, 2, 4, 64, 4>(ctx, x, w, logits, T, stream);
+    case k128x192x64s3: return router_tile<128, 192, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
+    case k128x256x64s3: return router_tile<128, 256, 2, 4, 64, 3>(ctx, x, w, logits, T, stream);
+  }
+  return fail(ctx, REVIVE_EINVAL, "router: no kernel");
 }
 
 // Many tokens in fp32, K in the router kernel's slices.  The number of experts is a multiple of 4.

@@ -1,7 +1,42 @@
 // Which kernel serves a call of the gate: rules on sizes, with both sides of each line measured.  Host code without HIP.
 #pragma once
 
+#include <cstdint>
+
 namespace revive {
+
+// The bf16 router with K in one sequence: router_sequence_kernel with 8 x 8 or 16 x 16 tiles of tokens and experts, or
+// router_tile_kernel.  The names give tokens x experts x K-elements of a step and the stages of the ring.
+enum RouterForm { kSeq8x8, kSeq16x16, k32x32x64s2, k128x64x64s2, k32x32x128s4, k32x64x128s4, k64x64x128s4, k64x128x64s3, k128x128x64s4, k128x192x64s3, k128x256x64s3 };
+
+// The smallest tiles of which at most 256, one per CU, cover the logits.  us with cold caches, E = 256, H = 7168, of a 128 x
+// 64 register-staged GEMM and of the tile taken: 512 tokens 73 and 19 (16 x 16 in sequence: 20), 1003 tokens 74 and 21 (32
+// x 64 tiles 25), 2048 74 and 26 (32 x 32 tiles 32, 64 x 64 36), 4096 77 and 36 (32 x 64 49, 64 x 128 50), 8192 81 and 54
+// (64 x 64 68, 128 x 128 73), 16 384 95 and 79 (64 x 128 102), 32 768 163 and 129 (128 x 128 156); 32 768 tokens and
+// E = 384 247 and 187 (128 x 128 219).  Just past a line the next tile leaves CUs without work, but the smaller ones would
+// take a second round: back to back, 257 tokens (72 tiles of 32 x 32) 18.8 (16 x 16 in sequence 16.5), 1025 tokens (132 of
+// 32 x 64) 23.4 (32 x 32 22.2), 2049 (132 of 64 x 64) 27.4 (32 x 64 41), 4097 (130 of 64 x 128) 41.1 (64 x 64 51).
+//
+// A short K does not fill a deep ring of large steps: what a tile costs is its first copies and its stores, which need
+// several workgroups on a CU to hide one another.  us of route() back to back, of the GEMM, of the rule above (which sent
+// all of H = 64 to 16 x 16 in sequence) and of the short forms: H = 64, E = 256: 1003 tokens 6.9, 9.3, 6.0, 8192 14.1, 40,
+// 11.8, 65 536 36, 252, 37; H = 64, E = 40, 16 384 tokens 9.9, 19.0, 8.7; H = 128, E = 256, 32 768 tokens 28, 34, 27; H =
+// 320, the same 28, 30, 28.  At H = 704 the two are equal (E = 192, 65 536 tokens 42 and 43).
+inline RouterForm router_form(int T, int E, int H) {
+  auto tiles = [&](int bm, int bn) { return static_cast<int64_t>((T + bm - 1) / bm) * ((E + bn - 1) / bn); };
+  auto fits = [&](int bm, int bn) { return tiles(bm, bn) <= 256; };
+  if (fits(8, 8)) return kSeq8x8;
+  if (H < 128) return tiles(32, 32) <= 1024 ? k32x32x64s2 : k128x64x64s2;
+  if (fits(16, 16)) return kSeq16x16;
+  if (fits(32, 32)) return k32x32x128s4;
+  if (fits(32, 64)) return k32x64x128s4;
+  if (fits(64, 64)) return k64x64x128s4;
+  if (fits(64, 128)) return k64x128x64s3;
+  if (H < 512) return k128x64x64s2;
+  const int wide = (E + 255) / 256, each = (E + wide - 1) / wide;  // column tiles of up to 256 experts, and their experts
+  if (static_cast<int64_t>((T + 127) / 128) * wide < 256) return k128x128x64s4;
+  return each <= 192 ? k128x192x64s3 : k128x256x64s3;
+}
 
 // The selection with a row of 16 lanes per token (route_topk_rows_kernel) instead of a wavefront (route_topk_kernel).
 //

@@ -97,7 +97,7 @@ done:
 
 // More tokens: BM tokens and BN experts per workgroup of WM x WN wavefronts; K in steps of BK through a ring of S
 // stages filled by asynchronous global->LDS copies.  What bounds it is how fast a CU pulls its rows of x and w in out
-// of L2, so the tile is the largest that still gives every CU one (router_tile in route.hip has the figures).
+// of L2, or with a short K the start and end of a tile (router_form has the rule and the figures).
 //
 // LDS layout of a stage: row r (tokens, then experts) at r * BK * 2 bytes, its 16-byte chunks stored at chunk ^ swizzle,
 // so that the 16 rows of a fragment read fall on 16 different 16-byte bank groups.

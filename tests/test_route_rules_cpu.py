@@ -18,6 +18,7 @@ int main() {
   int T, E, a, b;
   while (std::cin >> op >> T >> E >> a >> b)
     if (op == "select") std::cout << revive::selects_by_rows(T, E, a, b) << '\\n';
+    else if (op == "router") std::cout << revive::router_form(T, E, a) << '\\n';
 }
 """
 
@@ -59,3 +60,28 @@ def test_selection_by_rows_only_where_its_lanes_fit(ask):
     for (T, E, g, k), rows in zip(calls, ask("select", calls)):
         fits = k <= 16 and (g == 1 or (g in (2, 4, 8) and E % 16 == 0))
         assert fits or rows == "0", (T, E, g, k)
+
+
+FORMS = ["seq8x8", "seq16x16", "32x32x64s2", "128x64x64s2", "32x32x128s4", "32x64x128s4", "64x64x128s4", "64x128x64s3", "128x128x64s4",
+         "128x192x64s3", "128x256x64s3"]  # as in the header
+# (T, E, H): us of route() back to back with each form of the router
+ROUTER = {
+    (65, 256, 7168): {"seq8x8": 12.7, "seq16x16": 12.5, "32x32x128s4": 18.8},
+    (1025, 256, 7168): {"seq16x16": 35.4, "32x32x128s4": 22.2, "32x64x128s4": 23.4, "64x64x128s4": 27.1},
+    (4097, 256, 7168): {"64x64x128s4": 50.8, "64x128x64s3": 41.1, "128x128x64s4": 59.1},
+    (8193, 256, 7168): {"64x128x64s3": 64.1, "128x128x64s4": 60.6, "128x256x64s3": 95.9},
+    # a short K
+    (1003, 256, 64): {"seq16x16": 9.2, "32x32x64s2": 6.0, "128x64x64s2": 6.9, "64x128x64s3": 6.9},
+    (8192, 256, 64): {"seq16x16": 40.0, "32x32x64s2": 13.0, "128x64x64s2": 11.8, "64x128x64s3": 12.0, "128x256x64s3": 15.0},
+    (65536, 256, 64): {"seq16x16": 251.8, "128x64x64s2": 37.3, "128x256x64s3": 45.8},
+    (16384, 40, 64): {"seq16x16": 19.0, "32x32x64s2": 8.8, "128x64x64s2": 8.7},
+    (65536, 192, 128): {"64x128x64s3": 33.8, "128x192x64s3": 36.7, "128x64x64s2": 29.6},
+    (32768, 256, 128): {"64x128x64s3": 28.6, "128x256x64s3": 33.2, "128x64x64s2": 27.2},
+    (32768, 256, 192): {"64x128x64s3": 27.8, "128x256x64s3": 31.0, "128x64x64s2": 26.8},
+    (16384, 384, 320): {"64x128x64s3": 26.4, "128x192x64s3": 28.6, "128x64x64s2": 28.2},
+}
+
+
+def test_router_takes_a_fast_form(ask):
+    for (call, us), form in zip(ROUTER.items(), ask("router", [(*c, 0) for c in ROUTER])):
+        assert us[FORMS[int(form)]] <= 1.1 * min(us.values()), (call, FORMS[int(form)])
