@@ -559,6 +559,7 @@ int router_one_sequence(revive_ctx* ctx, const void* x, const void* w, float* lo
     case kSeq16x16: return router_sequence<16, 16>(ctx, x, w, logits, T, stream);
     case k32x32x64s2: return router_tile<32, 32, 2, 2, 64, 2>(ctx, x, w, logits, T, stream);
     case k128x64x64s2: return router_tile<128, 64, 4, 2, 64, 2>(ctx, x, w, logits, T, stream);
+    case k128x64x64s3: return router_tile<128, 64, 4, 2, 64, 3>(ctx, x, w, logits, T, stream);
     case k32x32x128s4: return router_tile<32, 32, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
     case k32x64x128s4: return router_tile<32, 64, 2, 2, 128, 4>(ctx, x, w, logits, T, stream);
     case k64x64x128s4: return router_tile<64, 64, 4, 2, 128, 4>(ctx, x, w, logits, T, stream);

@@ -7,7 +7,7 @@ namespace revive {
 
 // The bf16 router with K in one sequence: router_sequence_kernel with 8 x 8 or 16 x 16 tiles of tokens and experts, or
 // router_tile_kernel.  The names give tokens x experts x K-elements of a step and the stages of the ring.
-enum RouterForm { kSeq8x8, kSeq16x16, k32x32x64s2, k128x64x64s2, k32x32x128s4, k32x64x128s4, k64x64x128s4, k64x128x64s3, k128x128x64s4, k128x192x64s3, k128x256x64s3 };
+enum RouterForm { kSeq8x8, kSeq16x16, k32x32x64s2, k128x64x64s2, k128x64x64s3, k32x32x128s4, k32x64x128s4, k64x64x128s4, k64x128x64s3, k128x128x64s4, k128x192x64s3, k128x256x64s3 };
 
 // The smallest tiles of which at most 256, one per CU, cover the logits.  us with cold caches, E = 256, H = 7168, of a 128 x
 // 64 register-staged GEMM and of the tile taken: 512 tokens 73 and 19 (16 x 16 in sequence: 20), 1003 tokens 74 and 21 (32
@@ -22,6 +22,12 @@ enum RouterForm { kSeq8x8, kSeq16x16, k32x32x64s2, k128x64x64s2, k32x32x128s4, k
 // all of H = 64 to 16 x 16 in sequence) and of the short forms: H = 64, E = 256: 1003 tokens 6.9, 9.3, 6.0, 8192 14.1, 40,
 // 11.8, 65 536 36, 252, 37; H = 64, E = 40, 16 384 tokens 9.9, 19.0, 8.7; H = 128, E = 256, 32 768 tokens 28, 34, 27; H =
 // 320, the same 28, 30, 28.  At H = 704 the two are equal (E = 192, 65 536 tokens 42 and 43).
+//
+// Many tokens: one round of tiles as long as any form makes one; beyond it the widest.  Few experts do not fill a wide tile:
+// E = 40, H = 704, 32 769 tokens 128 x 64 16.4, 128 x 128 22.0, 128 x 192 25.2 (the GEMM 20.2); E = 64, H = 2112 33, 44, 51
+// (37); E = 100, of which 257 tiles of 128 x 128 would start a second round, 39, 45, 54 (47), but E = 128, 65 536 tokens 86,
+// 71, 76 (79).  E = 192, 16 385 tokens, H = 7168: 258 tiles of 128 x 128 113, 129 of 128 x 192 79 (the GEMM 88); E = 512,
+// 12 000 tokens, H = 2112: 376 of 128 x 128 48, 188 of 128 x 256 43 (50).
 inline RouterForm router_form(int T, int E, int H) {
   auto tiles = [&](int bm, int bn) { return static_cast<int64_t>((T + bm - 1) / bm) * ((E + bn - 1) / bn); };
   auto fits = [&](int bm, int bn) { return tiles(bm, bn) <= 256; };
@@ -33,8 +39,10 @@ inline RouterForm router_form(int T, int E, int H) {
   if (fits(64, 64)) return k64x64x128s4;
   if (fits(64, 128)) return k64x128x64s3;
   if (H < 512) return k128x64x64s2;
+  if (E <= 64) return k128x64x64s3;
+  if (fits(128, 128)) return k128x128x64s4;
+  if (E <= 128) return tiles(128, 128) <= 384 ? k128x64x64s3 : k128x128x64s4;
   const int wide = (E + 255) / 256, each = (E + wide - 1) / wide;  // column tiles of up to 256 experts, and their experts
-  if (static_cast<int64_t>((T + 127) / 128) * wide < 256) return k128x128x64s4;
   return each <= 192 ? k128x192x64s3 : k128x256x64s3;
 }
 

@@ -85,3 +85,9 @@ def test_every_tile_gives_the_same_bits(E, H):
         logits = torch.full((T, E), float("nan"), device="cuda")
         assert torch.equal(L.route(x[:T].contiguous(), w, T, logits=logits)[0], whole[:T]), T
     L.close()
+
+
+# few experts, which take narrow tiles with many tokens, and experts of which one round of 128 x 128 tiles just does not do
+@pytest.mark.parametrize("E,H", [(40, 704), (100, 576), (16, 64), (130, 64)])
+def test_every_tile_gives_the_same_bits_few_experts(E, H):
+    test_every_tile_gives_the_same_bits(E, H)
