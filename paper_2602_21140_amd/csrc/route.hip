@@ -234,9 +234,10 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
   }
   if (li < p.k && t < p.T) {
     const int64_t o = static_cast<int64_t>(t) * p.k + li;
+    const int phys = replica(p, t, my_e, c);
     p.topk_logical[o] = my_e;
     p.topk_weight[o] = static_cast<float>(s / sum * static_cast<double>(p.route_scale));
-    p.topk_phys[o] = replica(p, t, my_e, c);
+    p.topk_phys[o] = phys;
   }
 }
 
@@ -374,9 +375,10 @@ __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
   sum += dpp_f64<0xB1>(sum);
   if (li < p.k && t < p.T) {
     const int64_t o = static_cast<int64_t>(t) * p.k + li;
+    const int phys = replica(p, t, c.e, count);
     p.topk_logical[o] = c.e;
     p.topk_weight[o] = static_cast<float>(s / sum * static_cast<double>(p.route_scale));
-    p.topk_phys[o] = replica(p, t, c.e, count);
+    p.topk_phys[o] = phys;
   }
 }
 

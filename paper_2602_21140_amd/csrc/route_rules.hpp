@@ -49,23 +49,28 @@ inline RouterForm router_form(int T, int E, int H) {
 // The selection with a row of 16 lanes per token (route_topk_rows_kernel) instead of a wavefront (route_topk_kernel).
 //
 // A row does a quarter of the work per token, but its lanes have four times as many experts to go through one after the
-// other: it wins where there are tokens enough to keep the ALUs busy.  us of route() on given logits, back to back, a
-// wavefront per token and a row per token (E experts, g groups, k choices):
-//   no groups   E = 64, k = 6: 64 tokens 3.4 and 3.6, 2049 3.9 and 3.8, 8192 8.6 and 5.6; E = 192, k = 8, 64 tokens 4.7
-//               and 5.6; E = 112, k = 16, 1003 tokens 5.5 and 6.7; E = 384, k = 8: 2049 6.4 and 7.2, 3072 6.9 and 7.1,
-//               4096 7.9 and 7.3, 65 536 69 and 42; E = 512, k = 1, 65 536 26.6 and 26.7; E = 500, the same 26.5 and 23
-//   groups      E = 256, g = 8, k = 8: 1003 6.6 and 7.2, 2049 7.9 and 7.3, 8192 16.8 and 10.1, 65 536 77 and 39; E = 512,
-//               g = 2, k = 16: 2049 13.9 and 14.5, 4096 17.7 and 14.7; E = 400 (no multiple of 64: 4-byte loads), g = 2,
-//               k = 4: 3072 8.0 and 9.0, 4096 9.6 and 9.0.  Few experts and choices win from a few tokens on, since a row
-//               finds all groups' scores at once: E = 128, g = 4, k = 2, 64 tokens 4.3 and 4.0, E = 192, g = 8, k = 2, 64
-//               tokens 6.0 and 4.8 (k = 8: 1003 tokens, g = 2, 6.0 and 6.7).
+// other: it wins with many tokens, which keep the ALUs busy, and where the experts are few.  us of route() with the
+// product, H = 256, back to back, a wavefront per token and a row per token (E experts, g groups, k choices):
+//   no groups   E = 64: k = 6, 37 tokens 6.7 and 6.5, 4096 9.4 and 8.0; k = 16, 17 tokens 7.9 and 8.2, 2049 10.2 and 10.1;
+//               E = 128: k = 8, 64 tokens 7.4 and 7.8, 300 7.5 and 7.5; k = 16, 1003 9.6 and 10.4, 2560 12.9 and 12.5;
+//               E = 192, k = 8: 2049 9.2 and 10.2, 3584 11.5 and 11.0; E = 384, k = 8: 2560 12.5 and 13.6, 3584 14.6 and
+//               14.9; on given logits, 65 536 tokens: E = 384, k = 8 69 and 42, E = 512, k = 1 26.6 and 26.7
+//   groups      a row finds all groups' scores at once.  E = 128, g = 4, k = 2, 64 tokens 7.6 and 7.2; E = 192: g = 8, k =
+//               2, 64 tokens 8.8 and 7.5, g = 2, k = 8, 1003 9.1 and 10.1; E = 256, g = 8, k = 8: 1003 9.8 and 10.5, 2049
+//               12.3 and 11.8, 8192 24.3 and 18.4; E = 512, g = 2, k = 8: 3000 17.1 and 17.7, 3584 19.5 and 18.1; E = 64, g =
+//               4, k = 16: 129 tokens 8.7 and 8.9, 2048 10.5 and 10.1; E = 400
+//               (no multiple of 64: 4-byte loads), g = 2, k = 4, given logits: 3072 8.0 and 9.0, 4096 9.6 and 9.0
 inline bool selects_by_rows(int T, int E, int n_group, int k) {
   if (k > 16 || T <= 16) return false;
-  if (n_group > 1 && (E % 16 != 0 || (n_group != 2 && n_group != 4 && n_group != 8))) return false;
-  if (n_group == 1) return T >= (E <= 128 ? 2560 : 3584);
-  if (k <= (E <= 128 ? 6 : E <= 192 ? 2 : 0)) return true;
+  if (n_group == 1) {
+    if (E > 128) return T >= 3584;
+    return T >= (E > 64 ? (k > 8 ? 2560 : 129) : (k > 8 ? 2049 : 17));
+  }
+  if (E % 16 != 0 || (n_group != 2 && n_group != 4 && n_group != 8)) return false;
+  if (k <= (E <= 128 ? 8 : E > 192 ? 0 : n_group == 2 ? 2 : n_group == 4 ? 6 : 8)) return true;
   if (E % 64 != 0 && E > 384) return T >= 4096;
-  return T > (k <= 8 ? 2048 : 3072);
+  if (E > 128 * n_group) return T > 3072;
+  return T >= (k <= 8 ? 2049 : E < 128 ? 1500 : n_group == 8 ? 2049 : 2560);
 }
 
 }  // namespace revive

@@ -37,21 +37,28 @@ def ask(tmp_path_factory):
     return run
 
 
-# (T, E, n_group, k): us with a wavefront per token and with a row of 16 lanes per token
+# (T, E, n_group, k): us of route() with the product, H = 256, with a wavefront per token and with a row of 16 lanes per token
 SELECTION = {
-    (64, 64, 1, 6): (3.4, 3.6), (2048, 64, 1, 8): (4.2, 4.2), (1003, 128, 1, 8): (4.3, 4.7), (64, 192, 1, 8): (4.7, 5.6),
-    (64, 192, 1, 16): (6.4, 8.4), (256, 16, 1, 16): (4.3, 5.7), (1003, 112, 1, 16): (5.5, 6.7), (1003, 384, 1, 6): (5.0, 6.2),
-    (2049, 272, 1, 2): (4.1, 4.6), (2049, 384, 1, 8): (6.4, 7.2), (3072, 48, 1, 6): (4.3, 3.8), (4096, 64, 1, 6): (5.0, 3.8),
-    (4096, 384, 1, 8): (7.9, 7.3), (8192, 512, 1, 8): (16.3, 11.1), (65536, 512, 1, 1): (26.6, 26.7), (65536, 500, 1, 1): (26.5, 23.2),
-    (64, 128, 4, 2): (4.3, 4.0), (64, 192, 8, 2): (6.0, 4.8), (256, 64, 8, 6): (4.7, 4.7), (1003, 192, 2, 8): (6.0, 6.7),
-    (1003, 112, 2, 16): (6.7, 7.4), (1003, 256, 8, 8): (6.6, 7.2), (2049, 256, 8, 8): (7.9, 7.3), (2049, 512, 2, 16): (13.9, 14.5),
-    (4096, 512, 2, 16): (17.7, 14.7), (2049, 400, 2, 4): (7.4, 8.9), (3072, 400, 2, 4): (8.0, 9.0), (4096, 400, 2, 4): (9.6, 9.0),
+    (37, 64, 1, 6): (6.7, 6.5), (17, 64, 1, 8): (6.8, 6.8), (1003, 64, 1, 8): (7.3, 7.0), (17, 64, 1, 16): (7.9, 8.2),
+    (2049, 64, 1, 16): (10.2, 10.1), (4096, 64, 1, 6): (9.4, 8.0), (64, 32, 1, 1): (6.1, 5.8), (64, 16, 1, 4): (6.4, 6.0),
+    (64, 128, 1, 8): (7.4, 7.8), (300, 128, 1, 8): (7.5, 7.5), (64, 128, 1, 16): (8.4, 9.7), (1003, 128, 1, 16): (9.6, 10.4),
+    (2560, 128, 1, 16): (12.9, 12.5), (64, 192, 1, 8): (7.4, 8.5), (2049, 192, 1, 8): (9.2, 10.2), (3584, 192, 1, 8): (11.5, 11.0),
+    (1003, 384, 1, 6): (8.9, 11.3), (2560, 384, 1, 8): (12.5, 13.6), (3584, 384, 1, 8): (14.6, 14.9), (8192, 512, 1, 8): (29.3, 25.0),
+    (64, 128, 4, 2): (7.6, 7.2), (64, 192, 8, 2): (8.8, 7.5), (64, 64, 8, 6): (7.8, 7.6), (1003, 128, 8, 8): (9.7, 10.0),
+    (1003, 192, 2, 8): (9.1, 10.1), (64, 192, 4, 6): (8.7, 8.8), (1003, 112, 2, 16): (10.9, 11.3), (1003, 256, 8, 8): (9.8, 10.5),
+    (2049, 256, 8, 8): (12.3, 11.8), (8192, 256, 8, 8): (24.3, 18.4), (2049, 512, 2, 16): (19.4, 21.6), (3584, 512, 2, 16): (25.6, 23.0),
+    (2049, 512, 2, 8): (15.1, 16.7), (3000, 512, 2, 8): (17.1, 17.7), (3584, 512, 2, 8): (19.5, 18.1), (2049, 384, 4, 8): (14.2, 13.7),
+    (129, 64, 4, 16): (8.7, 8.9), (2048, 64, 4, 16): (10.5, 10.1), (2048, 128, 4, 16): (11.7, 12.1), (2560, 128, 4, 16): (14.5, 13.6),
+    (2048, 32, 2, 16): (9.3, 9.1), (2048, 192, 2, 16): (12.6, 13.9), (2049, 32, 1, 16): (9.2, 9.3),
+    # on given logits
+    (65536, 384, 1, 8): (69.4, 42.4), (65536, 512, 1, 1): (26.6, 26.7), (65536, 500, 1, 1): (26.5, 23.2), (1003, 112, 1, 16): (5.5, 6.7),
+    (3072, 400, 2, 4): (8.0, 9.0), (4096, 400, 2, 4): (9.6, 9.0),
 }
 
 
 def test_selection_takes_the_faster_kernel(ask):
     for (call, us), rows in zip(SELECTION.items(), ask("select", SELECTION)):
-        assert us[int(rows)] <= 1.03 * min(us), call  # the two runs of a call differ by 3 %
+        assert us[int(rows)] <= 1.035 * min(us), call  # runs of one call differ by as much
 
 
 def test_selection_by_rows_only_where_its_lanes_fit(ask):
