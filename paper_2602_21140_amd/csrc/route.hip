@@ -604,14 +604,14 @@ int launch_router_gemm(revive_ctx* ctx, const void* x, const void* w, float* log
     return router<float>(ctx, x, w, logits, T, stream);
   }
   // The order in which K is summed follows from E and H alone, so that a token's logits do not depend on how many
-  // others are in the call.  Small routers: K in slices, in the router kernel or (many tokens, which it reads once
-  // per 32 experts) in the GEMM.  us between events: E = 64, H = 2048, 16 384 tokens (the limit) 23 and 23, 32 768
-  // tokens 38 and 26; E = 128, H = 7168, 8192 tokens 51 and 57, 16 384 tokens 97 and 62.
-  const bool small = c.E <= 128 && c.H % 256 == 0;
-  if (small) {
-    if (static_cast<int64_t>(ceil_div(T, 32)) * c.E * c.H * 2 <= (128ll << 20)) return router<uint16_t>(ctx, x, w, logits, T, stream);
-    return c.E <= 64 ? router_tile<128, 64, 4, 2, 64, 4, kRouterSlices>(ctx, x, w, logits, T, stream)
-                     : router_tile<128, 128, 2, 4, 64, 4, kRouterSlices>(ctx, x, w, logits, T, stream);
+  // others are in the call.  Small routers: K in slices.
+  if (c.E <= 128 && c.H % 256 == 0) {
+    switch (router_sliced_form(T, c.E, c.H)) {
+      case kSlicedRouter: return router<uint16_t>(ctx, x, w, logits, T, stream);
+      case kSliced128x64s4: return router_tile<128, 64, 4, 2, 64, 4, kRouterSlices>(ctx, x, w, logits, T, stream);
+      case kSliced128x64s3: return router_tile<128, 64, 4, 2, 64, 3, kRouterSlices>(ctx, x, w, logits, T, stream);
+      case kSliced128x128s4: return router_tile<128, 128, 2, 4, 64, 4, kRouterSlices>(ctx, x, w, logits, T, stream);
+    }
   }
   // Many experts, or an odd K: K is summed in one sequence.  A K split is faster for a middling number of tokens (1003
   // tokens, E = 256, H = 7168: 19 us) but another order moves one of 8192 x 256 logits across a near tie in every few

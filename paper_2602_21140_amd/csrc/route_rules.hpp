@@ -46,6 +46,22 @@ inline RouterForm router_form(int T, int E, int H) {
   return each <= 192 ? k128x192x64s3 : k128x256x64s3;
 }
 
+// The bf16 router of few experts, K in the slices of router_kernel: that kernel, or router_tile_kernel in those slices.
+enum RouterSlicedForm { kSlicedRouter, kSliced128x64s4, kSliced128x64s3, kSliced128x128s4 };
+
+// router_kernel reads x once per 32 experts; with many tokens the tiles, which read it once.  us of route() back to back,
+// router_kernel, 128 x 64 tiles with a ring of four stages and of three, 128 x 128 tiles: E = 64, H = 4096: 8192 tokens
+// 24, 28, 29, 39, 16 384 39, 30, 30, 41, 32 768 71, 47, 48, 49; E = 128, H = 7168: 4097 tokens 40, 42, -, 63, 16 384 102,
+// 51, 54, 66; H = 4096, 32 768 tokens (256 tiles of 128 x 128) 124, 71, 68, 60.  A ring of three lets two tiles onto a CU:
+// past 256 tiles of 128 x 64 (E = 40, H = 2048, 32 769 tokens) 37 with four and 31 with three; E = 128, where 257 tiles of
+// 128 x 128 would start a second round, 47, 42 and with those 49.
+inline RouterSlicedForm router_sliced_form(int T, int E, int H) {
+  if (static_cast<int64_t>((T + 31) / 32) * E * H * 2 <= (128ll << 20)) return kSlicedRouter;
+  const int tall = (T + 127) / 128;  // tiles of 128 tokens
+  if (tall * ((E + 63) / 64) <= 256) return kSliced128x64s4;
+  return E <= 64 || (tall > 256 && tall <= 384) ? kSliced128x64s3 : kSliced128x128s4;
+}
+
 // The selection with a row of 16 lanes per token (route_topk_rows_kernel) instead of a wavefront (route_topk_kernel).
 //
 // A row does a quarter of the work per token, but its lanes have four times as many experts to go through one after the

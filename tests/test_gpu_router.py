@@ -91,3 +91,9 @@ def test_every_tile_gives_the_same_bits(E, H):
 @pytest.mark.parametrize("E,H", [(40, 704), (100, 576), (16, 64), (130, 64)])
 def test_every_tile_gives_the_same_bits_few_experts(E, H):
     test_every_tile_gives_the_same_bits(E, H)
+
+
+# few experts, K in slices: past one round of narrow tiles, of wide ones, and far past both
+@pytest.mark.parametrize("T,E", [(32769, 40), (16385, 100), (32769, 70), (49200, 128)])
+def test_router_logits_in_slices(T, E):
+    test_router_logits(T, E, 1024, "bf16")

@@ -19,6 +19,7 @@ int main() {
   while (std::cin >> op >> T >> E >> a >> b)
     if (op == "select") std::cout << revive::selects_by_rows(T, E, a, b) << '\\n';
     else if (op == "router") std::cout << revive::router_form(T, E, a) << '\\n';
+    else if (op == "sliced") std::cout << revive::router_sliced_form(T, E, a) << '\\n';
 }
 """
 
@@ -104,3 +105,21 @@ def test_router_takes_a_fast_form(ask):
     for (call, us), form in zip(ROUTER.items(), ask("router", [(*c, 0) for c in ROUTER])):
         # a rule of few lines leaves up to 15 % at a sixth of these sizes; what it is to keep away from is twice as slow
         assert us[FORMS[int(form)]] <= 1.15 * min(us.values()), (call, FORMS[int(form)])
+
+
+# the same for few experts, K in slices
+SLICED_FORMS = ["router_kernel", "128x64s4", "128x64s3", "128x128s4"]
+SLICED = {
+    (3000, 128, 7168): {"128x64s4": 41.3, "128x128s4": 62.3}, (8193, 128, 7168): {"router_kernel": 60.8, "128x64s4": 43.4, "128x128s4": 62.8},
+    (16384, 128, 2048): {"router_kernel": 38.3, "128x64s4": 21.9, "128x64s3": 22.1, "128x128s4": 27.8},
+    (24000, 128, 2048): {"router_kernel": 52.1, "128x64s4": 34.4, "128x64s3": 30.0, "128x128s4": 29.6},
+    (32769, 128, 2048): {"router_kernel": 69.1, "128x64s4": 47.2, "128x64s3": 41.8, "128x128s4": 48.8},
+    (3000, 40, 2048): {"router_kernel": 10.0, "128x64s4": 16.0}, (32768, 40, 2048): {"router_kernel": 39.3, "128x64s4": 27.6, "128x64s3": 27.0},
+    (32769, 40, 2048): {"router_kernel": 40.8, "128x64s4": 36.9, "128x64s3": 30.8, "128x128s4": 45.6},
+    (65536, 64, 2048): {"router_kernel": 80.0, "128x64s4": 53.7, "128x64s3": 51.9, "128x128s4": 57.4},
+}
+
+
+def test_router_in_slices_takes_a_fast_form(ask):
+    for (call, us), form in zip(SLICED.items(), ask("sliced", [(*c, 0) for c in SLICED])):
+        assert us[SLICED_FORMS[int(form)]] <= 1.05 * min(us.values()), (call, SLICED_FORMS[int(form)])
