@@ -653,10 +653,8 @@ int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk
 #undef REVIVE_ROUTE_LAUNCH
     return check_hip(ctx, hipGetLastError(), "route_topk launch");
   }
-  // Few tokens, other groups, more choices.  Four tokens to a wavefront do less work in all but take longer one by one:
-  // E = 256, 8 groups, k = 8, with the counts and launches around it, 4096 tokens 17.0 us (one) and 17.9 (four), 8192:
-  // 21.2 and 21.1, 32768: 58 and 51.
-  const bool four = T > 8192 && c.k <= 16 && c.n_group <= 8;
+  // Few tokens, other groups, more choices.
+  const bool four = selects_four_tokens(T, c.n_group, c.k);
   const dim3 grid(ceil_div(T, four ? 16 : 4)), block(256);
   const int vals = ceil_div(c.E, 64);
 #define REVIVE_ROUTE_LAUNCH(V)                                                                                       \

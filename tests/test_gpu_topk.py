@@ -18,7 +18,7 @@ SHAPES = [(64, 8, 3, 6), (128, 8, 4, 8), (256, 8, 4, 8), (512, 8, 4, 8), (192, 8
           (256, 2, 1, 8), (32, 8, 8, 16), (512, 32, 8, 32), (320, 20, 3, 8), (256, 8, 4, 17), (61, 1, 1, 1), (384, 1, 1, 8), (500, 1, 1, 32)]
 
 
-@pytest.mark.parametrize("T", [1, 301, 8193])  # 8193: four tokens to a wavefront, the last wavefront with one
+@pytest.mark.parametrize("T", [1, 301, 8193])
 @pytest.mark.parametrize("score_fn", ["softmax", "sigmoid"])
 @pytest.mark.parametrize("E,n_group,topk_group,k", SHAPES)
 def test_topk(E, n_group, topk_group, k, score_fn, T):
@@ -60,6 +60,21 @@ def test_a_row_of_lanes_per_token(E, n_group, topk_group, k, T):
                                                     (511, 1, 1, 5), (512, 1, 1, 1), (512, 2, 2, 16)])
 def test_a_row_of_lanes_per_token_many_tokens(E, n_group, topk_group, k, T):
     test_topk(E, n_group, topk_group, k, "softmax" if k % 2 else "sigmoid", T)
+
+
+# four tokens to a wavefront, the last wavefront with one: every count of logits per lane, groups that are aligned runs of
+# 8, 32 and 64 lanes and groups that are not; and one token to a wavefront just before
+@pytest.mark.parametrize("T", [16384, 16385])
+@pytest.mark.parametrize("E,n_group,topk_group,k", [(24, 3, 2, 4), (72, 8, 3, 6), (96, 3, 1, 16), (120, 5, 2, 6), (192, 3, 2, 9), (200, 8, 2, 16),
+                                                    (360, 5, 3, 8), (504, 7, 3, 16)])
+def test_four_tokens_to_a_wavefront(E, n_group, topk_group, k, T):
+    test_topk(E, n_group, topk_group, k, "sigmoid" if E % 3 else "softmax", T)
+
+
+@pytest.mark.parametrize("E,n_group,topk_group,k", [(24, 3, 2, 4), (200, 8, 2, 16), (504, 7, 3, 8)])
+def test_four_tokens_to_a_wavefront_nan(E, n_group, topk_group, k):
+    test_nan_logits_are_absent_from_their_group(E, n_group, topk_group, k, "softmax", 16385)
+    test_row_of_nan_keeps_valid_ids(E, n_group, k, 16385)
 
 
 # places of a lane that hold no expert are never chosen, not even where all the token's logits are NaN

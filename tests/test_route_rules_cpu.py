@@ -18,6 +18,7 @@ int main() {
   int T, E, a, b;
   while (std::cin >> op >> T >> E >> a >> b)
     if (op == "select") std::cout << revive::selects_by_rows(T, E, a, b) << '\\n';
+    else if (op == "four") std::cout << revive::selects_four_tokens(T, a, b) << '\\n';
     else if (op == "router") std::cout << revive::router_form(T, E, a) << '\\n';
     else if (op == "sliced") std::cout << revive::router_sliced_form(T, E, a) << '\\n';
 }
@@ -60,6 +61,19 @@ SELECTION = {
 def test_selection_takes_the_faster_kernel(ask):
     for (call, us), rows in zip(SELECTION.items(), ask("select", SELECTION)):
         assert us[int(rows)] <= 1.035 * min(us), call  # runs of one call differ by as much
+
+
+# the same with a wavefront per token and per four of them, on given logits
+FOUR = {
+    (8193, 120, 5, 2): (13.7, 14.1), (12288, 120, 5, 2): (17.7, 14.9), (65536, 120, 5, 2): (71.4, 55.7), (8193, 200, 8, 16): (28.0, 37.0),
+    (12288, 200, 8, 16): (35.9, 38.3), (65536, 200, 8, 16): (156.9, 144.7), (8193, 504, 7, 8): (28.0, 35.8), (16384, 504, 7, 8): (45.2, 45.3), (32768, 360, 5, 8): (64.4, 59.5),
+    (1003, 24, 3, 4): (4.1, 5.4), (16384, 24, 3, 4): (14.9, 11.4),
+}
+
+
+def test_selection_of_four_tokens_where_it_is_faster(ask):
+    for (call, us), four in zip(FOUR.items(), ask("four", FOUR)):
+        assert us[int(four)] <= 1.035 * min(us), call
 
 
 def test_selection_by_rows_only_where_its_lanes_fit(ask):
