@@ -199,11 +199,14 @@ def test_limits_of_the_streaming_kernel(P, H, I, I_shared, N, streamed):
     L.close()
 
 
-def test_fp32_rows_of_64_mib():
-    """Tiles whose 64 rows reach 4 GiB and further take 64-bit offsets.  x holds four elements of a row, so that every sum
-    has four products and 1e-5 is fp32's error; they lie at the ends and in the middle."""
-    H, I, counts = 1 << 24, 4, [64, 0, 17]
-    N, at = sum(counts), torch.tensor([0, 5, (1 << 23) + 3, (1 << 24) - 1], device="cuda")
+# The longest rows that 64 of them take 32-bit offsets for, and longer ones: rows 61 to 63 of a tile, of x and of the
+# weights, lie 4 GiB and more behind its first, where 32 bits would read other rows.
+@pytest.mark.parametrize("H", [(1 << 24) - 8, (1 << 24) + (1 << 20)])
+def test_fp32_rows_of_64_mib(H):
+    """x holds four elements of a row, at its ends and in the middle: a sum over H has four products, one over I 64 of them,
+    and 1e-5 is twenty times fp32's error."""
+    I, counts = 64, [64, 0, 17]
+    N, at = sum(counts), [0, 5, (1 << 23) + 3, H - 1]
     gen = torch.Generator(device="cuda").manual_seed(9)
     cfg = SimpleNamespace(T=N, H=H, E=3, k=1, I=I, I_shared=0, n_ranks=3, slots_per_rank=1, max_replicas=2, score_fn="softmax",
                           n_group=1, topk_group=1, dtype="fp32")
@@ -211,8 +214,9 @@ def test_fp32_rows_of_64_mib():
     weights = [(torch.randn(2 * I, H, generator=gen, device="cuda"), torch.randn(H, I, generator=gen, device="cuda")) if c else (None, None)
                for c in counts]
     L.set_expert_weights([w[0] for w in weights], [w[1] for w in weights])
-    x = torch.zeros(N, H, device="cuda")
-    x[:, at] = torch.randn(N, len(at), generator=gen, device="cuda")
+    own, x = torch.randn(N, len(at), generator=gen, device="cuda"), torch.zeros(N, H, device="cuda")
+    for j, col in enumerate(at):
+        x[:, col] = own[:, j]
     y = L.empty(N, H).fill_(float("nan"))
     off = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
     L.expert_ffn(x, off, N, out=(y, None))
@@ -221,6 +225,12 @@ def test_fp32_rows_of_64_mib():
         rows = slice(int(off[p]), int(off[p]) + c)
         if not c:
             continue
-        h = x[rows][:, at] @ weights[p][0][:, at].T
-        ref = (torch.nn.functional.silu(h[:, :I]) * h[:, I:]) @ weights[p][1].T
-        assert float((y[rows] - ref).abs().max() / ref.abs().max()) < 1e-5
+        h = own[rows].double() @ torch.stack([weights[p][0][:, col] for col in at]).double()
+        h = torch.nn.functional.silu(h[:, :I]) * h[:, I:]
+        worst, largest = [], []
+        for a in range(0, H, 1 << 20):  # a library's product over all of H has left rows of its result at zero
+            ref = h @ weights[p][1][a:a + (1 << 20)].double().T
+            worst.append((y[rows, a:a + (1 << 20)] - ref).abs().max())
+            largest.append(ref.abs().max())
+        assert float(torch.stack(worst).max() / torch.stack(largest).max()) < 1e-5, p
+    L.close()
