@@ -24,11 +24,10 @@ constexpr int kTimingPairs = 8192;    // event pairs kept before timing results 
 // record except for their position; tile_span() gives the rows of tile j.  The group's weight
 // matrices ride along so that a workgroup needs one read to know everything about its tile.
 struct MTile {
-  int32_t group;
   int32_t group_begin;
   int32_t group_end;
   int32_t pad;          // (row-tiles of the group << 16) | position of this tile inside its group
-  const void* w[2];     // the group's gate/up and down matrices (null when the caller uses a table)
+  const void* w[2];     // the group's gate/up and down matrices
 };
 
 // Row-tiles of a group with `rows` rows.  tall_m > tile_m: the largest number of rows that one (the only) tile of

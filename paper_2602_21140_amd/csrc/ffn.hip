@@ -70,7 +70,6 @@ __global__ __launch_bounds__(kMaxP) void ffn_tiles_kernel(const int32_t* __restr
     }
     const int g = lo;  // among slots with equal base (empty ones) the last, which is the one that holds tiles
     MTile t;
-    t.group = g;
     t.group_begin = slot_offsets[g];
     t.group_end = slot_offsets[g + 1];
     t.pad = ((tile_base[g + 1] - tile_base[g]) << 16) | (i - tile_base[g]);
@@ -101,8 +100,7 @@ constexpr int kTallM_bf16 = 320, kTallRowsPerSlot = 128, kTallWorkgroups = 128;
 
 struct Bf16Ffn {  // one SwiGLU FFN: rows of A -> h -> y
   const void* A;
-  const void* const* gu_tab; const void* gu_one;
-  const void* const* dn_tab; const void* dn_one;
+  const void* gu; const void* dn;  // weights (dense; the slots' are in the tile records)
   void* h; void* y;
   int I;
   const MTile* tiles; const int32_t* tile_count; int M;
@@ -113,13 +111,12 @@ struct Bf16Ffn {  // one SwiGLU FFN: rows of A -> h -> y
 GemmArgs gate_up_args(const revive_ctx* ctx, const Bf16Ffn& f, int bn_out) {
   GemmArgs a{};
   a.A = f.A; a.lda = ctx->cfg.H;
-  a.B_tab = f.gu_tab; a.B_one = f.gu_one; a.ldb = ctx->cfg.H;
+  a.B = f.gu;
   a.C = f.h; a.ldc = f.I; a.c_rows = f.h_rows;
   a.n_out = f.I; a.K = ctx->cfg.H;
   a.tiles = f.tiles; a.tile_count = f.tile_count; a.M = f.M;
   a.n_col_tiles = ceil_div(f.I, bn_out);
-  a.b_sel = f.tiles ? 0 : -1;
-  a.b_tiled = 1;
+  a.b_sel = 0;
   a.b_rows_pad = ceil_div(f.I, kWeightTileRows) * kWeightTileRows;
   return a;
 }
@@ -127,13 +124,12 @@ GemmArgs gate_up_args(const revive_ctx* ctx, const Bf16Ffn& f, int bn_out) {
 GemmArgs down_args(const revive_ctx* ctx, const Bf16Ffn& f, int bn_out) {
   GemmArgs d{};
   d.A = f.h; d.lda = f.I; d.a_rows = f.h_rows;
-  d.B_tab = f.dn_tab; d.B_one = f.dn_one; d.ldb = f.I;
+  d.B = f.dn;
   d.C = f.y; d.ldc = ctx->cfg.H;
   d.n_out = ctx->cfg.H; d.K = f.I;
   d.tiles = f.tiles; d.tile_count = f.tile_count; d.M = f.M;
   d.n_col_tiles = ceil_div(ctx->cfg.H, bn_out);
-  d.b_sel = f.tiles ? 1 : -1;
-  d.b_tiled = 1;
+  d.b_sel = 1;
   d.b_rows_pad = ceil_div(ctx->cfg.H, kWeightTileRows) * kWeightTileRows;
   return d;
 }
@@ -350,10 +346,10 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
                        tall ? kTallM_bf16 : kTileM_bf16, w_gate_up, w_down, tiles, tile_count);
     REVIVE_HIP(ctx, hipGetLastError());
   }
-  Bf16Ffn routed{x_perm, w_gate_up, nullptr, w_down, nullptr, f.h, y_perm, c.I, tiles, tile_count, 0,
+  Bf16Ffn routed{x_perm, nullptr, nullptr, f.h, y_perm, c.I, tiles, tile_count, 0,
                  max_tiles(N, ctx->P, kTileM_bf16), f.N};
   // routed and shared experts in the same two launches
-  Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, f.h_shared, y_shared, c.I_shared,
+  Bf16Ffn shared{x, w_sh_gate_up, w_sh_down, f.h_shared, y_shared, c.I_shared,
                  nullptr, nullptr, T, ceil_div(T, kTileM_bf16), T};
   const Bf16Ffn* second = y_shared ? &shared : nullptr;
   return tall ? bf16_ffn<kTallM_bf16, GU, DN>(ctx, routed, second, stream) : bf16_ffn<kTileM_bf16, GU, DN>(ctx, routed, second, stream);
@@ -369,7 +365,7 @@ int launch_shared_ffn(revive_ctx* ctx, const void* x, const void* w_sh_gate_up, 
   // Always the small workgroups: the down projection has few output columns however wide the shared expert is
   // (H = 1024, 1 token, I_shared = 32 000: 107 us against 173, 65 536: 217 against 351).
   if (T <= kStreamDenseRows) return stream_ffn_as<4, 2, 4, 2, SGU, SDN>(ctx, f, stream);
-  Bf16Ffn shared{x, nullptr, w_sh_gate_up, nullptr, w_sh_down, h_shared, y_shared, c.I_shared, nullptr, nullptr, T, ceil_div(T, kTileM_bf16), T};
+  Bf16Ffn shared{x, w_sh_gate_up, w_sh_down, h_shared, y_shared, c.I_shared, nullptr, nullptr, T, ceil_div(T, kTileM_bf16), T};
   return bf16_ffn<kTileM_bf16, SGU, SDN>(ctx, shared, nullptr, stream);
 }
 

@@ -54,9 +54,7 @@ constexpr int kWeightTileK = 32;
 struct GemmArgs {
   const void* A;             // [rows, K] bf16
   int64_t lda;               // elements between rows of A
-  const void* const* B_tab;  // device table: group -> [n_rows_B, K] bf16, or null
-  const void* B_one;         // used for every group when B_tab is null
-  int64_t ldb;               // elements between rows of B
+  const void* B;             // dense: [n_rows_B, K] bf16 in the tiled weight layout (see kWeightTileRows); grouped: the tile records have it
   void* C;                   // [rows, n_out] bf16
   int64_t ldc;
   int n_out;                 // output columns (SwiGLU: I, with B holding 2*I rows)
@@ -65,9 +63,8 @@ struct GemmArgs {
   const int32_t* tile_count; // device count of valid entries in `tiles`
   int M;                     // dense case: number of rows
   int n_col_tiles;
-  int b_sel;                 // -1: weights from B_tab / B_one; 0 or 1: from the tile record's w[b_sel]
-  int b_tiled;               // B is stored in the tiled weight layout (see kWeightTileRows)
-  int b_rows_pad;            // tiled: rows of B (of each half for SwiGLU) padded to whole tiles
+  int b_sel;                 // grouped: which of the tile record's two matrices
+  int b_rows_pad;            // rows of B (of each half for SwiGLU) padded to whole tiles
   int a_rows;                // > 0: A is stored K-panel-major, [K/32][a_rows][32]: the 32 K-elements of a row that one
                              // K-step needs are 64 contiguous bytes and consecutive rows follow each other, so the
                              // copies of a row-tile read one contiguous run per K-step (used for the intermediate h)
@@ -158,7 +155,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   constexpr int TM0 = BM0 / WAVES_M / 16;
   static_assert(TM0 == 8 && (BM == BM0 || TM == TM0 + 2), "row sub-tile dispatch below");
   static_assert(EPI != EPI_SWIGLU || TN % 2 == 0, "SwiGLU needs gate and up tiles in one wave");
-  typedef __attribute__((address_space(1))) const void* gptr;
   typedef __attribute__((address_space(3))) void* lptr;
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -233,11 +229,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
       }
     }
     tile_span(t.group_begin, t.group_end, in_group, j, row_begin, row_end);
-    Bbase = static_cast<const unsigned char*>(g.b_sel >= 0 ? t.w[g.b_sel] : (g.B_tab ? g.B_tab[t.group] : g.B_one));
+    Bbase = static_cast<const unsigned char*>(t.w[g.b_sel]);
   } else {
     row_begin = m_idx * BM0;
     row_end = min(g.M, row_begin + BM0);
-    Bbase = static_cast<const unsigned char*>(g.B_one);
+    Bbase = static_cast<const unsigned char*>(g.B);
   }
   const unsigned char* Abase = static_cast<const unsigned char*>(g.A);
   const int n0 = n_idx * BN_OUT;
@@ -266,28 +262,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
                                : static_cast<uint32_t>((static_cast<int64_t>(rrow) * g.lda + chunk * 8) * 2);
       cp_dst[i] = blk * 1024;
     } else {
-      if (g.b_tiled) {
-        // padded row index of this LDS row in the tiled matrix (gate half first, then up half)
-        int R;
-        if (EPI == EPI_SWIGLU) {
-          const int half = row >= BN / 2;
-          R = min(n0 + row - half * (BN / 2), g.b_rows_pad - 1) + half * g.b_rows_pad;
-        } else {
-          R = min(n0 + row, g.b_rows_pad - 1);
-        }
-        const int64_t panel = static_cast<int64_t>(R / kWeightTileRows) * (g.K / kWeightTileK) * kWeightTileRows;
-        cp_off[i] = static_cast<uint32_t>(((panel + (R % kWeightTileRows)) * kWeightTileK + chunk * 8) * 2);
+      // padded row index of this LDS row in the tiled matrix (gate half first, then up half)
+      int R;
+      if (EPI == EPI_SWIGLU) {
+        const int half = row >= BN / 2;
+        R = min(n0 + row - half * (BN / 2), g.b_rows_pad - 1) + half * g.b_rows_pad;
       } else {
-        int brow;
-        if (EPI == EPI_SWIGLU) {
-          const int half = row >= BN / 2;
-          const int col = min(n0 + row - half * (BN / 2), g.n_out - 1);
-          brow = col + half * g.n_out;
-        } else {
-          brow = min(n0 + row, g.n_out - 1);
-        }
-        cp_off[i] = static_cast<uint32_t>((static_cast<int64_t>(brow) * g.ldb + chunk * 8) * 2);
+        R = min(n0 + row, g.b_rows_pad - 1);
       }
+      const int64_t panel = static_cast<int64_t>(R / kWeightTileRows) * (g.K / kWeightTileK) * kWeightTileRows;
+      cp_off[i] = static_cast<uint32_t>(((panel + (R % kWeightTileRows)) * kWeightTileK + chunk * 8) * 2);
       cp_dst[i] = BM * 64 + blk * 1024;
     }
   }
@@ -303,7 +287,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
   uint64_t base_b = uniform64(reinterpret_cast<uint64_t>(Bbase));
   // Five wait states before a copy may read a scalar register that a vector instruction wrote.
   asm volatile("s_nop 4" : "+s"(base_a), "+s"(base_b));
-  const uint32_t kstep_b = g.b_tiled ? kWeightTileRows * kWeightTileK * 2 : 64;  // bytes between K-steps of B
+  constexpr uint32_t kstep_b = kWeightTileRows * kWeightTileK * 2;  // bytes between K-steps of B
   auto issue_copy = [&](int kt, auto cp_tag) {
     const uint32_t stage = smem_lds + stage_of(kt) * STAGE;
     const uint64_t src_a = base_a + static_cast<uint64_t>(kt) * kstep_a;
