@@ -229,7 +229,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_bf16_dma_kernel(G
       }
     }
     tile_span(t.group_begin, t.group_end, in_group, j, row_begin, row_end);
-    Bbase = static_cast<const unsigned char*>(t.w[g.b_sel]);
+    Bbase = static_cast<const unsigned char*>(g.b_sel ? t.w[1] : t.w[0]);  // indexed, the record would go through private scratch
   } else {
     row_begin = m_idx * BM0;
     row_end = min(g.M, row_begin + BM0);
