@@ -108,7 +108,7 @@ __device__ __forceinline__ float silu_f32(float z) { return z * __builtin_amdgcn
 // workgroup barrier, placed before the second half of the row sub-tiles' MFMAs so that the first
 // fragment reads of the next stage overlap them.
 //
-// What bounds it on large problems is power: the clock falls to 1.4 to 1.6 GHz under it.  Hence the
+// What bounds it on large problems is power: the clock falls to 1.5 to 1.7 GHz under it.  Hence the
 // MFMA that costs least for a product, 16x16x32 (it reads and writes half the accumulators of
 // 32x32x16 per multiplication; the sums are the same bits), and an order in which each MFMA shares
 // an operand with the one before.  And sub-tiles of 16 rows pad a ragged row-tile less.  TFLOP/s of
@@ -116,8 +116,9 @@ __device__ __forceinline__ float silu_f32(float z) { return z * __builtin_amdgcn
 // dense 8192 x 7168 x 4096 with SwiGLU 1289, 1400, 1429 (1318 and 1476 in another run); gate/up of
 // 414 slots of 640 to 740 rows, K = 7168, 1111, 1124, 1162, 1196, down 1068, 1095, 1130, 1154; of 261
 // slots of 230 to 290 rows 986 and 1025, 964 and 1000; of 63 slots of 350 to 430 rows, K = 2048 and
-// 1408, 865 and 887, 800 and 838.  4 x 2 wavefronts (64 x 128 each) are 1 % faster on the dense shape
-// and 2 to 4 % slower on slots; 2 x 2 wavefronts 10 % slower; weights kept over the row sub-tiles
+// 1408, 865 and 887, 800 and 838.  By counters, 414 slots of 293 to 830 rows, K = 7168, gate/up with 32x32x16 and as it is:
+// 1.37 and 1.55 GHz, matrix cores busy in 79 and 73 % of the cycles, 15.7 and 14.7 ms.
+// 4 x 2 wavefronts (64 x 128 each) are 1 % faster on the dense shape and 2 to 4 % slower on slots; 2 x 2 wavefronts 10 % slower; weights kept over the row sub-tiles
 // beat activations kept over the column tiles by 1 %.
 //
 // LDS layout of a stage: row r at r*64 bytes, its four 16-byte chunks stored at chunk ^ ((r>>2)&3):

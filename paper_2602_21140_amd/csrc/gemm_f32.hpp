@@ -9,12 +9,16 @@
 // step, with the loads of D steps in flight in registers.  A lane's 16 LDS bytes are four consecutive
 // K-elements of its row and feed four MFMAs (both operands permute K alike).  The matrix cores are what
 // bounds a full tile (16 MFMAs of 32 cycles per 16 K-elements and wavefront against 160 to 192 cycles of
-// LDS for the whole workgroup); a tile of few rows is bound by latency.  D = 4 was 5 % slower on full tiles
-// (224 registers, one workgroup per CU less) and no faster on the others; loads issued a step earlier gained nothing.
+// LDS for the whole workgroup); a tile of few rows is bound by latency.  D = 4 takes 216 registers with SwiGLU, one
+// workgroup per CU less, and is 1 to 19 % slower there (2181 tokens, H = 88, I = 1288, 256 experts, k = 4: 211 -> 250 us;
+// 3952 tokens, H = 312, I = 168: 113 -> 129); tiles of up to 16 rows gain where a CU has several of them (7 tokens, H =
+// 296, I = 1188, 128 experts, k = 8: 68 -> 52 us; 10 tokens, H = 368, I = 1928: 66 -> 54) and nothing where it has one
+// (5 tokens, H = 1144, I = 80: 28).  D = 2 throughout.  Loads issued a step earlier gained nothing.
 // Vector instructions between the MFMAs cost as well: a thread keeps 32-bit offsets from wavefront-uniform bases and
 // LDS addresses that are the same in every step, and copies only as many rows as the tile has sub-tiles.  Routed and
 // shared expert, H = 1024, I = 512, 32 experts, k = 4: 200 tokens 91 -> 82 us, 1001 tokens 199 -> 184, 4000 tokens
-// 580 -> 557 (113 TFLOP/s).  What is left at 1001 tokens is balance: a CU's three workgroups hold 7 to 13 sub-tiles.
+// 580 -> 557 (113 TFLOP/s).  What is left at 1001 tokens is balance: of gate/up's 800 workgroups, of one to four sub-tiles
+// each, 768 fit at once (48 KiB of LDS, three to a CU), and CUs end between 81 and 132 us.
 // Narrower workgroups spread better and lose more by reading the activations twice as often (1001 tokens 195 us; of
 // two wavefronts, 239, since they load the SIMDs unevenly).
 //
