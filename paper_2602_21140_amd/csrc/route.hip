@@ -22,6 +22,7 @@ struct RouteParams {
   float* topk_weight;
   int32_t* topk_phys;
   int T, E, k, max_replicas, score_fn, n_group, topk_group;
+  int none;            // expert that route_topk_kernel gives a row of NaN, which holds no best key
   long long t_offset;  // index of token 0 within the whole batch
   float route_scale;
 };
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(RouteParams p) {
     }
   }
 
-  my_e = min(my_e, p.E - 1);  // a row of NaN holds no best key but the -inf of lanes without an expert: its ids stay valid
+  my_e = min(my_e, p.E - 1);  // a row of NaN holds no best key but the -inf of lanes without an expert (RouteParams::none)
 
   // weights: score of the chosen expert over the sum of the chosen scores
   const int t = t0 + my_q;
@@ -356,8 +357,7 @@ __global__ __launch_bounds__(256) void route_topk_rows_kernel(RouteParams p) {
       at = min(min(part[0], part[1]), min(part[2], part[3]));
     }
     const int mine = at < V ? expert(at) : kNone, e = row_min(mine);
-    // No key is the best one in a row of NaN: its ids stay valid.
-    if (mine == e) chosen[wave][row][j] = {min(e, p.E - 1), best};
+    if (mine == e) chosen[wave][row][j] = {e == kNone ? p.none : e, best};  // kNone: no key is the best one in a row of NaN
     at = mine == e ? at : V;
 #pragma unroll
     for (int i = 0; i < V; ++i) key[i] = i == at ? NEG : key[i];
@@ -633,6 +633,8 @@ int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk
   p.score_fn = c.score_fn; p.n_group = c.n_group; p.topk_group = c.topk_group;
   p.route_scale = c.route_scale;
   p.t_offset = ctx->token_offset;
+  const int vals = ceil_div(c.E, 64), held = vals <= 2 ? vals : vals <= 4 ? 4 : vals <= 6 ? 6 : 8;  // experts per lane of route_topk_kernel
+  p.none = c.E == held * 64 ? 0 : c.E - 1;
   KernelTimer timer(ctx, REVIVE_K_ROUTE_TOPK, stream);
   if (selects_by_rows(T, c.E, c.n_group, c.k)) {
     const int n = ceil_div(c.E, 16);
@@ -656,17 +658,16 @@ int launch_route_topk(revive_ctx* ctx, const float* logits, int T, int32_t* topk
   // Few tokens, other groups, more choices.
   const bool four = selects_four_tokens(T, c.n_group, c.k);
   const dim3 grid(ceil_div(T, four ? 16 : 4)), block(256);
-  const int vals = ceil_div(c.E, 64);
 #define REVIVE_ROUTE_LAUNCH(V)                                                                                       \
   do {                                                                                                               \
     if (four) hipLaunchKernelGGL((route_topk_kernel<V, 4, true>), grid, block, 0, stream, p);                        \
     else if (c.n_group > 1) hipLaunchKernelGGL((route_topk_kernel<V, 1, true>), grid, block, 0, stream, p);          \
     else hipLaunchKernelGGL((route_topk_kernel<V, 1, false>), grid, block, 0, stream, p);                            \
   } while (0)
-  if (vals <= 1) REVIVE_ROUTE_LAUNCH(1);
-  else if (vals <= 2) REVIVE_ROUTE_LAUNCH(2);
-  else if (vals <= 4) REVIVE_ROUTE_LAUNCH(4);
-  else if (vals <= 6) REVIVE_ROUTE_LAUNCH(6);
+  if (held == 1) REVIVE_ROUTE_LAUNCH(1);
+  else if (held == 2) REVIVE_ROUTE_LAUNCH(2);
+  else if (held == 4) REVIVE_ROUTE_LAUNCH(4);
+  else if (held == 6) REVIVE_ROUTE_LAUNCH(6);
   else REVIVE_ROUTE_LAUNCH(8);
 #undef REVIVE_ROUTE_LAUNCH
   return check_hip(ctx, hipGetLastError(), "route_topk launch");

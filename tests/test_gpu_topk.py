@@ -131,3 +131,32 @@ def test_row_of_nan_keeps_valid_ids(E, n_group, k, T):
     assert (top2[bad] >= 0).all() and (top2[bad] < E).all()
     assert np.array_equal(phys2, E - 1 - top2)
     L.close()
+
+
+# What NaN leave of a row is chosen alike by every kernel: a row that keeps fewer experts than it chooses, or none, takes the
+# same ones in a call of many tokens and in one of few.
+@pytest.mark.parametrize("T", [96, 8193, 16400])
+@pytest.mark.parametrize("E,n_group,topk_group,k", [(16, 1, 1, 2), (61, 1, 1, 3), (64, 8, 4, 8), (256, 2, 2, 16), (384, 8, 8, 3), (500, 1, 1, 8), (512, 1, 1, 16), (120, 5, 2, 2)])
+def test_rows_of_nan_do_not_depend_on_the_token_count(E, n_group, topk_group, k, T):
+    cfg = SimpleNamespace(T=T, H=64, E=E, k=k, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+                          score_fn="sigmoid", n_group=n_group, topk_group=topk_group, dtype="bf16")
+    L = ReviveLayer(cfg)
+    L.set_placement(np.arange(E, dtype=np.int32))
+    L.update_map(np.zeros(1, dtype=np.uint8))
+    gen = torch.Generator().manual_seed(E + k)
+    z = torch.randn(T, E, generator=gen)
+    kind = torch.arange(T) % 4
+    z[kind == 1] = float("nan")
+    z[(torch.rand(T, E, generator=gen) < 0.3) & (kind == 2)[:, None]] = float("nan")
+    few = kind == 3  # fewer than k left, of one group
+    keep = torch.randint(0, E // n_group, (T,), generator=gen)
+    left = z[torch.arange(T), keep].clone()
+    z[few] = float("nan")
+    z[torch.arange(T)[few], keep[few]] = left[few]
+    z = z.cuda()
+    _, *many = L.route(None, None, T, logits=z, logits_given=True)
+    for t0 in (0, (T - 12) // 2 & ~3, T - 12):
+        _, *some = L.route(None, None, 12, logits=z[t0:t0 + 12].contiguous(), logits_given=True)
+        for a, b in zip(many, some):  # a weight's NaN has no sign that would say anything
+            assert torch.equal(a[t0:t0 + 12].nan_to_num(nan=-1.0), b.nan_to_num(nan=-1.0)), t0
+    L.close()
