@@ -12,7 +12,7 @@
 #include <algorithm>
 
 #include "gemm_bf16.hpp"
-#include "gemm_f32.hpp"
+#include "gemm_f32_split.hpp"
 #include "gemm_stream.hpp"
 
 namespace revive {
@@ -312,7 +312,7 @@ int f32_gemm(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
     a.grouped.B_tab = gu ? f.w_gate_up : f.w_down;
   }
   KernelTimer timer(ctx, KID, stream);
-  return launch_gemm_f32<SWIGLU>(ctx, a, stream);
+  return launch_gemm_f32_split<SWIGLU>(ctx, a, stream);
 }
 
 template <int K_GATE_UP, int K_DOWN>

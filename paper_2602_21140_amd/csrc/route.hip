@@ -576,8 +576,7 @@ int router_one_sequence(revive_ctx* ctx, const void* x, const void* w, float* lo
 // Many tokens in fp32, K in the router kernel's slices.  The number of experts is a multiple of 4.
 int router_gemm_f32(revive_ctx* ctx, const void* x, const void* w, float* logits, int T, hipStream_t stream) {
   const revive_config& c = ctx->cfg;
-  GemmF32Args a{};
-  GemmF32Problem& p = a.dense;
+  GemmF32Problem p{};
   p.A = static_cast<const float*>(x); p.lda = c.H;
   p.B_one = static_cast<const float*>(w); p.ldb = c.H;
   p.C = logits; p.ldc = c.E;
@@ -585,7 +584,7 @@ int router_gemm_f32(revive_ctx* ctx, const void* x, const void* w, float* logits
   p.n_col_tiles = ceil_div(c.E, kTileN_f32);
   p.blocks = ceil_div(T, kTileM_f32) * p.n_col_tiles;
   p.M = T;
-  return launch_gemm_f32<false, kRouterSlices>(ctx, a, stream);
+  return launch_gemm_f32<kRouterSlices>(ctx, p, stream);
 }
 
 }  // namespace

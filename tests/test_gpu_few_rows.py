@@ -126,6 +126,56 @@ def test_fp32_row_tiles(H, I, shared):
     L.close()
 
 
+# fp32 on the bf16 matrix cores, at every number of 16-row sub-tiles and K-steps from one up, even and odd, full and not.
+# Rows and weights whose bf16 parts are no numbers (the largest fp32 values, infinities, NaN) go through sums in fp32; the
+# other rows of their tiles keep their bits.
+@pytest.mark.parametrize("H,I", [(16, 8), (32, 36), (40, 64), (96, 100), (1024, 512)])
+@pytest.mark.parametrize("rows", [1, 16, 17, 33, 64, 65])
+def test_fp32_parts_and_numbers_without_parts(H, I, rows):
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    cfg = SimpleNamespace(T=2 * rows, H=H, E=2, k=1, I=I, I_shared=0, n_ranks=2, slots_per_rank=1, max_replicas=1,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype="fp32")
+    L = ReviveLayer(cfg)
+    g, u, d = (torch.randn(*s, generator=gen, device="cuda") * s[0] ** -0.5 for s in ((H, I), (H, I), (I, H)))
+    g[5] *= 2e-38
+    u[5] *= 2e-38
+    gu, dn = pack_expert(g, u, d)
+    L.set_expert_weights([gu, gu], [dn, dn])
+    x = torch.randn(2 * rows, H, generator=gen, device="cuda")
+    off = torch.tensor([0, rows, 2 * rows], dtype=torch.int32, device="cuda")
+
+    def run():
+        y = L.empty(2 * rows, H).fill_(-7.0)
+        L.expert_ffn(x, off, 2 * rows, out=(y, None))
+        torch.cuda.synchronize()
+        return y
+
+    def reference():
+        z, w = x.double() @ g.double(), x.double() @ u.double()
+        return (torch.nn.functional.silu(z) * w) @ d.double()
+
+    plain, ref = run(), reference()
+    # a K-step rounds each sum once, by 2^-24 at most, in each of three products, which a small I does not average over
+    bound = 2.0 ** -24 * ((H + 31) // 32) ** 0.5 * 3
+    assert float((plain - ref).norm() / ref.norm()) < max(bound, 4e-7)
+    largest, nan = rows // 2, rows + rows // 2
+    x[largest, 5] = torch.finfo(torch.float32).max  # no finite bf16 is as large; times 2e-38 it is an ordinary number
+    x[nan, 7] = float("nan")
+    got, ref = run(), reference()
+    keep = torch.ones(2 * rows, dtype=torch.bool, device="cuda")
+    keep[[largest, nan]] = False
+    assert torch.equal(got[keep], plain[keep])
+    assert float((got[largest] - ref[largest]).norm() / ref[largest].norm()) < 1e-5  # sums in fp32, as above
+    assert bool(got[nan].isnan().all())
+    x[nan, 7] = float("inf")  # h is inf, -inf or (where the gate is -inf) NaN
+    z, w = x[nan].double() @ g.double(), x[nan].double() @ u.double()
+    h = torch.nn.functional.silu(z) * w
+    y = h @ d.double()
+    got = run()[nan]
+    assert torch.equal(got.isnan(), y.isnan()) and torch.equal(got[~y.isnan()].double(), y[~y.isnan()])
+    L.close()
+
+
 # The kernels that share the work by rows per slot give the same bits: a whole batch and its microbatches may take
 # different ones.  The same slots with other slots beside them: weights streamed, row-tiles of up to 256, of up to 320
 # rows; the shared expert in the same calls and alone.
