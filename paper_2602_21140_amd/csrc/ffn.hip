@@ -265,22 +265,31 @@ template <int K_GATE_UP, int K_DOWN>
 int stream_ffn(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
   const revive_config& c = ctx->cfg;
   const int64_t used = f.N < ctx->P ? f.N : ctx->P;  // slots that can hold a row
-  // Above 8 rows per slot some slots hold more than 64: row-tiles of 128 then read those slots' weights once
-  // (28 uneven rows per slot: gate/up 2.95 -> 2.52 ms), at one workgroup less per CU.  Where that leaves a quarter
-  // of the CUs without work and the cache holds the weights, which may then be read again, the small tiles are better:
-  // 16 rows per slot, 32 slots, H = 2048, I = 448 (128 workgroups) 41 us with tiles of 128, 35 with tiles of 64 (38
-  // with the 256-row kernel); with a shared expert of 4 I and 128 tokens 77, 51 (62).  From 192 workgroups of the
-  // smaller launch on either may win (150 slots, H = 256, I = 384, 14 rows: 21 and 25).
-  if (f.N > 8 * ctx->P || f.T > 128) {
-    const int64_t dense = ceil_div(f.T, 128);
+  const int64_t blocks = (used + (f.T > 0)) * ceil_div(c.I, stream_tile_n<2, 4, EPI_SWIGLU>);  // of gate/up, 64 columns each
+  // us of the FFN with other data in the caches, both sides on the same weights in one process (from one process to the next
+  // they differ by 4 %), layers of 72 slots, H = 2048, I = 1408 (m), 144, 4096, 1024 (q), 72, 1024, 512 (s), 288, 7168, 2048
+  // (d), 160, 5120, 1536 (u).
+  //
+  // Above 20 rows per slot some slots hold more than 64 and row-tiles of 128 then read those slots' weights once, at one
+  // workgroup less per CU; and where many rows of the shared expert would read its weights a quarter as often as the slots
+  // read theirs.  Tiles of 128 and of 64: 5.3 rows d 3935 and 3856, q 551 and 544; 8.3 rows q 580 and 551, s 70 and 58; 16.7
+  // rows m 249 and 240, q 590 and 570; 25 rows m 256 and 249; 33 rows q 624 and 635; 66.7 rows m 292 and 351.  Where they
+  // leave a quarter of the CUs without work and the cache holds the weights, which may then be read again, the small tiles
+  // are better: 16 rows per slot, 32 slots, H = 2048, I = 448 (128 workgroups) 41 and 35.  One or two tiles of 128 columns
+  // cover a narrow expert exactly and read its activations half as often (I = 128, 18.2 rows 250 and 279, 256, 10.1 rows 279
+  // and 299, but 192, 18 rows 248 and 231): there from 8 rows on.
+  const int rows_128 = c.I % 128 == 0 && c.I < 512 ? 8 : 20;
+  const int dense = ceil_div(f.T, 128);
+  if (f.N > rows_128 * ctx->P || (f.T > 128 && 8ll * dense * c.I_shared > used * c.I)) {
     const int64_t gate_up = used * ceil_div(c.I, stream_tile_n<4, 4, EPI_SWIGLU>) + dense * ceil_div(c.I_shared, stream_tile_n<4, 4, EPI_SWIGLU>);
     const int64_t down = (used + dense) * ceil_div(c.H, stream_tile_n<4, 4, EPI_BF16>);
     if (!weights_cached(ctx) || (gate_up >= 192 && down >= 192)) return stream_ffn_as<8, 4, 2, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
   }
-  // Fewer than two workgroups per CU: half as large ones spread the streams evenly over the CUs, and a CU
-  // alone does not pull more than about 38 GB/s from HBM (one token, 288 -> 576 workgroups: 110 -> 95 us).
-  const int64_t blocks = (used + (f.T > 0)) * ceil_div(c.I, stream_tile_n<2, 4, EPI_SWIGLU>);
-  if (blocks < 2 * 256) return stream_ffn_as<4, 2, 4, 2, K_GATE_UP, K_DOWN>(ctx, f, stream);
+  // Fewer than two workgroups per CU: half as large ones spread the streams evenly over the CUs, and a CU alone does not
+  // pull more than about 38 GB/s from HBM (one token, 288 -> 576 workgroups: 110 -> 95 us).  Up to four where the products
+  // are long: m 0.3 rows (550) 99 and 87; d 0.1 rows (544) 281 and 255; u 0.1 rows (600) 202 and 195; but H = 3840, I =
+  // 768, 0.7 rows (672) 98 and 102, H = 1920, I = 192 (648) 63.5 and 65.3, and d 0.1 rows (1056) 447 and 458.
+  if (blocks < 512 || (blocks < 1024 && std::min(c.H, c.I) >= 512 && c.H <= 4 * c.I)) return stream_ffn_as<4, 2, 4, 2, K_GATE_UP, K_DOWN>(ctx, f, stream);
   return stream_ffn_as<4, 2, 4, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
 }
 

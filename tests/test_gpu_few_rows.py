@@ -30,6 +30,10 @@ CASES = {
     "sub_tiles": (256, 192, SUB_TILES), "sub_tiles_tall": (1088, 448, SUB_TILES),
     # slots of many row-tiles, which a common height would leave with a row or a sub-tile in the last; the same streamed
     "many_tiles": (256, 192, [4097, 3601, 513, 0, 1]), "many_tiles_streamed": (704, 320, [4097, 1041] + [0] * 330),
+    # half the columns up to 1024 workgroups, tiles of 64 rows above 8 rows per slot, of 128 above 20, and for many rows of the shared expert
+    "half_columns": (1024, 1024, [1, 0, 63, 64, 65] + [2] * 32), "tiles_of_64": (2048, 576, [129, 64, 65, 1, 17] + [9] * 25),
+    "tiles_of_128": (2048, 576, [129, 128, 127, 257, 1] + [17] * 25),
+    "rows_shared": (1024, 1024, [140, 3] + [1] * 32 + [0] * 4),
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
