@@ -182,7 +182,7 @@ constexpr int kStreamRowsPerSlot = 96, kStreamRowsPerSlotCached = 16;
 constexpr int64_t kCachedWeights = 192ll << 20;
 constexpr int kStreamDenseRows = 128;
 
-// A streaming workgroup looks its row-tile up in all slots' offsets, 256 at a time; the 256-row kernel has a list.
+// A streaming workgroup looks its row-tile up in all slots' offsets; the 256-row kernel has a list.
 constexpr int kStreamSlotsCached = 640, kStreamSlots = 768;
 
 bool weights_cached(const revive_ctx* ctx) { return static_cast<int64_t>(ctx->P) * 6 * ctx->cfg.H * ctx->cfg.I <= kCachedWeights; }
@@ -199,7 +199,8 @@ bool takes_stream(const revive_ctx* ctx, const FfnArgs& f) {
   const revive_config& c = ctx->cfg;
   const bool cached = weights_cached(ctx);
   if (f.N > static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return false;
-  // With many slots that search costs more than it saves where a workgroup has little to stream.  us of the 256-row
+  // With many slots that search costs more than it saves where a workgroup has little to stream: the figures are of a
+  // search twice as long as today's, with which streaming wins further out than these lines.  us of the 256-row
   // kernel and streamed: cached, 1000 slots, H = 256, I = 128, 4 rows per slot 54 and 73, 16 rows 57 and 64.  Geometric
   // mean of the gain over random layers.  Cached: up to 64 rows in all, 513 to 640 slots 1.00, to 768 0.91, beyond
   // 0.78; more than 256 rows, to 768 slots 1.05, beyond 0.90.  Larger weights beyond 768 slots: up to 64 rows, products

@@ -56,12 +56,12 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
     row_end = min(g.M, row_begin + BM);
     B = g.B_one;
   } else {
-    const GridTile t = grid_tile(a.slot_offsets, a.P, BM, g.n_col_tiles, b);
+    const GridTile t = grid_tile(a.slot_offsets, a.P, BM, g.n_col_tiles, b, g.B_tab);
     if (t.group < 0) return;
     n_idx = t.n_idx;
     row_begin = t.row_begin;
     row_end = t.row_end;
-    B = static_cast<const float*>(g.B_tab[t.group]);
+    B = static_cast<const float*>(t.w);
   }
   const int n0 = n_idx * BN, rows = row_end - row_begin;
   const int tid = threadIdx.x, lane = tid & 63;

@@ -67,12 +67,12 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_bf16_stream_kernel(StreamArgs
     B = static_cast<const unsigned char*>(g.B_one);
     once = g.M <= 16 * TMX;
   } else {
-    const GridTile t = grid_tile(a.slot_offsets, a.P, 16 * TMX, g.n_col_tiles, b);
+    const GridTile t = grid_tile(a.slot_offsets, a.P, 16 * TMX, g.n_col_tiles, b, g.B_tab);
     if (t.group < 0) return;
     n_idx = t.n_idx;
     row_begin = t.row_begin;
     row_end = t.row_end;
-    B = static_cast<const unsigned char*>(g.B_tab[t.group]);
+    B = static_cast<const unsigned char*>(t.w);
     once = t.in_group == 1;
   }
   const int tid = threadIdx.x;

@@ -130,6 +130,31 @@ def test_fp32_row_tiles(H, I, shared):
     L.close()
 
 
+# A workgroup finds its row-tile among the slots by itself: a lane adds up ceil(P / 64) of them.
+@pytest.mark.parametrize("P", [1, 2, 63, 64, 65, 127, 128, 129, 320, 321, 961, 1024])
+def test_row_tiles_among_the_slots(P):
+    H, I = 16, 8
+    rng = np.random.default_rng(P)
+    for fill in (0.05, 0.5, 1.0):  # share of the slots that have rows, in one to three row-tiles
+        counts = np.where(rng.random(P) < fill, rng.integers(1, 150 if P < 100 else 8, P), 0)
+        counts[rng.integers(P)] = 130
+        N = int(counts.sum())
+        cfg = SimpleNamespace(T=N, H=H, E=min(P, 512), k=1, I=I, I_shared=0, n_ranks=P, slots_per_rank=1, max_replicas=2,
+                              score_fn="softmax", n_group=1, topk_group=1, dtype="fp32")
+        L = ReviveLayer(cfg)
+        gen = torch.Generator(device="cuda").manual_seed(P)
+        gu, dn = torch.randn(P, 2 * I, H, generator=gen, device="cuda"), torch.randn(P, H, I, generator=gen, device="cuda")
+        L.set_expert_weights([gu[p] if c else None for p, c in enumerate(counts)], [dn[p] if c else None for p, c in enumerate(counts)])
+        x, y = torch.randn(N, H, generator=gen, device="cuda"), L.empty(N, H).fill_(float("nan"))
+        off = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+        L.expert_ffn(x, off, N, out=(y, None))
+        slot = torch.from_numpy(np.repeat(np.arange(P), counts)).cuda()
+        z = (gu[slot].double() * x.double()[:, None, :]).sum(2)
+        ref = (dn[slot].double() * (torch.nn.functional.silu(z[:, :I]) * z[:, I:])[:, None, :]).sum(2)
+        assert float((y - ref).abs().max() / ref.abs().max()) < 1e-5, fill  # sums of at most 16 fp32 products
+        L.close()
+
+
 # fp32 on the bf16 matrix cores, at every number of 16-row sub-tiles and K-steps from one up, even and odd, full and not.
 # Rows and weights whose bf16 parts are no numbers (the largest fp32 values, infinities, NaN) go through sums in fp32; the
 # other rows of their tiles keep their bits.
