@@ -259,8 +259,11 @@ class ReviveLayer:
 
     @staticmethod
     def _stream(stream: Optional[torch.cuda.Stream]) -> int:
-        s = torch.cuda.current_stream() if stream is None else stream
-        return s.cuda_stream
+        if stream is not None:
+            return stream.cuda_stream
+        # the current device's current stream, without the Stream object that torch.cuda.current_stream() makes: that took
+        # 2.6 us of each call, half of an eager step of few tokens (64 tokens, H = 256, fp32: 33 -> 24 us)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
     def close(self):
         if self._ctx:

@@ -466,3 +466,13 @@ def test_a_masked_expert_with_a_towering_logit_leaves_the_weights_finite(name):
         assert np.array_equal(_i(top_p), orc.remap(ref_l, m))
     finally:
         g.close()
+
+
+def test_calls_without_a_stream_take_the_current_one():
+    from paper_2602_21140_amd import ReviveLayer
+
+    side = torch.cuda.Stream()
+    assert ReviveLayer._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert ReviveLayer._stream(None) == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert ReviveLayer._stream(side) == side.cuda_stream and ReviveLayer._stream(None) != side.cuda_stream
