@@ -266,3 +266,19 @@ def test_hand_worked_dispatch_example_on_the_gpu():
         assert torch.equal(x_perm, g.x[torch.tensor([int(v) // cfg.k for v in rows["src_of"].split()], device=g.device)])
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 2047, 2048, 2049, 4097, 70001])
+def test_activation_counts_of_any_number_of_ids(n):
+    from types import SimpleNamespace
+
+    from paper_2602_21140_amd import ReviveLayer
+    E = 24
+    L = ReviveLayer(SimpleNamespace(T=n, H=64, E=E, k=1, I=64, I_shared=0, n_ranks=1, slots_per_rank=E, max_replicas=1,
+                                    score_fn="softmax", n_group=1, topk_group=1, dtype="bf16"))
+    ids = torch.randint(-2, E + 2, (n, 1), generator=torch.Generator().manual_seed(n), dtype=torch.int32)
+    counts = torch.arange(E, dtype=torch.int64, device="cuda")
+    L.expert_counts(ids.cuda(), n, counts=counts)
+    inside = ids[(ids >= 0) & (ids < E)].long()
+    assert torch.equal(counts.cpu(), torch.arange(E) + torch.bincount(inside, minlength=E))  # ids of no expert do not count
+    L.close()
