@@ -289,7 +289,8 @@ int stream_ffn(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
   // Fewer than two workgroups per CU: half as large ones spread the streams evenly over the CUs, and a CU alone does not
   // pull more than about 38 GB/s from HBM (one token, 288 -> 576 workgroups: 110 -> 95 us).  Up to four where the products
   // are long: m 0.3 rows (550) 99 and 87; d 0.1 rows (544) 281 and 255; u 0.1 rows (600) 202 and 195; but H = 3840, I =
-  // 768, 0.7 rows (672) 98 and 102, H = 1920, I = 192 (648) 63.5 and 65.3, and d 0.1 rows (1056) 447 and 458.
+  // 768, 0.7 rows (672) 98 and 102, H = 1920, I = 192 (648) 63.5 and 65.3, and d 0.1 rows (1056) 447 and 458.  How full the last
+  // round is moves either by 5 %: H = 6848, I = 1920, 36 slots, 6 tokens 174 and 155, 10 tokens 204 and 206, uneven 188 and 197.
   if (blocks < 512 || (blocks < 1024 && std::min(c.H, c.I) >= 512 && c.H <= 4 * c.I)) return stream_ffn_as<4, 2, 4, 2, K_GATE_UP, K_DOWN>(ctx, f, stream);
   return stream_ffn_as<4, 2, 4, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
 }
