@@ -4,13 +4,16 @@
 // belong to one group, and an optional fused SwiGLU (B holds gate rows then up rows).
 //
 // An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits, each the rounded rest of the one before), and
-// products of bf16 numbers are exact in fp32.  Six of the nine partial products are taken; those left out are below
-// 2^-25 of the product.  The leading one is summed on its own, the other five, a hundredth of it, beside it, so that
+// products of bf16 numbers are exact in fp32.  Six of the nine partial products are taken; two of those left out may reach
+// 2^-25 of the product each.  The leading one is summed on its own, the other five, a hundredth of it, beside it, so that
 // what they lose to rounding does not show.  Against 64 bits (2-norm) sums of 1024 products then FFN: 3.2e-7, where
 // v_mfma_f32_16x16x4_f32 gives 9.6e-7; of 256: 1.6e-7 and 4.8e-7 (with all six in one sum 8.2e-7 and 3.8e-7).  A K-step
 // of 32 takes 6 x 16 cycles of the matrix cores for 16 x 16 outputs, instead of 8 x 32.
-// The parts of numbers below 2^-110 are denormal and lose bits.  A number that rounds to no finite bf16, or is not
-// finite itself, makes its sums NaN: outputs whose sums are not finite are worked out again in fp32 (redo).
+// The parts of numbers below 2^-110 are denormal (the matrix cores keep those) and lose up to 2^-134 of them: a sum of K
+// products up to K 2^-134 times the largest numbers of its two rows together.  Sums that are not 2^22 times as large, and
+// not of zeros, are worked out again in fp32 (redo); so are those that are not finite, since a number that rounds to no
+// finite bf16, or is not finite itself, makes its sums NaN.  With numbers in ordinary ranges neither occurs.  To know the
+// largest numbers costs 2 % (layer of 1001 tokens, H = 1024, I = 512, 32 experts: 169.6 -> 173.6 us).
 //
 // 64 x 64 outputs per workgroup of four wavefronts, each with all the tile's rows and 16 output columns (SwiGLU: 16 gate
 // and 16 up), so that a tile of few rows keeps every wavefront equally busy and skips the 16-row sub-tiles it has not
@@ -26,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
+#include <cmath>
 #include <type_traits>
 
 #include "gemm_bf16.hpp"
@@ -44,6 +48,7 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
   constexpr int NB = W * BN * 8 / 256;           // 16-byte words of weights per thread and K-step
   constexpr int PLANE = (BM + W * BN) * 64;      // bytes of one of the three parts of a step: rows of 32 bf16
   __shared__ __attribute__((aligned(16))) unsigned char lds[2][3 * PLANE];
+  __shared__ __attribute__((aligned(16))) float largest[BM + W * BN];  // magnitude in each row of the tile and of the weights
   const bool dense = blockIdx.x < static_cast<unsigned>(a.dense.blocks);
   const GemmF32Problem g = dense ? a.dense : a.grouped;
   const int b = dense ? blockIdx.x : blockIdx.x - a.dense.blocks;
@@ -81,6 +86,8 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
   const gptr b_base[2] = {base(B + n0 * g.ldb), base(B + (static_cast<int64_t>(n0) + g.n_out) * g.ldb)};
   auto run = [&](auto tm_tag) {
     constexpr int TM = decltype(tm_tag)::value;
+    // keeps the four forms' beginnings apart: shared, they would stay in registers through the first form's loop (40 spilled)
+    asm volatile("; %0 sub-tiles" ::"n"(TM) : "memory");
     // copy plan: 16-byte word w of a step is K-chunk w % 8 of row w / 8
     constexpr int NA = (TM + 1) / 2;  // words of activations per thread and K-step: no more rows than the tile's sub-tiles hold
     constexpr int WORDS = NA + NB;
@@ -91,6 +98,9 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
 #pragma unroll
     for (int i = 0; i < BN / 32; ++i) b_off[i] = static_cast<Off>(min(i * 32 + r0, g.n_out - 1 - n0)) * static_cast<Off>(g.ldb * 4);
     f32x4 word[D][WORDS];  // of the activations, then of the weights
+    float top[WORDS];      // largest magnitude of the row's words that this thread has staged
+#pragma unroll
+    for (int u = 0; u < WORDS; ++u) top[u] = 0.f;
     auto load = [&](int kt, int d) {  // past the last K-element: the last four again
       const Off k = static_cast<Off>(min(kt * 32 + c * 4, g.K - 4)) * 4;
 #pragma unroll
@@ -105,6 +115,9 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = in ? v[j] : 0.f;
       }
+      // fmaxf() would first quieten its operands, twice the instructions
+      asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top[u]) : "v"(v[0]), "v"(v[1]));
+      asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top[u]) : "v"(v[2]), "v"(v[3]));
       unsigned char* dst = lds[buf] + put + (u < NA ? u * (32 * 64) : BM * 64 + (u - NA) * (32 * 64));
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
@@ -181,36 +194,95 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    // Once the last words are staged.  The lane's numbers are worked out here and not ahead of the loop, where they would
+    // take registers; likewise below.
+    auto late = [&]() {
+      int t = tid;
+      asm volatile("" : "+v"(t));
+      return t;
+    };
+    auto share_largest = [&]() {
+      int m[WORDS];  // not negative: in the order of the numbers
+#pragma unroll
+      for (int u = 0; u < WORDS; ++u) {
+        m[u] = __float_as_int(top[u]);
+        asm volatile("s_nop 1" : "+v"(m[u]));  // two wait states between the v_max3 above, of which the compiler may not know, and the lanes' exchange
+      }
+      // the eight threads of a row: lanes ^ 1, ^ 2 and 7 - lane
+#pragma unroll
+      for (int u = 0; u < WORDS; ++u) m[u] = max(m[u], dpp_or_zero<0xB1, 0xF>(m[u]));
+#pragma unroll
+      for (int u = 0; u < WORDS; ++u) m[u] = max(m[u], dpp_or_zero<0x4E, 0xF>(m[u]));
+#pragma unroll
+      for (int u = 0; u < WORDS; ++u) m[u] = max(m[u], dpp_or_zero<0x141, 0xF>(m[u]));
+      const int t = late();
+      if ((t & 7) == 0) {
+#pragma unroll
+        for (int u = 0; u < WORDS; ++u) largest[(u < NA ? u * 32 : BM + (u - NA) * 32) + (t >> 3)] = __int_as_float(m[u]);
+      }
+    };
     if (kt + 1 < KT) {
       step(kt, 1, 0, Y{});
+      share_largest();
       publish();
       step(kt + 1, 0, 1, F{});
     } else {
+      share_largest();
       step(kt, 0, 0, F{});
+      publish();
+    }
+    const int t = late(), r16 = t & 15, quad = t >> 4 & 3;
+    // the size from which on a sum has lost nothing that counts, in two terms; none where a row has only zeros
+    const float share = static_cast<float>(g.K) * 0x1p-112f;
+    auto term = [&](float top) { return top > 0.f ? top * share : -INFINITY; };
+    f32x4 w_term[W];
+    float w_most = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+      w_term[s] = *reinterpret_cast<const f32x4*>(&largest[BM + s * BN + wave * 16 + quad * 4]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w_most = fmaxf(w_most, w_term[s][r] = term(w_term[s][r]));
     }
     // a lane holds four consecutive output columns of activation row lane % 16
     const int col = n0 + wave * 16 + quad * 4;
-    uint32_t redo = 0;  // outputs i * 4 + r with a sum that is not finite
+    bool suspect = false;  // a sum of the lane's may not be what the parts give
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+      float least = FLT_MAX, total = 0.f;
 #pragma unroll
       for (int s = 0; s < W; ++s) {
         acc[s][i] += low[s][i];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (!(fabsf(acc[s][i][r]) <= FLT_MAX)) redo |= 1u << (i * 4 + r);
+        for (int r = 0; r < 4; ++r) {
+          const float size = fabsf(acc[s][i][r]);
+          least = fminf(least, size);
+          total += size;
+        }
       }
+      suspect |= !((total <= FLT_MAX) & (least >= term(largest[i * 16 + r16]) + w_most));
       const int row = row_begin + i * 16 + r16;
-      if (row >= row_end || col >= g.n_out) {
-        redo &= ~(15u << (i * 4));
-        continue;
-      }
+      if (row >= row_end || col >= g.n_out) continue;
       f32x4 v = acc[0][i];
       if (SWIGLU) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = v[r] / (1.0f + expf(-v[r])) * acc[W - 1][i][r];
       }
       *reinterpret_cast<f32x4*>(g.C + static_cast<int64_t>(row) * g.ldc + col) = v;  // n_out is a multiple of 4
+    }
+    if (__ballot(suspect) == 0) return;
+    uint32_t redo = 0;  // outputs i * 4 + r with a sum that the parts do not give
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const float x_term = term(largest[i * 16 + r16]);
+      uint32_t fine = 15;
+#pragma unroll
+      for (int s = 0; s < W; ++s)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float size = fabsf(acc[s][i][r]);
+          if (!((size <= FLT_MAX) & (size >= x_term + w_term[s][r]))) fine &= ~(1u << r);
+        }
+      if (row_begin + i * 16 + r16 < row_end && col < g.n_out) redo |= (fine ^ 15) << (i * 4);
     }
     while (redo) {
       const int o = __builtin_ctz(redo);

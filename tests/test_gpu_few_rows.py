@@ -205,6 +205,40 @@ def test_fp32_parts_and_numbers_without_parts(H, I, rows):
     L.close()
 
 
+# Numbers whose bf16 parts are denormal lose bits in them: outputs that those bits could show in are sums of fp32 products
+# instead.  Powers of two on x and the weights, by column of x where `column`, that leave ordinary outputs or small ones.
+@pytest.mark.parametrize("x_exp,gate_exp,up_exp,down_exp,column", [
+    (127, -127, -127, 0, True), (118, -118, -118, 0, True), (118, -118, -118, 0, False), (-118, 118, 118, 0, False),
+    (-109, 109, 109, 0, False), (0, 0, 0, -120, False), (0, 0, 0, -109, False), (-60, -60, 60, 121, False)])
+@pytest.mark.parametrize("H,I,rows", [(40, 64, 1), (96, 100, 65), (1024, 512, 33)])
+def test_fp32_small_numbers(H, I, rows, x_exp, gate_exp, up_exp, down_exp, column):
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    cfg = SimpleNamespace(T=2 * rows, H=H, E=2, k=1, I=I, I_shared=0, n_ranks=2, slots_per_rank=1, max_replicas=1,
+                          score_fn="softmax", n_group=1, topk_group=1, dtype="fp32")
+    L = ReviveLayer(cfg)
+    g, u, d = (torch.randn(*s, generator=gen, device="cuda") * s[0] ** -0.5 for s in ((H, I), (H, I), (I, H)))
+    x = torch.empty(2 * rows, H, device="cuda").uniform_(0.6, 0.9, generator=gen) * torch.randn(2 * rows, H, generator=gen, device="cuda").sign()
+    at = slice(5, 6) if column else slice(None)
+    for t, e in ((x[:, at], x_exp), (g[at], gate_exp), (u[at], up_exp), (d, down_exp)):
+        t.ldexp_(torch.tensor(e, device="cuda"))
+    zero, dead = rows // 2, 7  # a row of zeros among the others, an output that only zero weights go into
+    x[zero] = 0
+    g[:, dead] = u[:, dead] = 0
+    packed = pack_expert(g, u, d)
+    L.set_expert_weights([packed[0]] * 2, [packed[1]] * 2)
+    y = L.empty(2 * rows, H).fill_(-7.0)
+    L.expert_ffn(x, torch.tensor([0, rows, 2 * rows], dtype=torch.int32, device="cuda"), 2 * rows, out=(y, None))
+    # h is held in fp32, like the kernel's: its denormal values are what the down projection is given
+    h = (torch.nn.functional.silu(x.double() @ g.double()) * (x.double() @ u.double())).float().double()
+    ref = h @ d.double()
+    assert float(ref[1].norm()) > 0 and bool((y[zero] == 0).all())
+    scale = 2.0 ** -min(down_exp, 0)  # small outputs
+    y, ref = y.double() * scale, ref * scale
+    # sums of up to 1024 fp32 products, each rounded by 2^-24 of a partial sum: 2^-24 sqrt(1024), in three products
+    assert float((y - ref).norm() / ref.norm()) < 3 * 2.0 ** -24 * max(H, I) ** 0.5
+    L.close()
+
+
 # The kernels that share the work by rows per slot give the same bits: a whole batch and its microbatches may take
 # different ones.  The same slots with other slots beside them: weights streamed, row-tiles of up to 256, of up to 320
 # rows; the shared expert in the same calls and alone.
