@@ -13,7 +13,10 @@
 // products up to K 2^-134 times the largest numbers of its two rows together.  Sums that are not 2^22 times as large, and
 // not of zeros, are worked out again in fp32 (redo); so are those that are not finite, since a number that rounds to no
 // finite bf16, or is not finite itself, makes its sums NaN.  With numbers in ordinary ranges neither occurs.  To know the
-// largest numbers costs 2 % (layer of 1001 tokens, H = 1024, I = 512, 32 experts: 169.6 -> 173.6 us).
+// largest numbers costs 2 % (layer of 1001 tokens, H = 1024, I = 512, 32 experts: 169.6 -> 173.6 us).  us of the FFN, H =
+// 1024, I = 512, 36 slots and a shared expert, 5 and 110 rows per slot: 58 and 240; one row of NaN 59 and 220, one infinity
+// 79 and 220, all NaN 69 and 267, all x of 2^-115 159 and 608 (v_mfma_f32_16x16x4_f32 throughout: 70 and 260 to 290).  The
+// sums in fp32 read their operands a row per lane, which is what they wait for; loads two groups ahead gained nothing.
 //
 // 64 x 64 outputs per workgroup of four wavefronts, each with all the tile's rows and 16 output columns (SwiGLU: 16 gate
 // and 16 up), so that a tile of few rows keeps every wavefront equally busy and skips the 16-row sub-tiles it has not
@@ -284,20 +287,55 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
         }
       if (row_begin + i * 16 + r16 < row_end && col < g.n_out) redo |= (fine ^ 15) << (i * 4);
     }
-    while (redo) {
-      const int o = __builtin_ctz(redo);
-      redo &= redo - 1;
-      const int row = row_begin + (o >> 2) * 16 + r16, n = col + (o & 3);
-      float sum[W];
-#pragma unroll
-      for (int s = 0; s < W; ++s) {
-        const float* x = g.A + static_cast<int64_t>(row) * g.lda;
-        const float* w = B + (static_cast<int64_t>(n) + s * g.n_out) * g.ldb;
-        sum[s] = 0.f;
+    // In fp32 then, 16 rows at a time where one of the wavefront's lanes asks for it: operands from memory, 16x16x4 MFMAs.
+    // Both operands permute K alike, as a lane's 16 bytes are four consecutive K-elements that feed four MFMAs.  A sum that
+    // is NaN stays it, and one row of NaN makes its sums NaN throughout: no further where nothing else is left.
+    const gptr w_row = base(B + min(n0 + wave * 16 + r16, g.n_out - 1) * g.ldb);
 #pragma unroll 1
-        for (int k = 0; k < g.K; ++k) sum[s] = fmaf(x[k], w[k], sum[s]);
+    for (int i = 0; i < TM; ++i) {
+      const uint32_t mine = redo >> (i * 4) & 15;
+      if (__ballot(mine != 0) == 0) continue;
+      const int row = row_begin + i * 16 + r16;
+      const gptr x_row = base(g.A + static_cast<int64_t>(min(row, row_end - 1)) * g.lda);
+      constexpr int U = 4;  // groups of 16 K-elements that are loaded together, each with sums of its own
+      f32x4 sum[U][W], all[W];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int s = 0; s < W; ++s) sum[u][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int k0 = 0; k0 < g.K; k0 += U * 16) {
+        f32x4 x[U], w[U][W];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {  // past the last K-element: zeros, not the last four again
+          const int64_t k = min(k0 + u * 16 + quad * 4, g.K - 4) * 4ll;
+          x[u] = *reinterpret_cast<gptr_f32x4>(x_row + k);
+#pragma unroll
+          for (int s = 0; s < W; ++s) w[u][s] = *reinterpret_cast<gptr_f32x4>(w_row + s * g.n_out * g.ldb * 4 + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = k0 + u * 16 + quad * 4 < g.K;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int s = 0; s < W; ++s) sum[u][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? w[u][s][j] : 0.f, in ? x[u][j] : 0.f, sum[u][s], 0, 0, 0);
+        }
+        bool open = false;
+#pragma unroll
+        for (int s = 0; s < W; ++s) all[s] = (sum[0][s] + sum[1][s]) + (sum[2][s] + sum[3][s]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) open |= (mine >> r & 1) && !(isnan(all[0][r]) || isnan(all[W - 1][r]));
+        if (__ballot(open) == 0) break;
       }
-      g.C[static_cast<int64_t>(row) * g.ldc + n] = SWIGLU ? sum[0] / (1.0f + expf(-sum[0])) * sum[W - 1] : sum[0];
+      f32x4 v = all[0];
+      if (SWIGLU) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = v[r] / (1.0f + expf(-v[r])) * all[W - 1][r];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (mine >> r & 1) g.C[static_cast<int64_t>(row) * g.ldc + col + r] = v[r];
     }
   };
   if (rows <= 16) run(std::integral_constant<int, 1>{});
