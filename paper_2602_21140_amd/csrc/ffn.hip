@@ -11,6 +11,7 @@
 // slot), or the workgroup works it out from slot_offsets itself (row_tiles.hpp).
 #include <algorithm>
 
+#include "ffn_rules.hpp"
 #include "gemm_bf16.hpp"
 #include "gemm_f32_split.hpp"
 #include "gemm_stream.hpp"
@@ -167,25 +168,9 @@ int bf16_ffn(revive_ctx* ctx, const Bf16Ffn& f0, const Bf16Ffn* f1, hipStream_t 
                                                                     f1 ? f1->max_m_tiles : 0, stream);
 }
 
-// Which problems take the streaming kernel (gemm_stream.hpp).  Up to 96 routed rows per slot on average the
-// weights dominate and it wins whatever the load's shape: against the 256-row-tile kernel, H = 7168, I = 2048,
-// 288 slots, whole layer: 5 rows 4.31 -> 3.80 ms, 28 uneven rows 4.38 -> 3.99, 42 rows 4.71 -> 4.44, 89 rows
-// 5.17 -> 4.87; at 114 rows a slot often needs a second row-tile of 128 and it loses (5.70 -> 5.89).  The
-// shared expert's rows go along in the same launches (k = 1, 8192 tokens: 5.16 -> 4.85) unless they are many and
-// weigh more than the slots (takes_stream).
 // Alone, the shared expert streams up to 128 tokens (H = 7168, I_shared = 2048, 1 token 76 -> 29 us, 128 tokens 98 ->
 // 56; more have not been compared).
-// Weights that the 256 MB last-level cache holds come in faster than HBM streams; above 16 rows per slot the
-// streaming kernel's set-up then costs more than it saves (141 MB, 61 rows: 84 -> 88 us; 27 MB, 20 rows: 58 ->
-// 59; 226 MB, 40 rows: 108 -> 104; 113 MB, 14 rows: 71 -> 65).
-constexpr int kStreamRowsPerSlot = 96, kStreamRowsPerSlotCached = 16;
-constexpr int64_t kCachedWeights = 192ll << 20;
 constexpr int kStreamDenseRows = 128;
-
-// A streaming workgroup looks its row-tile up in all slots' offsets; the 256-row kernel has a list.
-constexpr int kStreamSlotsCached = 640, kStreamSlots = 768;
-
-bool weights_cached(const revive_ctx* ctx) { return static_cast<int64_t>(ctx->P) * 6 * ctx->cfg.H * ctx->cfg.I <= kCachedWeights; }
 
 // One FFN call: routed experts, shared expert, or both.
 struct FfnArgs {
@@ -194,32 +179,6 @@ struct FfnArgs {
   const void* x; const void* w_sh_gate_up; const void* w_sh_down; void* h_shared; void* y_shared;
   int T;  // tokens of the shared expert; 0 = none
 };
-
-bool takes_stream(const revive_ctx* ctx, const FfnArgs& f) {
-  const revive_config& c = ctx->cfg;
-  const bool cached = weights_cached(ctx);
-  if (f.N > static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * ctx->P) return false;
-  // With many slots that search costs more than it saves where a workgroup has little to stream: the figures are of a
-  // search twice as long as today's, with which streaming wins further out than these lines.  us of the 256-row
-  // kernel and streamed: cached, 1000 slots, H = 256, I = 128, 4 rows per slot 54 and 73, 16 rows 57 and 64.  Geometric
-  // mean of the gain over random layers.  Cached: up to 64 rows in all, 513 to 640 slots 1.00, to 768 0.91, beyond
-  // 0.78; more than 256 rows, to 768 slots 1.05, beyond 0.90.  Larger weights beyond 768 slots: up to 64 rows, products
-  // of 640 columns and less 0.88, more 1.18; more rows, 128 K-elements and less in one of the products 0.84 to 0.95
-  // (but I = 64 1.03: half of the other kernel's columns are idle then), more 1.05 to 1.15.
-  if (cached && (ctx->P > kStreamSlots || (ctx->P > kStreamSlotsCached && f.N <= 256))) return false;
-  if (ctx->P > kStreamSlots && f.N <= 256 && std::max(c.H, c.I) <= 640) return false;
-  if (ctx->P > kStreamSlots && f.N > 64 && std::min(c.H, c.I) <= 128 && c.I > 64) return false;
-  // Every 128 rows of the shared expert read its weights once more.  That loses against the 256-row kernel once they
-  // are many rows and what is read that way outweighs the slots' weights, sooner where the cache does not hold the
-  // shared expert.  288 slots, H = 7168, I = 2048, one row per token, ms of the 256-row kernel and streamed:
-  // I_shared = 9 I, 2048 tokens 5.60 and 5.40, 4096 (as much as the slots) 6.65 and 7.17, 27 648 21.8 and 30.5;
-  // 2 I (cached), 27 648 tokens (1.5 times the slots) 8.70 and 8.71.  Share of 1500 random layers that lose: up to
-  // 1024 tokens none; above, uncached, from the slots' weights on 66 %; cached, up to 4096 tokens 9 %, above 3 % up to
-  // twice the slots' weights and 54 % from there on.
-  const bool shared_cached = 6ll * c.H * c.I_shared <= kCachedWeights;
-  if (f.T <= (shared_cached ? 4096 : 1024)) return true;
-  return static_cast<int64_t>(ceil_div(f.T, 128)) * c.I_shared < static_cast<int64_t>(shared_cached ? 2 : 1) * ctx->P * c.I;
-}
 
 // The FFN of few rows per slot: two launches of the streaming kernel.
 template <int TMX, int W, int D, int NW, int EPI, int KID>
@@ -263,36 +222,15 @@ int stream_ffn_as(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
 
 // Routed experts, with the shared expert or without.
 template <int K_GATE_UP, int K_DOWN>
-int stream_ffn(revive_ctx* ctx, const FfnArgs& f, hipStream_t stream) {
-  const revive_config& c = ctx->cfg;
-  const int64_t used = f.N < ctx->P ? f.N : ctx->P;  // slots that can hold a row
-  const int64_t blocks = (used + (f.T > 0)) * ceil_div(c.I, stream_tile_n<2, 4, EPI_SWIGLU>);  // of gate/up, 64 columns each
-  // us of the FFN with other data in the caches, both sides on the same weights in one process (from one process to the next
-  // they differ by 4 %), layers of 72 slots, H = 2048, I = 1408 (m), 144, 4096, 1024 (q), 72, 1024, 512 (s), 288, 7168, 2048
-  // (d), 160, 5120, 1536 (u).
-  //
-  // Above 20 rows per slot some slots hold more than 64 and row-tiles of 128 then read those slots' weights once, at one
-  // workgroup less per CU; and where many rows of the shared expert would read its weights a quarter as often as the slots
-  // read theirs.  Tiles of 128 and of 64: 5.3 rows d 3935 and 3856, q 551 and 544; 8.3 rows q 580 and 551, s 70 and 58; 16.7
-  // rows m 249 and 240, q 590 and 570; 25 rows m 256 and 249; 33 rows q 624 and 635; 66.7 rows m 292 and 351.  Where they
-  // leave a quarter of the CUs without work and the cache holds the weights, which may then be read again, the small tiles
-  // are better: 16 rows per slot, 32 slots, H = 2048, I = 448 (128 workgroups) 41 and 35.  One or two tiles of 128 columns
-  // cover a narrow expert exactly and read its activations half as often (I = 128, 18.2 rows 250 and 279, 256, 10.1 rows 279
-  // and 299, but 192, 18 rows 248 and 231): there from 8 rows on.
-  const int rows_128 = c.I % 128 == 0 && c.I < 512 ? 8 : 20;
-  const int dense = ceil_div(f.T, 128);
-  if (f.N > rows_128 * ctx->P || (f.T > 128 && 8ll * dense * c.I_shared > used * c.I)) {
-    const int64_t gate_up = used * ceil_div(c.I, stream_tile_n<4, 4, EPI_SWIGLU>) + dense * ceil_div(c.I_shared, stream_tile_n<4, 4, EPI_SWIGLU>);
-    const int64_t down = (used + dense) * ceil_div(c.H, stream_tile_n<4, 4, EPI_BF16>);
-    if (!weights_cached(ctx) || (gate_up >= 192 && down >= 192)) return stream_ffn_as<8, 4, 2, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+int stream_ffn(revive_ctx* ctx, const FfnArgs& f, const FfnSizes& sizes, hipStream_t stream) {
+  static_assert(stream_tile_n<4, 4, EPI_SWIGLU> == 128 && stream_tile_n<4, 4, EPI_BF16> == 256 && stream_tile_n<2, 4, EPI_SWIGLU> == 64 &&
+                stream_tile_n<2, 2, EPI_SWIGLU> == 32, "the columns that stream_form() counts");
+  switch (stream_form(sizes)) {
+    case k128x128: return stream_ffn_as<8, 4, 2, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+    case k64x64: return stream_ffn_as<4, 2, 4, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+    case k64x32: break;
   }
-  // Fewer than two workgroups per CU: half as large ones spread the streams evenly over the CUs, and a CU alone does not
-  // pull more than about 38 GB/s from HBM (one token, 288 -> 576 workgroups: 110 -> 95 us).  Up to four where the products
-  // are long: m 0.3 rows (550) 99 and 87; d 0.1 rows (544) 281 and 255; u 0.1 rows (600) 202 and 195; but H = 3840, I =
-  // 768, 0.7 rows (672) 98 and 102, H = 1920, I = 192 (648) 63.5 and 65.3, and d 0.1 rows (1056) 447 and 458.  How full the last
-  // round is moves either by 5 %: H = 6848, I = 1920, 36 slots, 6 tokens 174 and 155, 10 tokens 204 and 206, uneven 188 and 197.
-  if (blocks < 512 || (blocks < 1024 && std::min(c.H, c.I) >= 512 && c.H <= 4 * c.I)) return stream_ffn_as<4, 2, 4, 2, K_GATE_UP, K_DOWN>(ctx, f, stream);
-  return stream_ffn_as<4, 2, 4, 4, K_GATE_UP, K_DOWN>(ctx, f, stream);
+  return stream_ffn_as<4, 2, 4, 2, K_GATE_UP, K_DOWN>(ctx, f, stream);
 }
 
 // fp32: the routed and the shared experts in the same two launches.
@@ -343,7 +281,8 @@ int launch_expert_ffn(revive_ctx* ctx, const void* x_perm, const int32_t* slot_o
   const FfnArgs f{x_perm, slot_offsets, w_gate_up, w_down, ctx->d_ws + ctx->ws.off_h, y_perm, static_cast<int>(N),
                   x, w_sh_gate_up, w_sh_down, ctx->d_ws + ctx->ws.off_h_shared, y_shared, y_shared ? T : 0};
   if (c.dtype != REVIVE_DTYPE_BF16) return f32_ffn<GU, DN>(ctx, f, stream);
-  if (takes_stream(ctx, f)) return stream_ffn<GU, DN>(ctx, f, stream);
+  const FfnSizes sizes{ctx->P, c.H, c.I, c.I_shared, N, f.T};
+  if (takes_stream(sizes)) return stream_ffn<GU, DN>(ctx, f, sizes, stream);
   MTile* tiles = reinterpret_cast<MTile*>(ctx->d_ws + ctx->ws.off_tiles);
   int32_t* tile_count = reinterpret_cast<int32_t*>(ctx->d_ws + ctx->ws.off_tile_count);
   // a row-tile per slot and 256 rows of the shared expert, times the column tiles of each launch

@@ -30,10 +30,13 @@ CASES = {
     "sub_tiles": (256, 192, SUB_TILES), "sub_tiles_tall": (1088, 448, SUB_TILES),
     # slots of many row-tiles, which a common height would leave with a row or a sub-tile in the last; the same streamed
     "many_tiles": (256, 192, [4097, 3601, 513, 0, 1]), "many_tiles_streamed": (704, 320, [4097, 1041] + [0] * 330),
-    # half the columns up to 1024 workgroups, tiles of 64 rows above 8 rows per slot, of 128 above 20, and for many rows of the shared expert
+    # half the columns up to 1024 workgroups, tiles of 64 rows above 8 rows per slot, of 128 above 20 (12 where they are many),
+    # and for many rows of the shared expert; narrow experts, with few workgroups and cached weights and with many
     "half_columns": (1024, 1024, [1, 0, 63, 64, 65] + [2] * 32), "tiles_of_64": (2048, 576, [129, 64, 65, 1, 17] + [9] * 25),
-    "tiles_of_128": (2048, 576, [129, 128, 127, 257, 1] + [17] * 25),
-    "rows_shared": (1024, 1024, [140, 3] + [1] * 32 + [0] * 4),
+    "tiles_of_64_wide": (2368, 576, [129, 64, 65, 1, 17] + [9] * 52), "tiles_of_128": (2048, 576, [129, 128, 127, 257, 1] + [17] * 25),
+    "tiles_of_128_many": (1344, 960, [129, 128, 127, 257, 1] + [8] * 91),
+    "rows_shared": (1024, 1024, [300, 100, 65, 20] + [1] * 35),
+    "small_tiles_narrow": (704, 256, [130, 65, 64, 1, 0, 16, 3] + [0] * 13), "tiles_of_128_narrow": (1024, 128, [129, 128, 257, 1] + [6] * 188),
     "one_row": (448, 128, [0] * 7 + [1] + [0] * 56),
     "few": (256, 320, [5, 1, 0, 8, 3, 16, 2, 7] * 8),
     "many_slots": (128, 64, ([0, 2, 1, 65] + [0] * 12) * 60),
