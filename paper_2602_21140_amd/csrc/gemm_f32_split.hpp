@@ -13,7 +13,7 @@
 // products up to K 2^-134 times the largest numbers of its two rows together.  Sums that are not 2^22 times as large, and
 // not of zeros, are worked out again in fp32 (redo); so are those that are not finite, since a number that rounds to no
 // finite bf16, or is not finite itself, makes its sums NaN.  With numbers in ordinary ranges neither occurs.  To know the
-// largest numbers costs 2 % (layer of 1001 tokens, H = 1024, I = 512, 32 experts: 169.6 -> 173.6 us).  us of the FFN, H =
+// largest numbers costs 2 % (layer of 1001 tokens, H = 1024, I = 512, 32 experts: 171.6 -> 174.5 us).  us of the FFN, H =
 // 1024, I = 512, 36 slots and a shared expert, 5 and 110 rows per slot: 58 and 240; one row of NaN 59 and 220, one infinity
 // 79 and 220, all NaN 69 and 267, all x of 2^-115 159 and 608 (v_mfma_f32_16x16x4_f32 throughout: 70 and 260 to 290).  The
 // sums in fp32 read their operands a row per lane, which is what they wait for; loads two groups ahead gained nothing.
@@ -118,9 +118,9 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = in ? v[j] : 0.f;
       }
-      // fmaxf() would first quieten its operands, twice the instructions
-      asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top[u]) : "v"(v[0]), "v"(v[1]));
-      asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top[u]) : "v"(v[2]), "v"(v[3]));
+      // not fmaxf(), which would first quieten its operands
+#pragma unroll
+      for (int j = 0; j < 4; ++j) top[u] = __builtin_elementwise_maximum(top[u], fabsf(v[j]));
       unsigned char* dst = lds[buf] + put + (u < NA ? u * (32 * 64) : BM * 64 + (u - NA) * (32 * 64));
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
@@ -207,10 +207,7 @@ __global__ __launch_bounds__(256, SWIGLU ? 2 : 3) void gemm_f32_split_kernel(Gem
     auto share_largest = [&]() {
       int m[WORDS];  // not negative: in the order of the numbers
 #pragma unroll
-      for (int u = 0; u < WORDS; ++u) {
-        m[u] = __float_as_int(top[u]);
-        asm volatile("s_nop 1" : "+v"(m[u]));  // two wait states between the v_max3 above, of which the compiler may not know, and the lanes' exchange
-      }
+      for (int u = 0; u < WORDS; ++u) m[u] = __float_as_int(top[u]);
       // the eight threads of a row: lanes ^ 1, ^ 2 and 7 - lane
 #pragma unroll
       for (int u = 0; u < WORDS; ++u) m[u] = max(m[u], dpp_or_zero<0xB1, 0xF>(m[u]));
