@@ -16,6 +16,7 @@ import torch
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "librevive.so"
 _lib = None
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # private to torch: another one may not have it
 
 SCORE_FN = {"softmax": 0, "sigmoid": 1}
 DTYPE = {"fp32": 0, "bf16": 1}
@@ -261,9 +262,11 @@ class ReviveLayer:
     def _stream(stream: Optional[torch.cuda.Stream]) -> int:
         if stream is not None:
             return stream.cuda_stream
-        # the current device's current stream, without the Stream object that torch.cuda.current_stream() makes: that took
-        # 2.6 us of each call, half of an eager step of few tokens (64 tokens, H = 256, fp32: 33 -> 24 us)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        # without the Stream object that torch.cuda.current_stream() makes: that took 2.6 us of each of the four calls of an
+        # eager step (64 tokens, H = 256, fp32: 33 -> 24 us)
+        return _raw_stream(torch.cuda.current_device())
 
     def close(self):
         if self._ctx:

@@ -468,9 +468,13 @@ def test_a_masked_expert_with_a_towering_logit_leaves_the_weights_finite(name):
         g.close()
 
 
-def test_calls_without_a_stream_take_the_current_one():
-    from paper_2602_21140_amd import ReviveLayer
+@pytest.mark.parametrize("raw", [True, False])  # False: a torch without the private function for it
+def test_calls_without_a_stream_take_the_current_one(raw, monkeypatch):
+    from paper_2602_21140_amd import ReviveLayer, binding
 
+    if not raw:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+        monkeypatch.setattr(binding, "_raw_stream", None)
     side = torch.cuda.Stream()
     assert ReviveLayer._stream(None) == torch.cuda.current_stream().cuda_stream
     with torch.cuda.stream(side):
