@@ -22,7 +22,7 @@ CASES = {
     "tiles": (704, 320, EDGES + [3] * 10),  # above, at this size, the 256-row tiles
     # one row-tile up to 320 rows, from the shortest K to several turns of the ring
     "tall": (256, 192, TALL), "tall_short_k": (64, 64, TALL), "tall_long_k": (1088, 448, TALL),
-    # few workgroups and cached weights: row-tiles of 64 above 8 rows per slot and beside many rows of the shared expert
+    # few workgroups and cached weights: row-tiles of 64 also beside many rows of the shared expert
     "small_tiles": (704, 320, [130, 65, 64, 1, 0, 16, 3] + [0] * 13),
     # the same with enough workgroups for tall tiles
     "tall_many_short_k": (64, 64, TALL * 12), "tall_many": (192, 320, TALL * 12), "tall_wide": (2880, 1472, TALL),
@@ -187,9 +187,9 @@ def test_fp32_parts_and_numbers_without_parts(H, I, rows):
         return (torch.nn.functional.silu(z) * w) @ d.double()
 
     plain, ref = run(), reference()
-    # a K-step rounds each sum once, by 2^-24 at most, in each of three products, which a small I does not average over
-    bound = 2.0 ** -24 * ((H + 31) // 32) ** 0.5 * 3
-    assert float((plain - ref).norm() / ref.norm()) < max(bound, 4e-7)
+    # a K-step rounds the leading sum once, by 2^-24 of it at most, in one direction or the other; h and y are rounded once
+    # more.  Measured: 0.6e-7 to 3.6e-7; with all six products in one sum twice as much.
+    assert float((plain - ref).norm() / ref.norm()) < 2.0 ** -24 * (1 + ((H + 31) // 32) ** 0.5)
     largest, nan = rows // 2, rows + rows // 2
     x[largest, 5] = torch.finfo(torch.float32).max  # no finite bf16 is as large; times 2e-38 it is an ordinary number
     x[nan, 7] = float("nan")
