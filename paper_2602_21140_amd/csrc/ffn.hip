@@ -9,8 +9,6 @@
 // cover floor(N / tile) + P row-tiles, and workgroups beyond the last one exit at once.  Which rows a
 // workgroup owns comes from a list that a small kernel makes of slot_offsets (bf16, many rows per
 // slot), or the workgroup works it out from slot_offsets itself (row_tiles.hpp).
-#include <algorithm>
-
 #include "ffn_rules.hpp"
 #include "gemm_bf16.hpp"
 #include "gemm_f32_split.hpp"

@@ -29,13 +29,11 @@ inline bool weights_cached(const FfnSizes& f) { return static_cast<int64_t>(f.P)
 inline bool takes_stream(const FfnSizes& f) {
   const bool cached = weights_cached(f);
   if (f.N > static_cast<int64_t>(cached ? kStreamRowsPerSlotCached : kStreamRowsPerSlot) * f.P) return false;
-  // With many slots that search costs more than it saves where a workgroup has little to stream: the figures are of a
-  // search twice as long as today's, with which streaming wins further out than these lines.  us of the 256-row
-  // kernel and streamed: cached, 1000 slots, H = 256, I = 128, 4 rows per slot 54 and 73, 16 rows 57 and 64.  Geometric
-  // mean of the gain over random layers.  Cached: up to 64 rows in all, 513 to 640 slots 1.00, to 768 0.91, beyond
-  // 0.78; more than 256 rows, to 768 slots 1.05, beyond 0.90.  Larger weights beyond 768 slots: up to 64 rows, products
-  // of 640 columns and less 0.88, more 1.18; more rows, 128 K-elements and less in one of the products 0.84 to 0.95
-  // (but I = 64 1.03: half of the other kernel's columns are idle then), more 1.05 to 1.15.
+  // With many slots a search that took twice as long cost more than it saved where a workgroup has little to stream, and
+  // the lines were drawn for it.  Today's costs less than the lines allow for; they have not been moved.  Time of the 256-row
+  // kernel over time streamed, other data in the caches, 400 random layers: cached, 513 to 768 slots 1.45, beyond 1.37 (at
+  // least 1.06); larger weights beyond 768 slots, up to 256 rows in all and products of up to 640 columns 1.47, more than 64
+  // rows and up to 128 K-elements in one of the products 1.14 (least 0.87: P = 1000, H = 128, I = 320, 921 rows 66 and 76 us).
   if (cached && (f.P > kStreamSlots || (f.P > kStreamSlotsCached && f.N <= 256))) return false;
   if (f.P > kStreamSlots && f.N <= 256 && std::max(f.H, f.I) <= 640) return false;
   if (f.P > kStreamSlots && f.N > 64 && std::min(f.H, f.I) <= 128 && f.I > 64) return false;
